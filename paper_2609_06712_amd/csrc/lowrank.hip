@@ -24,6 +24,7 @@
 // summary's is dealt round-robin (measured faster for it).
 #include "common.h"
 #include "launch.h"
+#include "reduce.h"
 
 namespace rola {
 namespace {
@@ -412,30 +413,6 @@ __global__ __launch_bounds__(256) void summary_simple_kernel(
     if (e < r * D) P[e] = acc[i];
   }
   if (threadIdx.x < r) P[(long)r * D + threadIdx.x] = zacc;
-}
-
-// C, z = sum over chunks in chunk order (fixed order: reproducible).
-__global__ __launch_bounds__(256) void summary_reduce_kernel(int rd, int r, int n_chunks,
-                                                             const float* __restrict__ part,
-                                                             float* __restrict__ C,
-                                                             float* __restrict__ z) {
-  const long head = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int per = rd + r;
-  if (e >= per) return;
-  const float* P = part + head * n_chunks * (long)per + e;
-  // chunk order kept; the loads of a batch are all issued before the first add
-  constexpr int kBatch = 8;
-  float s = 0.f;
-  for (int c0 = 0; c0 < n_chunks; c0 += kBatch) {
-    float v[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) v[u] = P[(long)min(c0 + u, n_chunks - 1) * per];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) s = c0 + u < n_chunks ? s + v[u] : s;
-  }
-  if (e < rd) C[head * rd + e] = s;
-  else if (z) z[head * r + (e - rd)] = s;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -881,9 +858,7 @@ hipError_t launch_lowrank_summary(const Shape& s, const void* Kn, const void* V,
   }
   if (e != hipSuccess) return e;
   const int per = r * s.d + r;
-  hipLaunchKernelGGL(summary_reduce_kernel, dim3((per + 255) / 256, s.B * s.H), dim3(256), 0, st,
-                     r * s.d, r, n_chunks, part, C, z);
-  return hipGetLastError();
+  return launch_chunk_reduce(per, r * s.d, per, 1, s.B * s.H, n_chunks, part, C, z, st);
 }
 
 hipError_t launch_lowrank_readout(const Shape& s, const void* Qn, const void* Pq, int r,

@@ -16,6 +16,7 @@
 // every gradient is reproducible. fp32 arithmetic from bf16 inputs, r <= 64.
 #include "common.h"
 #include "launch.h"
+#include "reduce.h"
 
 namespace rola {
 namespace {
@@ -25,28 +26,6 @@ constexpr int kD = 128, kMaxR = 64;
 __device__ __forceinline__ float silu_grad(float y) {  // d/dy y sigmoid(y)
   const float s = sigmoid(y);
   return s * (1.f + y * (1.f - s));
-}
-
-// Partials part[(b * H + h) * n_chunks + c][e] summed in a fixed order (batch entries, then chunks):
-// per_head = true: out[(b * H + h)][e] over c; per_head = false: out[h][e] over (b, c).
-__global__ __launch_bounds__(256) void lr_bwd_reduce_kernel(int re, int B, int H, int n_chunks,
-                                                            bool per_head,
-                                                            const float* __restrict__ part,
-                                                            float* __restrict__ out) {
-  const long o = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= re) return;
-  float s = 0.f;
-  if (per_head) {
-    const float* src = part + o * n_chunks * (long)re + e;
-    for (int c = 0; c < n_chunks; ++c) s += src[(long)c * re];
-  } else {
-    for (int b = 0; b < B; ++b) {
-      const float* src = part + ((long)b * H + o) * n_chunks * (long)re + e;
-      for (int c = 0; c < n_chunks; ++c) s += src[(long)c * re];
-    }
-  }
-  out[o * re + e] = s;
 }
 
 // ---- MFMA path (r <= 64) ---------------------------------------------------------------------
@@ -483,7 +462,6 @@ hipError_t launch_lowrank_backward(const Shape& s, const void* Qn, const void* K
   float* dlog_h = (float*)(w + 3 * lay.part);
   float* dC = (float*)(w + 3 * lay.part + lay.dlog);
   const int re = r * kD;
-  const dim3 rgrid((re + 255) / 256, 1);
   const dim3 grid((unsigned)(heads * n_chunks));
   const LrBwdArgs q{s.N, s.H, r, chunk_len, n_chunks, ld, (const bf16*)Qn, (const bf16*)Pq,
                     cos_tab, sin_tab, C, (const bf16*)Os, logits, eps_lr, eps, (const bf16*)dO,
@@ -492,9 +470,11 @@ hipError_t launch_lowrank_backward(const Shape& s, const void* Qn, const void* K
     hipLaunchKernelGGL((lr_bwd_mfma_kernel<false, 1>), grid, dim3(256), 0, st, q);
   else
     hipLaunchKernelGGL((lr_bwd_mfma_kernel<false, 2>), grid, dim3(256), 0, st, q);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   // dC[b, h] = sum over chunks
-  hipLaunchKernelGGL(lr_bwd_reduce_kernel, dim3(rgrid.x, (unsigned)heads), dim3(256), 0, st, re, s.B,
-                     s.H, n_chunks, true, (const float*)part_dC, dC);
+  e = launch_chunk_reduce(re, re, re, 1, (int)heads, n_chunks, part_dC, dC, nullptr, st);
+  if (e != hipSuccess) return e;
   const LrBwdArgs k{s.N, s.H, r, chunk_len, n_chunks, ld, (const bf16*)Kn, (const bf16*)Pk,
                     cos_tab, sin_tab, dC, nullptr, nullptr, 0.f, 0.f, (const bf16*)V, nullptr,
                     dKn, dV, nullptr, nullptr, part_dPk};
@@ -502,11 +482,13 @@ hipError_t launch_lowrank_backward(const Shape& s, const void* Qn, const void* K
     hipLaunchKernelGGL((lr_bwd_mfma_kernel<true, 1>), grid, dim3(256), 0, st, k);
   else
     hipLaunchKernelGGL((lr_bwd_mfma_kernel<true, 2>), grid, dim3(256), 0, st, k);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
   // dP_q[h], dP_k[h] = sum over (b, chunk)
-  hipLaunchKernelGGL(lr_bwd_reduce_kernel, dim3(rgrid.x, (unsigned)s.H), dim3(256), 0, st, re, s.B,
-                     s.H, n_chunks, false, (const float*)part_dPq, dPq);
-  hipLaunchKernelGGL(lr_bwd_reduce_kernel, dim3(rgrid.x, (unsigned)s.H), dim3(256), 0, st, re, s.B,
-                     s.H, n_chunks, false, (const float*)part_dPk, dPk);
+  e = launch_chunk_reduce(re, re, re, s.B, s.H, n_chunks, part_dPq, dPq, nullptr, st);
+  if (e != hipSuccess) return e;
+  e = launch_chunk_reduce(re, re, re, s.B, s.H, n_chunks, part_dPk, dPk, nullptr, st);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(lr_bwd_logit_kernel, dim3((unsigned)(((long)s.B * s.N + 255) / 256)),
                      dim3(256), 0, st, (long)s.B * s.N, s.N, s.H, (const float*)dlog_h, dlogits);
   return hipGetLastError();

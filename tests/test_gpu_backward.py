@@ -235,6 +235,29 @@ def test_gate_backward():
     assert float(dbg.cpu()) == pytest.approx(want["dbg"], rel=1e-5)
 
 
+@pytest.mark.parametrize("dtype,B,N,dm", [("bf16", 1, 1, 8), ("bf16", 1, 513, 136), ("f32", 2, 700, 2056),
+                                          ("bf16", 1, 5003, 640), ("bf16", 1, 131, 5120)])
+def test_gate_backward_edges(dtype, B, N, dm):
+    """One row, ragged row chunks, every column tile width (16 to 256 columns of eight channels) and
+    few / many chunk partials. Every sum is fp32 over B N terms, in whatever order: its error is at
+    most B N 2^-24 sum |term|."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(N + dm)
+    X = torch.randn((B, N, dm), generator=gen).to(tdt)
+    Wg = (torch.randn((dm,), generator=gen) / dm ** 0.5).to(tdt)
+    dl = torch.randn((B, N), generator=gen)
+    dX, dWg, dbg = R.rola_gate_logits_backward(X.cuda(), Wg.cuda(), dl.cuda(), (N, 1, 1))
+    none, dWg2, _ = R.rola_gate_logits_backward(X.cuda(), Wg.cuda(), dl.cuda(), (N, 1, 1), want_dX=False)
+    torch.cuda.synchronize()
+    Xf, df = X.double().numpy().reshape(-1, dm), dl.double().numpy().ravel()
+    want = G.gate_grads(Xf, Wg.double().numpy(), df)
+    assert none is None and torch.equal(dWg, dWg2)
+    np.testing.assert_allclose(_f64(dX).reshape(-1, dm), want["dX"], rtol=2.0 ** -23)
+    u = B * N * 2.0 ** -24
+    assert np.all(np.abs(_f64(dWg) - want["dWg"]) <= u * (np.abs(df) @ np.abs(Xf)) + 1e-30)
+    assert abs(float(dbg.cpu()) - want["dbg"]) <= u * np.abs(df).sum()
+
+
 @pytest.mark.parametrize("grid,s", [((3, 10, 13), 0.5), ((4, 8, 16), 0.75)])
 def test_module_backward(grid, s):
     """The composed backward (paper_2609_06712_amd.train) against fp64 autograd of the whole module,
