@@ -176,33 +176,56 @@ __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
     for (int ct = 0; ct < 2; ++ct) accm[rt][ct] = accp[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();
 
+  // A step's inputs are loaded one step ahead: the step is one long dependent chain per wave with
+  // one or two waves per SIMD, so nothing else would cover the memory latency. Tokens past the chunk
+  // re-read its last one and are zeroed where they are used.
+  struct StepIn {
+    bf16x8 x[4], y[4], o[KEY ? 1 : 4];
+    float4 c[JT], s[JT];  // cos / sin of the lane's pairs 16 jt + 4g + v
+    float lg;
+  };
   const int t0 = chunk * a.chunk_len, t1 = min(a.N, t0 + a.chunk_len);
+  const int trow = 16 * wave + lr;  // this lane's token row in the step tiles
+  auto load_step = [&](int base, StepIn& in) {
+    const int tok = min(base + trow, t1 - 1);
+    const long row = (head * a.N + tok) * D + 8 * g;
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) {
+      in.x[kc] = *reinterpret_cast<const bf16x8*>(a.X + row + 32 * kc);
+      in.y[kc] = *reinterpret_cast<const bf16x8*>(a.Y + row + 32 * kc);
+      if constexpr (!KEY) in.o[kc] = *reinterpret_cast<const bf16x8*>(a.Os + row + 32 * kc);
+    }
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) {
+      // pairs past r/2 re-read the last four (their features meet zero rows of P and M);
+      // j0 + 3 < ld: ld >= half and both are multiples of 4
+      const int j0 = min(16 * jt + 4 * g, half - 4);
+      in.c[jt] = *reinterpret_cast<const float4*>(a.cos_tab + (long)tok * a.ld + j0);
+      in.s[jt] = *reinterpret_cast<const float4*>(a.sin_tab + (long)tok * a.ld + j0);
+    }
+    if constexpr (!KEY) in.lg = a.logits[b * a.N + tok];
+  };
+  StepIn in;
+  load_step(t0, in);
   for (int base = t0; base < t1; base += kStep) {
-    const int trow = 16 * wave + lr;  // this lane's token row in the step tiles
     const int tok = base + trow;
     const bool valid = tok < t1;
     const long row = (head * a.N + tok) * D;
     bf16x8 xf[4], yv[4], ov[4];
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
-      xf[kc] = valid ? *reinterpret_cast<const bf16x8*>(a.X + row + 32 * kc + 8 * g) : bf16x8{};
-      yv[kc] = valid ? *reinterpret_cast<const bf16x8*>(a.Y + row + 32 * kc + 8 * g) : bf16x8{};
-      if (!KEY)
-        ov[kc] = valid ? *reinterpret_cast<const bf16x8*>(a.Os + row + 32 * kc + 8 * g) : bf16x8{};
+      xf[kc] = valid ? in.x[kc] : bf16x8{};
+      yv[kc] = valid ? in.y[kc] : bf16x8{};
+      if (!KEY) ov[kc] = valid ? in.o[kc] : bf16x8{};
     }
-    float cc[JT][4], ss[JT][4];  // cos / sin of the lane's pairs 16 jt + 4g + v
+    float cc[JT][4], ss[JT][4];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      float4 c4 = make_float4(1.f, 1.f, 1.f, 1.f), s4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      const int j0 = 16 * jt + 4 * g;
-      if (valid && j0 < half) {  // j0 + 3 < ld: ld >= half and both are multiples of 4
-        c4 = *reinterpret_cast<const float4*>(a.cos_tab + (long)tok * a.ld + j0);
-        s4 = *reinterpret_cast<const float4*>(a.sin_tab + (long)tok * a.ld + j0);
-      }
-      cc[jt][0] = c4.x, cc[jt][1] = c4.y, cc[jt][2] = c4.z, cc[jt][3] = c4.w;
-      ss[jt][0] = s4.x, ss[jt][1] = s4.y, ss[jt][2] = s4.z, ss[jt][3] = s4.w;
+      cc[jt][0] = in.c[jt].x, cc[jt][1] = in.c[jt].y, cc[jt][2] = in.c[jt].z, cc[jt][3] = in.c[jt].w;
+      ss[jt][0] = in.s[jt].x, ss[jt][1] = in.s[jt].y, ss[jt][2] = in.s[jt].z, ss[jt][3] = in.s[jt].w;
     }
-    const float lg = (!KEY && valid) ? a.logits[b * a.N + tok] : 0.f;
+    const float lg = (!KEY && valid) ? in.lg : 0.f;
+    load_step(min(base + kStep, t1 - 1), in);
 
     // Y^T and the features
     f32x4 ye[JT], yo[JT];
@@ -417,9 +440,13 @@ __global__ __launch_bounds__(256) void lr_bwd_logit_kernel(long BN, int N, int H
   dlogits[e] = s;
 }
 
+// Workgroups of each pass. The query side and the r > 32 key side hold one per CU, so this is four
+// whole rounds: each round stages P and M anew and leaves partials to add (14B 720p layer, r 64, whole
+// call: 4096 2.96 ms, 2048 2.84 ms, 1024 2.77 ms).
+constexpr long kLrBwdWorkgroups = 1024;
 int lr_bwd_chunk_len(const Shape& s) {
   const long heads = (long)s.B * s.H;
-  const long want = (4096 + heads - 1) / heads;  // about 4096 workgroups
+  const long want = heads < kLrBwdWorkgroups ? kLrBwdWorkgroups / heads : 1;
   long len = (s.N + want - 1) / want;
   len = (len + kStep - 1) / kStep * kStep;  // whole steps of the MFMA path
   return (int)(len < kStep ? kStep : len);
