@@ -73,6 +73,9 @@ hipError_t launch_sparse_attn(const Shape& s, const void* Qr, const void* Kr, co
                               int block, int keep, const int32_t* idx, float scale, void* Os,
                               void* ws, hipStream_t st, const LowrankFuse* lf = nullptr,
                               void* fuse_ws = nullptr, float* lse = nullptr, bool planned = false);
+// attn_f32.hip: the fp32 path of launch_sparse_attn (idx == nullptr: dense, keep == n_blocks).
+hipError_t launch_attn_f32(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
+                           int keep, const int32_t* idx, float scale, void* Os, hipStream_t st);
 // Whether the path of (s, block) uses a plan (pairs, merged lists, queue counters in ws).
 bool plan_used(const Shape& s, int block);
 // The pairing and list merge of the 64-token bf16 path into ws (sparse_workspace_bytes), for the

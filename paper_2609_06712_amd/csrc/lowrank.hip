@@ -347,72 +347,140 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plain summary for the fp32 path: 32-token sub-tiles through LDS, thread per (pair) then (r, c).
+// fp32 path, on v_mfma_f32_16x16x4_f32 (A: row l%16, k = l/16; B: column l%16, k = l/16; D: column l%16,
+// rows 4(l/16) + i). fp32 layers are small, so a call is a chain of latencies: scalar dot products per
+// (token, pair) took 32 us (summary) and 10 us (readout) at the tiny layer, 9 and 5 us now.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void summary_simple_kernel(
-    int N, int H, int r, int chunk_len, int n_chunks, int ld, int feat, const T* __restrict__ Kn,
-    const T* __restrict__ V, const T* __restrict__ Pk, const float* __restrict__ cos_tab,
-    const float* __restrict__ sin_tab, float* __restrict__ part) {
-  constexpr int TT = 32, MAXR = 128;
-  __shared__ float Ks[TT][D];
-  __shared__ float Vs[TT][D];
-  __shared__ float kt[TT][MAXR];
-  const int chunk = blockIdx.x;
-  const long head = (long)blockIdx.z * gridDim.y + blockIdx.y;
-  const int h = blockIdx.y;
-  const T* Kh = Kn + head * (long)N * D;
-  const T* Vh = V + head * (long)N * D;
-  const T* Ph = Pk + (long)h * r * D;
-  const int half = r / 2;
-  const int t0 = chunk * chunk_len, t1 = min(N, t0 + chunk_len);
-  constexpr int MAXE = MAXR * D / 256;
-  float acc[MAXE];
-  float zacc = 0.f;
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Features of pair tile jt (pairs 16 jt ..) for 16 tokens, lane = token l%16, pairs 16 jt + 4(l/16) + i:
+// Y^T = P X^T with contraction step s of lane group g = channel g D/4 + s, so that x (the lane's quarter
+// of its token row) and the rows of P are contiguous 16-byte pieces. Pairs past r/2 get zero features.
+template <int D>
+__device__ __forceinline__ void features_f32(const float* __restrict__ P, int r, int jt,
+                                             const float4 (&x)[D / 16], const float* cos_row,
+                                             const float* sin_row, int feat, int lane, float (&fe)[4],
+                                             float (&fo)[4]) {
+  const int lr = lane % 16, g = lane / 16, half = r / 2, j = 16 * jt + lr, jb = 16 * jt + 4 * g;
+  const float* pe = P + (long)(2 * min(j, half - 1)) * D + g * (D / 4);
+  f32x4 ye = {0.f, 0.f, 0.f, 0.f}, yo = {0.f, 0.f, 0.f, 0.f};
+  float4 e[D / 16], o[D / 16];
 #pragma unroll
-  for (int i = 0; i < MAXE; ++i) acc[i] = 0.f;
-  for (int b0 = t0; b0 < t1; b0 += TT) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < TT * D; e += 256) {
-      const int tr = e / D, c = e % D, tok = b0 + tr;
-      Ks[tr][c] = tok < t1 ? to_f32(Kh[(long)tok * D + c]) : 0.f;
-      Vs[tr][c] = tok < t1 ? to_f32(Vh[(long)tok * D + c]) : 0.f;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < TT * half; e += 256) {
-      const int tr = e / half, j = e % half, tok = b0 + tr;
-      float ae = 0.f, ao = 0.f;
-      for (int c = 0; c < D; ++c) {
-        ae = fmaf(to_f32(Ph[(long)(2 * j) * D + c]), Ks[tr][c], ae);
-        ao = fmaf(to_f32(Ph[(long)(2 * j + 1) * D + c]), Ks[tr][c], ao);
-      }
-      float cs = 1.f, sn = 0.f;
-      if (tok < t1) { cs = cos_tab[(long)tok * ld + j]; sn = sin_tab[(long)tok * ld + j]; }
-      feature_pair<true>(ae, ao, cs, sn, feat);
-      kt[tr][2 * j] = ae;
-      kt[tr][2 * j + 1] = ao;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MAXE; ++i) {
-      const int e = threadIdx.x + 256 * i;
-      if (e < r * D) {
-        const int ri = e / D, c = e % D;
-        float s = acc[i];
-        for (int tr = 0; tr < TT; ++tr) s = fmaf(kt[tr][ri], Vs[tr][c], s);
-        acc[i] = s;
-      }
-    }
-    if (threadIdx.x < r)
-      for (int tr = 0; tr < TT; ++tr) zacc += kt[tr][threadIdx.x];
+  for (int s = 0; s < D / 16; ++s) {
+    e[s] = *reinterpret_cast<const float4*>(pe + 4 * s);
+    o[s] = *reinterpret_cast<const float4*>(pe + D + 4 * s);
   }
+  // the tables' rows are whole 16-byte pieces: a piece that starts below half can be read
+  float4 c4 = make_float4(1.f, 1.f, 1.f, 1.f), s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (jb < half) {
+    c4 = *reinterpret_cast<const float4*>(cos_row + jb);
+    s4 = *reinterpret_cast<const float4*>(sin_row + jb);
+  }
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    ye = mfma_f32(e[s].x, x[s].x, ye);
+    yo = mfma_f32(o[s].x, x[s].x, yo);
+    ye = mfma_f32(e[s].y, x[s].y, ye);
+    yo = mfma_f32(o[s].y, x[s].y, yo);
+    ye = mfma_f32(e[s].z, x[s].z, ye);
+    yo = mfma_f32(o[s].z, x[s].z, yo);
+    ye = mfma_f32(e[s].w, x[s].w, ye);
+    yo = mfma_f32(o[s].w, x[s].w, yo);
+  }
+  const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = ye[i], b = yo[i];
+    feature_pair<true>(a, b, cc[i], ss[i], feat);
+    fe[i] = jb + i < half ? a : 0.f;
+    fo[i] = jb + i < half ? b : 0.f;
+  }
+}
+
+// Summary: per (b, h, token chunk) one workgroup, 64 tokens per step. Each wave computes the features of
+// 16 tokens and leaves them in LDS ([token][coordinate]); after a barrier each wave contracts all 64
+// tokens for its own quarter of the channels, C[coord][ch] += f[tok][coord] V[tok][ch], step s of lane
+// group g = token 4s + g, column n of channel tile t = channel w D/4 + n CT + t (contiguous V pieces).
+template <int D>
+__global__ __launch_bounds__(256) void summary_f32_kernel(
+    int N, int H, int r, int chunk_len, int n_chunks, int ld, int feat, const float* __restrict__ Kn,
+    const float* __restrict__ V, const float* __restrict__ Pk, const float* __restrict__ cos_tab,
+    const float* __restrict__ sin_tab, float* __restrict__ part) {
+  constexpr int TT = 64, RP = 128 + 4, CT = D / 64;
+  typedef float vvec __attribute__((ext_vector_type(CT)));
+  __shared__ __attribute__((aligned(16))) float ft[TT][RP];
+  __shared__ float zs[2][128];
+  const int chunk = blockIdx.x, h = blockIdx.y;
+  const long head = (long)blockIdx.z * gridDim.y + h;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_uniform(tid / 64);
+  const int lr = lane % 16, g = lane / 16;
+  const int JT = (r / 2 + 15) / 16, RT = (r + 15) / 16;
+  const float* Kh = Kn + head * (long)N * D;
+  const float* Vh = V + head * (long)N * D + wave * (D / 4) + lr * CT;
+  const float* Ph = Pk + (long)h * r * D;
+  const int t0 = chunk * chunk_len, t1 = min(N, t0 + chunk_len);
+  f32x4 acc[8][CT];
+#pragma unroll
+  for (int rt = 0; rt < 8; ++rt)
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float z = 0.f;  // thread: coordinate tid % 128, half the tokens of each step
+  for (int b0 = t0; b0 < t1; b0 += TT) {
+    // tokens past the chunk re-read its last one and get zero features
+    vvec v[TT / 4];
+#pragma unroll
+    for (int s = 0; s < TT / 4; ++s)
+      v[s] = *reinterpret_cast<const vvec*>(Vh + (long)min(b0 + 4 * s + g, t1 - 1) * D);
+    const int tok = b0 + 16 * wave + lr, tk = min(tok, t1 - 1);
+    float4 x[D / 16];
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+      x[s] = *reinterpret_cast<const float4*>(Kh + (long)tk * D + g * (D / 4) + 4 * s);
+    for (int jt = 0; jt < JT; ++jt) {
+      float fe[4], fo[4];
+      features_f32<D>(Ph, r, jt, x, cos_tab + (long)tk * ld, sin_tab + (long)tk * ld, feat, lane, fe, fo);
+      if (tok >= t1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fe[i] = fo[i] = 0.f;
+      }
+      float4* dst = reinterpret_cast<float4*>(&ft[16 * wave + lr][32 * jt + 8 * g]);
+      dst[0] = make_float4(fe[0], fo[0], fe[1], fo[1]);
+      dst[1] = make_float4(fe[2], fo[2], fe[3], fo[3]);
+    }
+    __syncthreads();
+    if (tid % 128 < r) {
+#pragma unroll 8
+      for (int t = 0; t < TT / 2; ++t) z += ft[TT / 2 * (tid / 128) + t][tid % 128];
+    }
+#pragma unroll
+    for (int rt = 0; rt < 8; ++rt) {
+      if (rt >= RT) break;
+#pragma unroll
+      for (int s = 0; s < TT / 4; ++s) {
+        const float a = ft[4 * s + g][16 * rt + lr];
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[rt][t] = mfma_f32(a, v[s][t], acc[rt][t]);
+      }
+    }
+    __syncthreads();
+  }
+  zs[tid / 128][tid % 128] = z;
+  __syncthreads();
   float* P = part + (head * n_chunks + chunk) * (long)(r * D + r);
 #pragma unroll
-  for (int i = 0; i < MAXE; ++i) {
-    const int e = threadIdx.x + 256 * i;
-    if (e < r * D) P[e] = acc[i];
+  for (int rt = 0; rt < 8; ++rt) {
+    if (rt >= RT) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int coord = 16 * rt + 4 * g + i;
+      if (coord >= r) continue;
+#pragma unroll
+      for (int t = 0; t < CT; ++t) P[(long)coord * D + wave * (D / 4) + lr * CT + t] = acc[rt][t][i];
+    }
   }
-  if (threadIdx.x < r) P[(long)r * D + threadIdx.x] = zacc;
+  if (tid < r) P[(long)r * D + tid] = zs[0][tid] + zs[1][tid];
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -594,86 +662,96 @@ __global__ __launch_bounds__(256) void readout_mfma_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plain readout (+ combine) for the fp32 path: 32 tokens per workgroup, 8 threads per token.
+// fp32 readout (+ combine): one wave per 16 tokens. u^T = C^T q~ with contraction step i of lane group g
+// = pair 4g + i of a pair tile (even, then odd coordinate), where features_f32 leaves q~; row l%16 of
+// channel tile w = channel (l%16) W + w, so C rows are read, and O rows written, in contiguous pieces.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, bool COMBINE>
-__global__ __launch_bounds__(256) void readout_simple_kernel(
-    int N, int H, int r, int ld, int feat, const T* __restrict__ Qn, const T* __restrict__ Pq,
+template <int D, bool COMBINE>
+__global__ __launch_bounds__(64) void readout_f32_kernel(
+    int N, int H, int r, int ld, int feat, const float* __restrict__ Qn, const float* __restrict__ Pq,
     const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
-    const float* __restrict__ C, float eps_lr, const T* Os, const float* __restrict__ logits,
-    float eps, T* Out) {
-  constexpr int TT = 32, MAXR = 128;
-  __shared__ float Cs[MAXR * D];
-  __shared__ float Qs[TT][D];
-  __shared__ float ft[TT][MAXR];
-  const long head = (long)blockIdx.z * gridDim.y + blockIdx.y;
-  const int h = blockIdx.y, b = blockIdx.z;
-  const int tok0 = blockIdx.x * TT;
-  const T* Qh = Qn + head * (long)N * D;
-  const T* Ph = Pq + (long)h * r * D;
-  const int half = r / 2;
-  for (int e = threadIdx.x; e < r * D; e += 256) Cs[e] = C[head * r * D + e];
-  for (int e = threadIdx.x; e < TT * D; e += 256) {
-    const int tr = e / D, c = e % D, tok = tok0 + tr;
-    Qs[tr][c] = tok < N ? to_f32(Qh[(long)tok * D + c]) : 0.f;
+    const float* __restrict__ C, float eps_lr, const float* Os, const float* __restrict__ logits,
+    float eps, float* Out) {
+  constexpr int W = D / 16;
+  const int h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x, lr = lane % 16, g = lane / 16;
+  const long head = (long)b * gridDim.y + h;
+  const int tok = blockIdx.x * 16 + lr, tk = min(tok, N - 1);
+  const int half = r / 2, JT = (half + 15) / 16;
+  const float* Ch = C + head * (long)r * D + lr * W;
+  const long row = (head * N + tk) * (long)D;
+  float4 x[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    x[s] = *reinterpret_cast<const float4*>(Qn + row + g * (D / 4) + 4 * s);
+  float os[4][W];  // O^s, channels (4g + i) W + w
+  float lg = 0.f;
+  if constexpr (COMBINE) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int s = 0; s < W / 4; ++s)
+        *reinterpret_cast<float4*>(&os[i][4 * s]) =
+            *reinterpret_cast<const float4*>(Os + row + (4 * g + i) * W + 4 * s);
+    lg = logits[(long)b * N + tk];
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < TT * half; e += 256) {
-    const int tr = e / half, j = e % half, tok = tok0 + tr;
-    float ae = 0.f, ao = 0.f;
-    for (int c = 0; c < D; ++c) {
-      ae = fmaf(to_f32(Ph[(long)(2 * j) * D + c]), Qs[tr][c], ae);
-      ao = fmaf(to_f32(Ph[(long)(2 * j + 1) * D + c]), Qs[tr][c], ao);
+  f32x4 u[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) u[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int jt = 0; jt < JT; ++jt) {
+    float4 cv[2][4][W / 4];  // C rows of the lane's pairs; pairs past r/2 meet zero features
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* cr = Ch + (long)(2 * min(16 * jt + 4 * g + i, half - 1)) * D;
+#pragma unroll
+      for (int s = 0; s < W / 4; ++s) {
+        cv[0][i][s] = *reinterpret_cast<const float4*>(cr + 4 * s);
+        cv[1][i][s] = *reinterpret_cast<const float4*>(cr + D + 4 * s);
+      }
     }
-    float cs = 1.f, sn = 0.f;
-    if (tok < N) { cs = cos_tab[(long)tok * ld + j]; sn = sin_tab[(long)tok * ld + j]; }
-    feature_pair<true>(ae, ao, cs, sn, feat);
-    ft[tr][2 * j] = ae;
-    ft[tr][2 * j + 1] = ao;
+    float f[2][4];
+    features_f32<D>(Pq + (long)h * r * D, r, jt, x, cos_tab + (long)tk * ld, sin_tab + (long)tk * ld,
+                    feat, lane, f[0], f[1]);
+#pragma unroll
+    for (int par = 0; par < 2; ++par)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const float4 v = cv[par][i][w / 4];
+          const float a = w % 4 == 0 ? v.x : w % 4 == 1 ? v.y : w % 4 == 2 ? v.z : v.w;
+          u[w] = mfma_f32(a, f[par][i], u[w]);
+        }
   }
-  __syncthreads();
-  const int tr = threadIdx.x / 8, sub = threadIdx.x % 8, tok = tok0 + tr;
-  constexpr int PER = D / 8;
-  float u[PER];
   float ss_u = 0.f;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int c = sub + 8 * k;
-    float s = 0.f;
-    for (int ri = 0; ri < r; ++ri) s = fmaf(ft[tr][ri], Cs[ri * D + c], s);
-    u[k] = s;
-    ss_u = fmaf(s, s, ss_u);
-  }
-  ss_u += __shfl_xor(ss_u, 1);
-  ss_u += __shfl_xor(ss_u, 2);
-  ss_u += __shfl_xor(ss_u, 4);
-  const float inv_u = 1.0f / sqrtf(ss_u / D + eps_lr);
-  T* orow = Out + head * (long)N * D + (long)tok * D;
+  for (int w = 0; w < W; ++w)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ss_u = fmaf(u[w][i], u[w][i], ss_u);
+  const float inv_u = 1.0f / sqrtf(rows_sum(ss_u) / D + eps_lr);
+  float rs = 1.f, gate = 0.f;
   if constexpr (COMBINE) {
-    const T* srow = Os + head * (long)N * D + (long)tok * D;
-    float os[PER];
     float ss_s = 0.f;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      os[k] = tok < N ? to_f32(srow[sub + 8 * k]) : 0.f;
-      ss_s = fmaf(os[k], os[k], ss_s);
-    }
-    ss_s += __shfl_xor(ss_s, 1);
-    ss_s += __shfl_xor(ss_s, 2);
-    ss_s += __shfl_xor(ss_s, 4);
-    const float rs = sqrtf(ss_s / D + eps);
-    if (tok < N) {
-      const float gate = 1.0f / (1.0f + expf(-logits[(long)b * N + tok]));
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int k = 0; k < PER; ++k)
-        orow[sub + 8 * k] = from_f32<T>((os[k] / rs + gate * (u[k] * inv_u)) * rs);
-    }
-  } else {
-    if (tok < N) {
-#pragma unroll
-      for (int k = 0; k < PER; ++k) orow[sub + 8 * k] = from_f32<T>(u[k] * inv_u);
-    }
+      for (int w = 0; w < W; ++w) ss_s = fmaf(os[i][w], os[i][w], ss_s);
+    rs = sqrtf(rows_sum(ss_s) / D + eps);
+    gate = 1.0f / (1.0f + expf(-lg));
   }
+  if (tok >= N) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int s = 0; s < W / 4; ++s) {
+      float4 o;
+      float* op = &o.x;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float ol = u[4 * s + k][i] * inv_u;
+        op[k] = COMBINE ? (os[i][4 * s + k] / rs + gate * ol) * rs : ol;
+      }
+      *reinterpret_cast<float4*>(Out + row + (4 * g + i) * W + 4 * s) = o;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -803,15 +881,10 @@ hipError_t readout_dispatch(const Shape& s, const void* Qn, const void* Pq, int 
     return readout_mfma_feat<4, COMBINE>(s, Qn, Pq, r, ct, st_, ld, feat, C, eps_lr, Os, logits,
                                          eps, Out, st);
   }
-  const dim3 grid((s.N + 31) / 32, s.H, s.B);
-  if (s.d == 64)
-    hipLaunchKernelGGL((readout_simple_kernel<float, 64, COMBINE>), grid, dim3(256), 0, st, s.N,
-                       s.H, r, ld, feat, (const float*)Qn, (const float*)Pq, ct, st_, C, eps_lr,
-                       (const float*)Os, logits, eps, (float*)Out);
-  else
-    hipLaunchKernelGGL((readout_simple_kernel<float, 128, COMBINE>), grid, dim3(256), 0, st, s.N,
-                       s.H, r, ld, feat, (const float*)Qn, (const float*)Pq, ct, st_, C, eps_lr,
-                       (const float*)Os, logits, eps, (float*)Out);
+  const auto kernel = s.d == 64 ? readout_f32_kernel<64, COMBINE> : readout_f32_kernel<128, COMBINE>;
+  hipLaunchKernelGGL(kernel, dim3((s.N + 15) / 16, s.H, s.B), dim3(64), 0, st, s.N, s.H, r, ld, feat,
+                     (const float*)Qn, (const float*)Pq, ct, st_, C, eps_lr, (const float*)Os, logits,
+                     eps, (float*)Out);
   return hipGetLastError();
 }
 
@@ -845,15 +918,10 @@ hipError_t launch_lowrank_summary(const Shape& s, const void* Kn, const void* V,
       e = summary_mfma_feat<2>(s, Kn, V, Pk, r, cos_tab, sin_tab, ld, feat, part, chunk_len,
                                n_chunks, st);
   } else {
-    const dim3 grid(n_chunks, s.H, s.B);
-    if (s.d == 64)
-      hipLaunchKernelGGL((summary_simple_kernel<float, 64>), grid, dim3(256), 0, st, s.N, s.H, r,
-                         chunk_len, n_chunks, ld, feat, (const float*)Kn, (const float*)V,
-                         (const float*)Pk, cos_tab, sin_tab, part);
-    else
-      hipLaunchKernelGGL((summary_simple_kernel<float, 128>), grid, dim3(256), 0, st, s.N, s.H, r,
-                         chunk_len, n_chunks, ld, feat, (const float*)Kn, (const float*)V,
-                         (const float*)Pk, cos_tab, sin_tab, part);
+    const auto kernel = s.d == 64 ? summary_f32_kernel<64> : summary_f32_kernel<128>;
+    hipLaunchKernelGGL(kernel, dim3(n_chunks, s.H, s.B), dim3(256), 0, st, s.N, s.H, r, chunk_len,
+                       n_chunks, ld, feat, (const float*)Kn, (const float*)V, (const float*)Pk, cos_tab,
+                       sin_tab, part);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;

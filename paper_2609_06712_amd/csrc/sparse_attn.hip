@@ -935,73 +935,6 @@ __global__ __launch_bounds__(G * BLK * 2, QUEUE && RJ < 2 && !DQ ? 3 : 2) void s
 }
 
 
-// Plain kernel for the fp32 path: one thread per query, keys streamed through LDS 32 at a time.
-template <typename T, int D>
-__global__ __launch_bounds__(128) void sparse_simple_kernel(int N, int block, int nb, int keep,
-                                                            const int32_t* __restrict__ idx,
-                                                            float scale, const T* __restrict__ Q,
-                                                            const T* __restrict__ K,
-                                                            const T* __restrict__ V,
-                                                            T* __restrict__ O) {
-  constexpr int KC = 32;
-  __shared__ float Ks[KC][D];
-  __shared__ float Vs[KC][D];
-  const int I = blockIdx.x;
-  const long head = (long)blockIdx.z * gridDim.y + blockIdx.y;
-  const T* Qh = Q + head * (long)N * D;
-  const T* Kh = K + head * (long)N * D;
-  const T* Vh = V + head * (long)N * D;
-  const int32_t* sel = idx ? idx + (head * nb + I) * (long)keep : nullptr;
-  const int p = I * block + threadIdx.x;
-  const bool valid = threadIdx.x < block && p < N;
-  float q[D], o[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) { q[c] = valid ? to_f32(Qh[(long)p * D + c]) : 0.f; o[c] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int t = 0; t < keep; ++t) {
-    const int J = sel ? sel[t] : t;
-    if ((unsigned)J >= (unsigned)nb) continue;  // out-of-range entry: skipped
-    const int k0 = J * block, k1 = min(N, k0 + block);
-    for (int c0 = k0; c0 < k1; c0 += KC) {
-      const int cn = min(KC, k1 - c0);
-      __syncthreads();
-      for (int e = threadIdx.x; e < KC * D; e += blockDim.x) {
-        const int r = e / D, c = e % D;
-        Ks[r][c] = r < cn ? to_f32(Kh[(long)(c0 + r) * D + c]) : 0.f;
-        Vs[r][c] = r < cn ? to_f32(Vh[(long)(c0 + r) * D + c]) : 0.f;
-      }
-      __syncthreads();
-      float s[KC];
-      float mx = m;
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        float a = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) a = fmaf(q[c], Ks[j][c], a);
-        s[j] = j < cn ? a * scale : -INFINITY;
-        mx = fmaxf(mx, s[j]);
-      }
-      const float alpha = expf(m - mx);
-      l *= alpha;
-#pragma unroll
-      for (int c = 0; c < D; ++c) o[c] *= alpha;
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        const float w = expf(s[j] - mx);
-        l += w;
-#pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = fmaf(w, Vs[j][c], o[c]);
-      }
-      m = mx;
-    }
-  }
-  if (valid) {
-    const float inv = 1.0f / l;
-#pragma unroll
-    for (int c = 0; c < D; ++c) O[head * (long)N * D + (long)p * D + c] = from_f32<T>(o[c] * inv);
-  }
-}
-
 // Workgroups of `kernel` (threads each) that the current device holds at once, cached per device
 // in `cache` (one per kernel: every variant has the same function type).
 constexpr int kMaxDevices = 64;
@@ -1107,15 +1040,6 @@ hipError_t launch_bf16(const Shape& s, const void* Qr, const void* Kr, const voi
                                            pairs, *fz, queue, st, knorm);
   return launch_bf16_rj<BLK, G, NBUF, 2>(s, Qr, Kr, V, lists, list_len, list_stride, scale, Os,
                                          pairs, *fz, queue, st, knorm);
-}
-
-template <typename T, int D>
-hipError_t launch_simple(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
-                         int keep, const int32_t* idx, float scale, void* Os, hipStream_t st) {
-  const int nb = num_blocks(s.N, block);
-  hipLaunchKernelGGL((sparse_simple_kernel<T, D>), dim3(nb, s.H, s.B), dim3(block), 0, st, s.N,
-                     block, nb, keep, idx, scale, (const T*)Qr, (const T*)Kr, (const T*)V, (T*)Os);
-  return hipGetLastError();
 }
 
 // Query blocks per workgroup when a workspace for the merged lists is given.
@@ -1325,8 +1249,7 @@ hipError_t launch_sparse_attn(const Shape& s, const void* Qr, const void* Kr, co
     if (!idx) return launch_bf16<128, 1, 3>(s, Qr, Kr, V, nullptr, nb, 0, scale, Os, st, nullptr, fp);
     return launch_bf16<128, 1, 3>(s, Qr, Kr, V, idx, keep, keep, scale, Os, st, nullptr, fp);
   }
-  if (s.d == 64) return launch_simple<float, 64>(s, Qr, Kr, V, block, keep, idx, scale, Os, st);
-  return launch_simple<float, 128>(s, Qr, Kr, V, block, keep, idx, scale, Os, st);
+  return launch_attn_f32(s, Qr, Kr, V, block, keep, idx, scale, Os, st);
 }
 
 }  // namespace rola

@@ -84,6 +84,26 @@ def test_tiny_fp32_module():
         _report(f"tiny h{h}", **res)
 
 
+@pytest.mark.parametrize("d,grid,H,B,block,s,r", [
+    (128, (3, 10, 13), 2, 1, 64, 0.5, 128),   # ragged last block, every pair and channel tile
+    (64, (3, 7, 11), 3, 2, 128, 0.5, 2),      # one pair; the tail tile past the last token
+    (128, (2, 5, 3), 1, 1, 32, 0.0, 30),      # fewer tokens than a block, ragged pairs
+    (64, (1, 1, 1), 1, 1, 32, 0.0, 64),       # one token
+    (64, (4, 17, 16), 2, 1, 64, 0.75, 34),    # several summary chunks, a pair tile with one pair
+    (128, (4, 8, 16), 1, 1, 128, 0.5, 64)])
+def test_f32_every_element(d, grid, H, B, block, s, r):
+    """The fp32 kernels at the edges of their 16-query, 16-key, 16-pair and 64-token tiles."""
+    split = (28, 18, 18) if d == 64 else (44, 42, 42)
+    w = synth.TINY.replace(name="f32", grid=grid, H=H, B=B, d_h=d, block=block, sparsity=s, r=r,
+                           split=split, unit_rms=True)
+    inp, f64 = _inputs(w, seed=1)
+    gpu = T.run_gpu(w, inp)
+    for b in range(B):
+        for h in range(H):
+            res = _compare_head(w, gpu, T.oracle_head(w, f64, b, h), b, h, "f32")
+            _report(f"f32 d{d} {grid} block{block} r{r} b{b} h{h}", **res)
+
+
 CASES = [
     # (name, grid, H, B, block, sparsity, r)
     ("ragged r32", (3, 10, 13), 2, 1, 64, 0.5, 32),
