@@ -41,7 +41,7 @@ __device__ __forceinline__ f32x4 mfma16x16x32(const bf16x8& a, const bf16x8& b, 
 // with the ROLA_PHI_* / ROLA_ROPE_* values of the ABI. Every phi maps 0 to 0, so zero rows (padding
 // tokens, padding pairs) keep zero features under every variant.
 constexpr int kPhiSilu = 0, kPhiIdentity = 1, kPhiTanh = 2, kPhiRelu = 3, kPhiGelu = 4;
-constexpr int kRopeOutside = 0, kRopeInside = 1, kRopeNone = 2;
+constexpr int kRopeOutside = 0, kRopeInside = 1;  // any other order: no rotation
 
 __device__ __forceinline__ float feature_act(float x, int phi) {
   switch (phi) {
@@ -54,16 +54,8 @@ __device__ __forceinline__ float feature_act(float x, int phi) {
 }
 
 // Features of one rotary pair from its two projections (e, o) = (P_2j x, P_2j+1 x) at a position
-// with rotation (c, s). GENERIC = false is the paper's design, SiLU then the rotation; GENERIC =
-// true applies feat at run time (the default feat gives the same arithmetic).
-template <bool GENERIC>
+// with rotation (c, s), feat at run time (the fp32 kernels).
 __device__ __forceinline__ void feature_pair(float& e, float& o, float c, float s, int feat) {
-  if (!GENERIC) {
-    const float a = silu(e), b = silu(o);
-    e = a * c - b * s;
-    o = a * s + b * c;
-    return;
-  }
   const int phi = feat & 0xFF, order = feat >> 8;
   if (order == kRopeInside) {
     const float a = e * c - o * s, b = e * s + o * c;
@@ -80,15 +72,90 @@ __device__ __forceinline__ void feature_pair(float& e, float& o, float c, float 
   }
 }
 
-int summary_chunk_len(const Shape& s) {
+// The bf16 kernels' form of feature_pair: the N pairs a lane holds at once, phi a template argument
+// (kPaper: SiLU with the rotation outside, compiled as the plain design; otherwise a ROLA_PHI_* value
+// with the rotation order at run time), and branch-free maps. One uniform branch per phase instead of
+// a switch and a divergent erff / tanhf per value lets the values of a tile overlap: readout at
+// r 128 with GELU inside, 39689 tokens x 12 heads: 383 us with the per-value form.
+constexpr int kPaper = -1;
+
+// GELU x Phi(x) from erfc(z) = t P(t) exp(-z^2), z = |x| / sqrt 2, t = 1 / (1 + 0.4 z): P is a degree-8
+// minimax fit of erfc's scaled form on z in [0, 5] (relative error 1.5e-8 before rounding), which keeps
+// the lower tail relatively accurate where 1 + erf cancels.
+__device__ __forceinline__ float gelu_fast(float x) {
+  const float z = fabsf(x) * 0.70710678118654752f;
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, z, 1.0f));
+  float p = 0.02058017541f;
+  p = fmaf(p, t, -0.0333637342f);
+  p = fmaf(p, t, -0.1531883735f);
+  p = fmaf(p, t, 0.3820583653f);
+  p = fmaf(p, t, -0.143041639f);
+  p = fmaf(p, t, 0.2988953582f);
+  p = fmaf(p, t, 0.1714113825f);
+  p = fmaf(p, t, 0.2313518033f);
+  p = fmaf(p, t, 0.2252966763f);
+  const float tail = 0.5f * t * p * __expf(-z * z);  // 1 - Phi(|x|)
+  return x * (x >= 0.f ? 1.0f - tail : tail);
+}
+
+// tanh: x + x^3 Q(x^2) (degree-4 minimax, 3e-9 relative) up to 0.6, 1 - 2 / (1 + e^2|x|) beyond.
+__device__ __forceinline__ float tanh_fast(float x) {
+  const float a = fabsf(x), u = x * x;
+  float q = -0.005905868674f;
+  q = fmaf(q, u, 0.02080538484f);
+  q = fmaf(q, u, -0.05378668365f);
+  q = fmaf(q, u, 0.1333195824f);
+  q = fmaf(q, u, -0.3333329927f);
+  const float small = fmaf(x * u, q, x);
+  const float large = 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * a));
+  return a < 0.6f ? small : copysignf(large, x);
+}
+
+template <int PHI>
+__device__ __forceinline__ float feature_map(float x) {
+  if constexpr (PHI == kPhiIdentity) return x;
+  if constexpr (PHI == kPhiTanh) return tanh_fast(x);
+  if constexpr (PHI == kPhiRelu) return fmaxf(x, 0.f);
+  if constexpr (PHI == kPhiGelu) return gelu_fast(x);
+  return silu(x);
+}
+
+template <int PHI, int N>
+__device__ __forceinline__ void feature_tile(float (&e)[N], float (&o)[N], const float (&c)[N],
+                                             const float (&s)[N], int order) {
+  const auto rotate = [&] {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float a = e[i], b = o[i];
+      e[i] = a * c[i] - b * s[i];
+      o[i] = a * s[i] + b * c[i];
+    }
+  };
+  if (PHI != kPaper && order == kRopeInside) rotate();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    e[i] = feature_map<PHI>(e[i]);
+    o[i] = feature_map<PHI>(o[i]);
+  }
+  if (PHI == kPaper || order == kRopeOutside) rotate();
+}
+
+// Tokens per workgroup when `heads` heads share about `workgroups` workgroups, whole steps of `step`.
+// Rounded so that there are at most `workgroups` (unless there are more heads): a few workgroups past a
+// whole number of rounds cost a round of their own.
+int chunk_tokens(const Shape& s, long workgroups, int step) {
   const long heads = (long)s.B * s.H;
-  // About 1024 workgroups, two rounds of the two per CU the chip holds. At the 14B shape, against
-  // 2048: r = 32 314 -> 309 us, r = 64 420 -> 388 us (fewer partials to write and reduce); 512 and
-  // 4096 were slower at r = 32.
-  const long want = (1024 + heads - 1) / heads;
+  const long want = heads < workgroups ? workgroups / heads : 1;
   long len = (s.N + want - 1) / want;
-  len = (len + kSummaryStep - 1) / kSummaryStep * kSummaryStep;
-  return (int)(len < kSummaryStep ? kSummaryStep : len);
+  len = (len + step - 1) / step * step;
+  return (int)(len < step ? step : len);
+}
+
+int summary_chunk_len(const Shape& s) {
+  // At most 1024 workgroups: two rounds of the two per CU the chip holds at r = 32, four of one beyond.
+  // (At the 14B shape, against 2048: r = 32 314 -> 309 us, r = 64 420 -> 388 us, fewer partials to
+  // write and reduce; 512 and 4096 were slower at r = 32.)
+  return chunk_tokens(s, 1024, kSummaryStep);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -97,9 +164,9 @@ int summary_chunk_len(const Shape& s) {
 // split = 2: each (b, h, chunk) is served by two workgroups, one per half of the pair tiles (r = 128
 // as two r = 64 halves: one workgroup holding all four tiles spills). The two sit eight launch
 // slots apart, i.e. on the same XCD at about the same time, so the second reads K^n and V from L2.
-template <int JT, bool GENERIC>
+template <int JT, int PHI>
 __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
-    int N, int H, int r, int chunk_len, int n_chunks, int total, int split, int ld, int feat,
+    int N, int H, int r, int chunk_len, int n_chunks, int total, int split, int ld, int order,
     const bf16* __restrict__ Kn, const bf16* __restrict__ V, const bf16* __restrict__ Pk,
     const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
     float* __restrict__ part) {
@@ -192,14 +259,16 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   // Each wave fills and reads only its own 32 rows of a stage, so the waves run their pipelines
   // independently, with no workgroup barrier: the K^n and V loads of step t+1 are issued before the
   // wave waits for those of step t, into registers and a stage that only this wave used at step
-  // t-1. The rotary-table entries (L2-resident rows shared by all heads) are loaded at the start of
-  // their own step: a second register set for them spills. At the 14B shape this loop is 1.5 %
-  // faster than a workgroup-synchronous one at r = 32 and 12 % at r = 64; double-buffered tables
-  // made it 19 % slower at r = 32.
+  // t-1. At the 14B shape this loop is 1.5 % faster than a workgroup-synchronous one at r = 32 and
+  // 12 % at r = 64. The rotary-table entries (L2-resident rows shared by all heads) come one step ahead
+  // too with two pair tiles, where a wave has its SIMD's registers to itself; with one tile (two waves
+  // per SIMD) a second register set for them spills and made the kernel 19 % slower, so there they are
+  // loaded at the start of their own step.
+  constexpr bool kTablesAhead = JT > 1;
   struct StepRegs {
     bf16x8 k[2][4];
+    float cs[JT][2][4], sn[JT][2][4];
   };
-  float tcs[JT][2][4], tsn[JT][2][4];  // this step's table entries
   auto issue_step = [&](int base, int buf, StepRegs& R) {
     // the previous step's LDS reads of this stage are complete before the DMA may overwrite it
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
@@ -213,21 +282,23 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
                                : bf16x8{};
     }
   };
-  auto load_tables = [&](int base) {
+  // Entries of tokens past the chunk and pairs past r/2 are those of the last ones: they meet zero
+  // projections, and every feature map takes zero to zero.
+  auto load_tables = [&](int base, StepRegs& R) {
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int tok = base + wave * 32 + tt * 16 + 4 * g + v, j = 16 * (jt0 + jt) + lr;
-          const bool ok = tok < t1 && j < half;
-          tcs[jt][tt][v] = ok ? cos_tab[(long)tok * ld + j] : 1.f;
-          tsn[jt][tt][v] = ok ? sin_tab[(long)tok * ld + j] : 0.f;
+          const int tok = min(base + wave * 32 + tt * 16 + 4 * g + v, t1 - 1);
+          const int j = min(16 * (jt0 + jt) + lr, half - 1);
+          R.cs[jt][tt][v] = cos_tab[(long)tok * ld + j];
+          R.sn[jt][tt][v] = sin_tab[(long)tok * ld + j];
         }
   };
-  // vector-memory instructions per wave of one issue_step
-  constexpr int kStepLoads = 8 + 8;
+  // vector-memory instructions per wave that one step's look-ahead puts in flight
+  constexpr int kStepLoads = 8 + 8 + (kTablesAhead ? 16 * JT : 0);
   constexpr int kAhead = kStepLoads < 63 ? kStepLoads : 63;
 
   auto compute = [&](const StepRegs& R, int buf) {
@@ -244,14 +315,14 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
           ye = mfma16x16x32(R.k[tt][kc], pe[jt][kc], ye);
           yo = mfma16x16x32(R.k[tt][kc], po[jt][kc], yo);
         }
+        float ke[4] = {ye[0], ye[1], ye[2], ye[3]}, ko[4] = {yo[0], yo[1], yo[2], yo[3]};
+        feature_tile<PHI>(ke, ko, R.cs[jt][tt], R.sn[jt][tt], order);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          float ke = ye[v], ko = yo[v];
-          feature_pair<GENERIC>(ke, ko, tcs[jt][tt][v], tsn[jt][tt][v], feat);
-          ze[jt] += ke;
-          zo[jt] += ko;
-          be[4 * tt + v] = (bf16)ke;
-          bo[4 * tt + v] = (bf16)ko;
+          ze[jt] += ke[v];
+          zo[jt] += ko[v];
+          be[4 * tt + v] = (bf16)ke[v];
+          bo[4 * tt + v] = (bf16)ko[v];
         }
       }
 #pragma unroll
@@ -266,10 +337,11 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   };
   // One step: start the next step's loads, wait for this step's (the next step's stay in flight),
   // compute.
-  auto step = [&](int base, int buf, const StepRegs& cur, StepRegs& nxt) {
-    load_tables(base);
+  auto step = [&](int base, int buf, StepRegs& cur, StepRegs& nxt) {
+    if (!kTablesAhead) load_tables(base, cur);
     if (base + TOK < t1) {
       issue_step(base + TOK, buf ^ 1, nxt);
+      if (kTablesAhead) load_tables(base + TOK, nxt);
       __builtin_amdgcn_s_waitcnt((kAhead & 15) | ((kAhead >> 4) << 14) | (7 << 4) | (15 << 8));
     } else {
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
@@ -279,6 +351,7 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
 
   StepRegs ra, rb;
   issue_step(t0, 0, ra);
+  if (kTablesAhead) load_tables(t0, ra);
   int base = t0;
   for (; base + TOK < t1; base += 2 * TOK) {
     step(base, 0, ra, rb);
@@ -393,7 +466,7 @@ __device__ __forceinline__ void features_f32(const float* __restrict__ P, int r,
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     float a = ye[i], b = yo[i];
-    feature_pair<true>(a, b, cc[i], ss[i], feat);
+    feature_pair(a, b, cc[i], ss[i], feat);
     fe[i] = jb + i < half ? a : 0.f;
     fo[i] = jb + i < half ? b : 0.f;
   }
@@ -486,40 +559,81 @@ __global__ __launch_bounds__(256) void summary_f32_kernel(
 // ------------------------------------------------------------------------------------------------
 // bf16 readout, optionally fused with the gated combine
 // ------------------------------------------------------------------------------------------------
-constexpr int kReadoutTilesPerWave = 4;  // 16-token tiles per wave per workgroup
+// One workgroup per (b, h, chunk of tokens), 16 tokens per wave and step. P (fragments in registers, in
+// LDS at r = 128) and C^T (fragments in LDS) are set up once per workgroup, so chunks are long: about
+// 1024 workgroups. The next tile's Q^n and O^s rows, table entries and logit load while a tile is
+// computed (tokens past the chunk re-read its last one and are not stored). r = 128 takes eight waves
+// to a workgroup: with its fragments in LDS one workgroup fills a CU, and two waves per SIMD overlap
+// one's products with the other's features.
+// Against 256-token workgroups that waited for each pair of tiles (32760 tokens x 40 heads, with the
+// combine): r 64 294 us; r 128 with GELU inside, 39689 tokens x 12 heads: 383 us.
+constexpr int kReadoutWorkgroups = 1024;
+template <int JT>
+constexpr int readout_waves() { return JT == 4 ? 8 : 4; }
 
-template <int JT, bool COMBINE, bool GENERIC>
-__global__ __launch_bounds__(256) void readout_mfma_kernel(
-    int N, int H, int r, int n_groups, int total, int ld, int feat, const bf16* __restrict__ Qn,
-    const bf16* __restrict__ Pq, const float* __restrict__ cos_tab,
-    const float* __restrict__ sin_tab, const float* __restrict__ C, float eps_lr,
-    const bf16* Os, const float* __restrict__ logits, float eps, bf16* Out) {
-  constexpr int D = 128, TPW = kReadoutTilesPerWave;
-  const int BH = total / n_groups;
+template <int JT, bool COMBINE, int PHI>
+__global__ __launch_bounds__(64 * readout_waves<JT>(), 2) void readout_mfma_kernel(
+    int N, int H, int r, int chunk_len, int n_chunks, int total, int ld, int order,
+    const bf16* __restrict__ Qn, const bf16* __restrict__ Pq, const float* __restrict__ cos_tab,
+    const float* __restrict__ sin_tab, const float* __restrict__ C, float eps_lr, const bf16* Os,
+    const float* __restrict__ logits, float eps, bf16* Out) {
+  constexpr int D = 128, NW = readout_waves<JT>(), THREADS = 64 * NW, STEP = 16 * NW;
+  constexpr bool kPLds = JT == 4;
+  const int BH = total / n_chunks;
   const int L = xcd_remap(blockIdx.x, total);
-  const int head = L % BH, grp = L / BH;
+  const int head = L % BH, chunk = L / BH;
   const int h = head % H, b = head / H;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, lr = lane % 16, g = lane / 16;
   const int half = r / 2;
-  const bf16* Qh = Qn + (long)head * N * D;
   const bf16* Ph = Pq + (long)h * r * D;
   const float* Ch = C + (long)head * r * D;
 
-  // A operand of Phi = P Q^T: even / odd rows of P for pair j = 16 jt + lr.
-  bf16x8 pe[JT][4], po[JT][4];
+  struct Tile {
+    bf16x8 q[4], o[COMBINE ? 4 : 1];
+    float4 c[JT], s[JT];
+    float lg;
+  };
+  const int t0 = chunk * chunk_len, t1 = min(N, t0 + chunk_len);
+  const int tok0 = 16 * wave + lr;
+  auto load_tile = [&](int base, Tile& t) {
+    const int tok = min(base + tok0, t1 - 1);
+    const long row = ((long)head * N + tok) * D + 8 * g;
 #pragma unroll
-  for (int jt = 0; jt < JT; ++jt) {
-    const int j = 16 * jt + lr;
+    for (int kc = 0; kc < 4; ++kc) t.q[kc] = *reinterpret_cast<const bf16x8*>(Qn + row + 32 * kc);
+    if constexpr (COMBINE) {
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-      if (j < half) {
-        pe[jt][kc] = *reinterpret_cast<const bf16x8*>(Ph + (long)(2 * j) * D + 32 * kc + 8 * g);
-        po[jt][kc] = *reinterpret_cast<const bf16x8*>(Ph + (long)(2 * j + 1) * D + 32 * kc + 8 * g);
-      } else {
-        pe[jt][kc] = bf16x8{};
-        po[jt][kc] = bf16x8{};
-      }
+      for (int kc = 0; kc < 4; ++kc) t.o[kc] = *reinterpret_cast<const bf16x8*>(Os + row + 32 * kc);
+      t.lg = logits[(long)b * N + tok];
     }
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) {  // pairs past r/2 re-read the last four and meet zero rows of P
+      const int jb = min(16 * jt + 4 * g, half - 4);
+      t.c[jt] = *reinterpret_cast<const float4*>(cos_tab + (long)tok * ld + jb);
+      t.s[jt] = *reinterpret_cast<const float4*>(sin_tab + (long)tok * ld + jb);
+    }
+  };
+  Tile nxt;
+  load_tile(t0, nxt);
+
+  // A operand of Phi = P Q^T: even / odd rows of P for pair j = 16 jt + lr.
+  __shared__ bf16x8 pfrag[kPLds ? 2 * JT * 4 * 64 : 1];
+  bf16x8 pe[kPLds ? 1 : JT][4], po[kPLds ? 1 : JT][4];
+  auto p_row = [&](int jt, int par, int kc, int ln) {
+    const int j = 16 * jt + ln % 16;
+    return j < half ? *reinterpret_cast<const bf16x8*>(Ph + (long)(2 * j + par) * D + 32 * kc + 8 * (ln / 16))
+                    : bf16x8{};
+  };
+  if constexpr (kPLds) {
+    for (int e = tid; e < 2 * JT * 4 * 64; e += THREADS)
+      pfrag[e] = p_row(e / 512, (e / 256) % 2, (e / 64) % 4, e % 64);
+  } else {
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc) {
+        pe[jt][kc] = p_row(jt, 0, kc, lane);
+        po[jt][kc] = p_row(jt, 1, kc, lane);
+      }
   }
   // A operand of u^T = C^T q~, staged once per workgroup in LDS in the order lanes read it.
   // Fragment (jt, w) row c holds channel 32(w/2) + 8(c/4) + 4(w%2) + c%4, so the output lane
@@ -527,7 +641,7 @@ __global__ __launch_bounds__(256) void readout_mfma_kernel(
   // O^s loads and O stores). Slots 0-3 = even rows 2(16jt+4g+s), slots 4-7 = odd rows. C = hi + lo
   // (two bf16 terms) keeps the contraction accurate to ~2^-16 relative with fp32 accumulation.
   __shared__ bf16x8 cfrag[2][JT * 8 * 64];
-  for (int e = tid; e < JT * 8 * 64; e += 256) {
+  for (int e = tid; e < JT * 8 * 64; e += THREADS) {
     const int ln = e % 64, w = (e / 64) % 8, jt = e / 512;
     const int c = ln % 16, ch = 32 * (w >> 1) + 8 * (c >> 2) + 4 * (w & 1) + (c & 3), gg = ln / 16;
     bf16x8 hi, lo;
@@ -543,120 +657,76 @@ __global__ __launch_bounds__(256) void readout_mfma_kernel(
   }
   __syncthreads();
 
-  // Two 16-token tiles per wave at a time: every load of both tiles (Q^n rows, table entries, O^s,
-  // gate logits) is issued before either is computed, so HBM sees both tiles' traffic in flight.
-  constexpr int TG = 2;
-  for (int it0 = 0; it0 < TPW; it0 += TG) {
-    bf16x8 qf[TG][4];
-    float4 c4[TG][JT], s4[TG][JT];
-    bf16x8 osr[TG][4];
-    float lg[TG];
-    int tokv[TG];
+  for (int base = t0; base < t1; base += STEP) {
+    const Tile t = nxt;
+    load_tile(min(base + STEP, t1 - 1), nxt);
+    const int tok = base + tok0;
+    if (tok - lr >= t1) continue;  // whole tile past the end (uniform)
+    const bool valid = tok < t1;
+    f32x4 u[8];
 #pragma unroll
-    for (int tg = 0; tg < TG; ++tg) {
-      const int tok = (grp * 4 * TPW + (it0 + tg) * 4 + wave) * 16 + lr;
-      const bool valid = tok < N;
-      tokv[tg] = tok;
+    for (int w = 0; w < 8; ++w) u[w] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kc = 0; kc < 4; ++kc)
-        qf[tg][kc] = valid ? *reinterpret_cast<const bf16x8*>(Qh + (long)tok * D + 32 * kc + 8 * g)
-                           : bf16x8{};
+    for (int jt = 0; jt < JT; ++jt) {
+      f32x4 ye = {0.f, 0.f, 0.f, 0.f}, yo = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        const int jb = 16 * jt + 4 * g;  // pairs jb..jb+3 of token `tok`
-        c4[tg][jt] = make_float4(1.f, 1.f, 1.f, 1.f);
-        s4[tg][jt] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (valid && jb < half) {
-          c4[tg][jt] = *reinterpret_cast<const float4*>(cos_tab + (long)tok * ld + jb);
-          s4[tg][jt] = *reinterpret_cast<const float4*>(sin_tab + (long)tok * ld + jb);
-        }
+      for (int kc = 0; kc < 4; ++kc) {
+        ye = mfma16x16x32(kPLds ? pfrag[((2 * jt) * 4 + kc) * 64 + lane] : pe[kPLds ? 0 : jt][kc], t.q[kc], ye);
+        yo = mfma16x16x32(kPLds ? pfrag[((2 * jt + 1) * 4 + kc) * 64 + lane] : po[kPLds ? 0 : jt][kc], t.q[kc], yo);
       }
-      if constexpr (COMBINE) {
-        const bf16* srow = Os + (long)head * N * D + (long)tok * D;
+      const float cc[4] = {t.c[jt].x, t.c[jt].y, t.c[jt].z, t.c[jt].w};
+      const float ss[4] = {t.s[jt].x, t.s[jt].y, t.s[jt].z, t.s[jt].w};
+      float qe[4] = {ye[0], ye[1], ye[2], ye[3]}, qo[4] = {yo[0], yo[1], yo[2], yo[3]};
+      feature_tile<PHI>(qe, qo, cc, ss, order);
+      bf16x8 bq, bl;  // q~ = hi + lo
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-          osr[tg][p] = valid ? *reinterpret_cast<const bf16x8*>(srow + 32 * p + 8 * g) : bf16x8{};
-        lg[tg] = valid ? logits[(long)b * N + tok] : 0.f;
+      for (int v = 0; v < 4; ++v) {
+        bq[v] = (bf16)qe[v];
+        bq[4 + v] = (bf16)qo[v];
+        bl[v] = (bf16)(qe[v] - (float)bq[v]);
+        bl[4 + v] = (bf16)(qo[v] - (float)bq[4 + v]);
+      }
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const bf16x8 ch = cfrag[0][(jt * 8 + w) * 64 + lane];
+        const bf16x8 cl = cfrag[1][(jt * 8 + w) * 64 + lane];
+        u[w] = mfma16x16x32(ch, bq, u[w]);
+        u[w] = mfma16x16x32(cl, bq, u[w]);
+        u[w] = mfma16x16x32(ch, bl, u[w]);
       }
     }
+    float ss_u = 0.f;
 #pragma unroll
-    for (int tg = 0; tg < TG; ++tg) {
-      const int tok = tokv[tg];
-      if (tok - lr >= N) continue;  // whole tile past the end (uniform)
-      const bool valid = tok < N;
-      f32x4 u[8];
+    for (int w = 0; w < 8; ++w)
 #pragma unroll
-      for (int w = 0; w < 8; ++w) u[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int v = 0; v < 4; ++v) ss_u = fmaf(u[w][v], u[w][v], ss_u);
+    const float inv_u = rsqrtf(rows_sum(ss_u) * (1.0f / D) + eps_lr);
+    // Lane holds channels 32p + 8g + 4h + v in u[2p + h][v].
+    float scale = inv_u;
+    if constexpr (COMBINE) {
+      float ss_s = 0.f;
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        f32x4 ye = {0.f, 0.f, 0.f, 0.f}, yo = {0.f, 0.f, 0.f, 0.f};
+      for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-          ye = mfma16x16x32(pe[jt][kc], qf[tg][kc], ye);
-          yo = mfma16x16x32(po[jt][kc], qf[tg][kc], yo);
+        for (int i = 0; i < 8; ++i) {
+          const float x = (float)t.o[p][i];
+          ss_s = fmaf(x, x, ss_s);
         }
-        const float cc[4] = {c4[tg][jt].x, c4[tg][jt].y, c4[tg][jt].z, c4[tg][jt].w};
-        const float ss[4] = {s4[tg][jt].x, s4[tg][jt].y, s4[tg][jt].z, s4[tg][jt].w};
-        bf16x8 bq, bl;  // q~ = hi + lo
+      const float rs = sqrtf(rows_sum(ss_s) * (1.0f / D) + eps);
+      // (O^s / r + g O^lr) r  ==  O^s + (g r / rms(u)) u
+      scale = sigmoid(t.lg) * rs * inv_u;
+    }
+    if (!valid) continue;
+    bf16* orow = Out + ((long)head * N + tok) * D + 8 * g;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          float qe = ye[v], qo = yo[v];
-          feature_pair<GENERIC>(qe, qo, cc[v], ss[v], feat);
-          bq[v] = (bf16)qe;
-          bq[4 + v] = (bf16)qo;
-          bl[v] = (bf16)(qe - (float)bq[v]);
-          bl[4 + v] = (bf16)(qo - (float)bq[4 + v]);
-        }
+    for (int p = 0; p < 4; ++p) {
+      bf16x8 o;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-          const bf16x8 ch = cfrag[0][(jt * 8 + w) * 64 + lane];
-          const bf16x8 cl = cfrag[1][(jt * 8 + w) * 64 + lane];
-          u[w] = mfma16x16x32(ch, bq, u[w]);
-          u[w] = mfma16x16x32(cl, bq, u[w]);
-          u[w] = mfma16x16x32(ch, bl, u[w]);
-        }
+      for (int i = 0; i < 8; ++i) {
+        const float x = u[2 * p + (i >> 2)][i & 3];
+        o[i] = COMBINE ? (bf16)fmaf(scale, x, (float)t.o[COMBINE ? p : 0][i]) : (bf16)(x * scale);
       }
-      float ss_u = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) ss_u = fmaf(u[w][v], u[w][v], ss_u);
-      const float inv_u = rsqrtf(rows_sum(ss_u) * (1.0f / D) + eps_lr);
-      bf16* orow = Out + (long)head * N * D + (long)tok * D;
-      // Lane holds channels 32p + 8g + 4h + v in u[2p + h][v].
-      if constexpr (COMBINE) {
-        float ss_s = 0.f;
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const float x = (float)osr[tg][p][i];
-            ss_s = fmaf(x, x, ss_s);
-          }
-        const float rs = sqrtf(rows_sum(ss_s) * (1.0f / D) + eps);
-        // (O^s / r + g O^lr) r  ==  O^s + (g r / rms(u)) u
-        const float coef = sigmoid(lg[tg]) * rs * inv_u;
-        if (valid) {
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            bf16x8 o;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-              o[i] = (bf16)fmaf(coef, u[2 * p + (i >> 2)][i & 3], (float)osr[tg][p][i]);
-            *reinterpret_cast<bf16x8*>(orow + 32 * p + 8 * g) = o;
-          }
-        }
-      } else {
-        if (valid) {
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            bf16x8 o;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = (bf16)(u[2 * p + (i >> 2)][i & 3] * inv_u);
-            *reinterpret_cast<bf16x8*>(orow + 32 * p + 8 * g) = o;
-          }
-        }
-      }
+      *reinterpret_cast<bf16x8*>(orow + 32 * p) = o;
     }
   }
 }
@@ -814,21 +884,21 @@ __global__ __launch_bounds__(256) void features_kernel(long total, int N, int H,
     e = fmaf(to_f32(pe[c]), xc, e);
     o = fmaf(to_f32(po[c]), xc, o);
   }
-  feature_pair<true>(e, o, cos_tab[(long)tok * ld + j], sin_tab[(long)tok * ld + j], feat);
+  feature_pair(e, o, cos_tab[(long)tok * ld + j], sin_tab[(long)tok * ld + j], feat);
   F[row * r + 2 * j] = e;
   F[row * r + 2 * j + 1] = o;
 }
 
-template <int JT, bool GENERIC>
+template <int JT, int PHI>
 hipError_t summary_mfma(const Shape& s, const void* Kn, const void* V, const void* Pk, int r,
-                        const float* ct, const float* st_, int ld, int feat, float* part,
+                        const float* ct, const float* st_, int ld, int order, float* part,
                         int chunk_len, int n_chunks, hipStream_t st) {
   const int total = s.B * s.H * n_chunks;
   const int split = r > 32 * JT ? 2 : 1;  // r = 128 on the two-tile kernel
   const unsigned grid = split == 2 ? (unsigned)((total + 7) / 8 * 16) : (unsigned)total;
-  hipLaunchKernelGGL((summary_mfma_kernel<JT, GENERIC>), dim3(grid), dim3(256), 0, st, s.N, s.H,
-                     r, chunk_len, n_chunks, total, split, ld, feat, (const bf16*)Kn,
-                     (const bf16*)V, (const bf16*)Pk, ct, st_, part);
+  hipLaunchKernelGGL((summary_mfma_kernel<JT, PHI>), dim3(grid), dim3(256), 0, st, s.N, s.H, r,
+                     chunk_len, n_chunks, total, split, ld, order, (const bf16*)Kn, (const bf16*)V,
+                     (const bf16*)Pk, ct, st_, part);
   return hipGetLastError();
 }
 
@@ -836,21 +906,26 @@ template <int JT>
 hipError_t summary_mfma_feat(const Shape& s, const void* Kn, const void* V, const void* Pk, int r,
                              const float* ct, const float* st_, int ld, int feat, float* part,
                              int chunk_len, int n_chunks, hipStream_t st) {
-  if (feat == 0)
-    return summary_mfma<JT, false>(s, Kn, V, Pk, r, ct, st_, ld, feat, part, chunk_len, n_chunks, st);
-  return summary_mfma<JT, true>(s, Kn, V, Pk, r, ct, st_, ld, feat, part, chunk_len, n_chunks, st);
+  const auto launch = feat == 0                         ? summary_mfma<JT, kPaper>
+                      : (feat & 0xFF) == kPhiIdentity ? summary_mfma<JT, kPhiIdentity>
+                      : (feat & 0xFF) == kPhiTanh     ? summary_mfma<JT, kPhiTanh>
+                      : (feat & 0xFF) == kPhiRelu     ? summary_mfma<JT, kPhiRelu>
+                      : (feat & 0xFF) == kPhiGelu     ? summary_mfma<JT, kPhiGelu>
+                                                      : summary_mfma<JT, kPhiSilu>;
+  return launch(s, Kn, V, Pk, r, ct, st_, ld, feat >> 8, part, chunk_len, n_chunks, st);
 }
 
-template <int JT, bool COMBINE, bool GENERIC>
+template <int JT, bool COMBINE, int PHI>
 hipError_t readout_mfma(const Shape& s, const void* Qn, const void* Pq, int r, const float* ct,
-                        const float* st_, int ld, int feat, const float* C, float eps_lr,
+                        const float* st_, int ld, int order, const float* C, float eps_lr,
                         const void* Os, const float* logits, float eps, void* Out, hipStream_t st) {
-  const int per_group = 4 * kReadoutTilesPerWave * 16;
-  const int n_groups = (s.N + per_group - 1) / per_group;
-  const int total = s.B * s.H * n_groups;
-  hipLaunchKernelGGL((readout_mfma_kernel<JT, COMBINE, GENERIC>), dim3(total), dim3(256), 0, st,
-                     s.N, s.H, r, n_groups, total, ld, feat, (const bf16*)Qn, (const bf16*)Pq, ct,
-                     st_, C, eps_lr, (const bf16*)Os, logits, eps, (bf16*)Out);
+  constexpr int threads = 64 * readout_waves<JT>();
+  const int chunk_len = chunk_tokens(s, kReadoutWorkgroups, threads / 4);
+  const int n_chunks = (s.N + chunk_len - 1) / chunk_len;
+  const int total = s.B * s.H * n_chunks;
+  hipLaunchKernelGGL((readout_mfma_kernel<JT, COMBINE, PHI>), dim3(total), dim3(threads), 0, st, s.N,
+                     s.H, r, chunk_len, n_chunks, total, ld, order, (const bf16*)Qn, (const bf16*)Pq,
+                     ct, st_, C, eps_lr, (const bf16*)Os, logits, eps, (bf16*)Out);
   return hipGetLastError();
 }
 
@@ -859,11 +934,13 @@ hipError_t readout_mfma_feat(const Shape& s, const void* Qn, const void* Pq, int
                              const float* ct, const float* st_, int ld, int feat, const float* C,
                              float eps_lr, const void* Os, const float* logits, float eps,
                              void* Out, hipStream_t st) {
-  if (feat == 0)
-    return readout_mfma<JT, COMBINE, false>(s, Qn, Pq, r, ct, st_, ld, feat, C, eps_lr, Os, logits,
-                                            eps, Out, st);
-  return readout_mfma<JT, COMBINE, true>(s, Qn, Pq, r, ct, st_, ld, feat, C, eps_lr, Os, logits,
-                                         eps, Out, st);
+  const auto launch = feat == 0                         ? readout_mfma<JT, COMBINE, kPaper>
+                      : (feat & 0xFF) == kPhiIdentity ? readout_mfma<JT, COMBINE, kPhiIdentity>
+                      : (feat & 0xFF) == kPhiTanh     ? readout_mfma<JT, COMBINE, kPhiTanh>
+                      : (feat & 0xFF) == kPhiRelu     ? readout_mfma<JT, COMBINE, kPhiRelu>
+                      : (feat & 0xFF) == kPhiGelu     ? readout_mfma<JT, COMBINE, kPhiGelu>
+                                                      : readout_mfma<JT, COMBINE, kPhiSilu>;
+  return launch(s, Qn, Pq, r, ct, st_, ld, feat >> 8, C, eps_lr, Os, logits, eps, Out, st);
 }
 
 template <bool COMBINE>
