@@ -155,7 +155,8 @@ int summary_chunk_len(const Shape& s) {
   // At most 1024 workgroups: two rounds of the two per CU the chip holds at r = 32, four of one beyond.
   // (At the 14B shape, against 2048: r = 32 314 -> 309 us, r = 64 420 -> 388 us, fewer partials to
   // write and reduce; 512 and 4096 were slower at r = 32.)
-  return chunk_tokens(s, 1024, kSummaryStep);
+  // The bf16 kernel takes two steps per turn.
+  return chunk_tokens(s, 1024, s.bf16 ? 2 * kSummaryStep : kSummaryStep);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -172,8 +173,7 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
     float* __restrict__ part) {
   constexpr int D = 128, TOK = kSummaryStep;
   constexpr int TILE = TOK * D * 2;  // one step's V tile: 32 KB, row-major, chunks swizzled
-  // Two V stages filled by direct global-to-LDS loads; the first stage is reused for the final
-  // cross-wave reduction.
+  // Two V stages filled by direct global-to-LDS loads, then reused for the cross-wave reduction.
   __shared__ __attribute__((aligned(1024))) char lds[2 * TILE];
 
   const int BH = total / n_chunks;
@@ -194,10 +194,12 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   const char* Vh = reinterpret_cast<const char*>(V + (long)head * N * D);
   const bf16* Ph = Pk + (long)h * r * D;
 
+  // This lane's pair of tile jt is jb + jt: a token's table entries of its pairs are consecutive.
+  const int jb = 16 * jt0 + JT * lr;
   bf16x8 pe[JT][4], po[JT][4];
 #pragma unroll
   for (int jt = 0; jt < JT; ++jt) {
-    const int j = 16 * (jt0 + jt) + lr;
+    const int j = jb + jt;
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
       if (j < half) {
@@ -220,30 +222,25 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
 
   const int t0 = chunk * chunk_len, t1 = min(N, t0 + chunk_len);
   // V tile DMA: lane l of 1-KB slot q (8 slots per wave) fills row 4q + l/16, position l%16 with
-  // source chunk position ^ 2(row%8); rows past the chunk re-read its last row (V rows of tokens
-  // beyond the chunk meet zero features, so they add nothing).
-  typedef __attribute__((address_space(3))) void lds_void;
-  // Slot i's row is row0 + 4i; its swizzle depends only on i's parity (rows advance by 4).
-  const int row0 = 32 * wave + lane / 16, pos = lane % 16;
-  int dvp[2];
+  // source chunk position ^ 2(row%8). Rows past the chunk re-read its last one, as do K^n rows and
+  // table entries: the features of those tokens are zeroed.
+  const int row0 = 32 * wave + lane / 16;
+  uint32_t dvp[2];  // slot i's row is row0 + 4i; its swizzle depends only on i's parity
 #pragma unroll
   for (int p = 0; p < 2; ++p)
-    dvp[p] = (row0 + 4 * p) * D * 2 + ((pos ^ (((row0 + 4 * p) & 7) << 1)) << 4);
-  auto issue_v = [&](int base, int buf) {
-    char* dst = lds + buf * TILE;
+    dvp[p] = (row0 + 4 * p) * D * 2 + (((lane % 16) ^ (((row0 + 4 * p) & 7) << 1)) << 4);
+  const uint32_t lds0 = lds_address(lds);
+  auto issue_v = [&](int base, int buf) {  // always 8 loads
+    const uint32_t dst = lds0 + buf * TILE + wave * 8192;
     if (base + TOK <= t1) {
       const char* vb = Vh + (long)base * D * 2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        __builtin_amdgcn_global_load_lds((const void*)(vb + dvp[i & 1] + (i >> 1) * 2048),
-                                         (lds_void*)(dst + (wave * 8 + i) * 1024), 16, 0, 0);
-    } else {  // tail: rows past the chunk re-read its last row
+      for (int i = 0; i < 8; ++i) dma16(vb, dvp[i & 1] + (i >> 1) * 2048, dst + i * 1024);
+    } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int row = row0 + 4 * i;
-        const long shift = (long)(min(base + row, t1 - 1) - row) * D * 2;
-        __builtin_amdgcn_global_load_lds((const void*)(Vh + shift + dvp[i & 1] + (i >> 1) * 2048),
-                                         (lds_void*)(dst + (wave * 8 + i) * 1024), 16, 0, 0);
+        const int row = row0 + 4 * i, src = min(base + row, t1 - 1);
+        dma16(Vh, (uint32_t)(src - row) * (D * 2) + dvp[i & 1] + (i >> 1) * 2048, dst + i * 1024);
       }
     }
   };
@@ -255,109 +252,130 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   for (int w = 0; w < 8; ++w)
     vo[w] = vr * 256 + (((2 * w + (mp >> 1)) ^ ((vr & 7) << 1)) << 4) + ((mp & 1) << 3);
 
-  // A step reads K^n operand rows from registers and V from the wave's own rows of an LDS stage.
-  // Each wave fills and reads only its own 32 rows of a stage, so the waves run their pipelines
-  // independently, with no workgroup barrier: the K^n and V loads of step t+1 are issued before the
-  // wave waits for those of step t, into registers and a stage that only this wave used at step
-  // t-1. At the 14B shape this loop is 1.5 % faster than a workgroup-synchronous one at r = 32 and
-  // 12 % at r = 64. The rotary-table entries (L2-resident rows shared by all heads) come one step ahead
-  // too with two pair tiles, where a wave has its SIMD's registers to itself; with one tile (two waves
-  // per SIMD) a second register set for them spills and made the kernel 19 % slower, so there they are
-  // loaded at the start of their own step.
-  constexpr bool kTablesAhead = JT > 1;
-  struct StepRegs {
+  // Pipeline, per wave (each wave fills and reads only its own 32 rows of a stage, so there is no
+  // workgroup barrier): the V rows (LDS DMA) and K^n rows (registers) of step t+1 are issued before
+  // step t is computed, the table entries of step t+2 in the middle of step t. No load is
+  // conditional, so the compiler's waits for a step's K^n rows and table entries leave the later
+  // loads in flight; with guarded loads it drained the whole queue at the top of each step, which
+  // serialised loads and compute (r = 64, 32760 tokens x 40 heads: 210 us).
+  // The V DMA is inline assembly, which the compiler does not track. What makes a step's V rows
+  // complete before they are read: vector-memory loads retire in order, the K^n loads of a step are
+  // issued after its V DMA (their address passes through an asm statement behind it), and the reads
+  // of V stand behind an asm statement that takes a product of the last of those K^n rows.
+  typedef float tvec __attribute__((ext_vector_type(JT)));
+  struct KRows {
     bf16x8 k[2][4];
-    float cs[JT][2][4], sn[JT][2][4];
   };
-  auto issue_step = [&](int base, int buf, StepRegs& R) {
-    // the previous step's LDS reads of this stage are complete before the DMA may overwrite it
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    issue_v(base, buf);
+  struct Tables {
+    tvec c[2][4], s[2][4];
+  };
+  // Rows are addressed from a scalar base per step with 32-bit lane offsets (whole 64-bit addresses
+  // per load cost the registers that the second sets need).
+  auto issue_k = [&](int base, KRows& R) {
+    uint32_t fence = 16 * g;
+    asm volatile("" : "+v"(fence) : : "memory");
+    const int first = min(base, t1 - 1), lim = t1 - 1 - first;
+    const char* kb = reinterpret_cast<const char*>(Kh + (long)first * D);
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      const int tok = base + wave * 32 + tt * 16 + lr;
+      const uint32_t off = (uint32_t)min(wave * 32 + tt * 16 + lr, lim) * (D * 2) + fence;
 #pragma unroll
-      for (int kc = 0; kc < 4; ++kc)
-        R.k[tt][kc] = tok < t1 ? *reinterpret_cast<const bf16x8*>(Kh + (long)tok * D + 32 * kc + 8 * g)
-                               : bf16x8{};
+      for (int kc = 0; kc < 4; ++kc) R.k[tt][kc] = *reinterpret_cast<const bf16x8*>(kb + off + 64 * kc);
     }
   };
-  // Entries of tokens past the chunk and pairs past r/2 are those of the last ones: they meet zero
-  // projections, and every feature map takes zero to zero.
-  auto load_tables = [&](int base, StepRegs& R) {
+  // pairs past r/2 re-read the last ones and meet zero rows of P
+  const uint32_t joff = 4 * min(jb, half - JT), ldb = 4 * ld;  // ld <= 65536: 24-bit products
+  auto load_tables = [&](int base, Tables& T) {
+    const int first = min(base, t1 - 1), lim = t1 - 1 - first;
+    const char* cb = reinterpret_cast<const char*>(cos_tab + (long)first * ld);
+    const char* sb = reinterpret_cast<const char*>(sin_tab + (long)first * ld);
 #pragma unroll
-    for (int jt = 0; jt < JT; ++jt)
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int tok = min(base + wave * 32 + tt * 16 + 4 * g + v, t1 - 1);
-          const int j = min(16 * (jt0 + jt) + lr, half - 1);
-          R.cs[jt][tt][v] = cos_tab[(long)tok * ld + j];
-          R.sn[jt][tt][v] = sin_tab[(long)tok * ld + j];
-        }
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t off = __umul24(min(wave * 32 + tt * 16 + 4 * g + v, lim), ldb) + joff;
+        T.c[tt][v] = *reinterpret_cast<const tvec*>(cb + off);
+        T.s[tt][v] = *reinterpret_cast<const tvec*>(sb + off);
+      }
   };
-  // vector-memory instructions per wave that one step's look-ahead puts in flight
-  constexpr int kStepLoads = 8 + 8 + (kTablesAhead ? 16 * JT : 0);
-  constexpr int kAhead = kStepLoads < 63 ? kStepLoads : 63;
-
-  auto compute = [&](const StepRegs& R, int buf) {
-    const char* Vs = lds + buf * TILE;
-    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+  auto step = [&](int base, int buf, const KRows& cur, KRows& nxt, Tables& T) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the reads of the stage V goes into are done
+    issue_v(base + TOK, buf ^ 1);
+    issue_k(base + TOK, nxt);
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 be[JT], bo[JT];
+    float last = 0.f;
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      bf16x8 be, bo;
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
         f32x4 ye = {0.f, 0.f, 0.f, 0.f}, yo = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc) {
-          ye = mfma16x16x32(R.k[tt][kc], pe[jt][kc], ye);
-          yo = mfma16x16x32(R.k[tt][kc], po[jt][kc], yo);
+          ye = mfma16x16x32(cur.k[tt][kc], pe[jt][kc], ye);
+          yo = mfma16x16x32(cur.k[tt][kc], po[jt][kc], yo);
         }
+        last = yo[0];
         float ke[4] = {ye[0], ye[1], ye[2], ye[3]}, ko[4] = {yo[0], yo[1], yo[2], yo[3]};
-        feature_tile<PHI>(ke, ko, R.cs[jt][tt], R.sn[jt][tt], order);
+        float cs[4], sn[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          cs[v] = T.c[tt][v][jt];
+          sn[v] = T.s[tt][v][jt];
+        }
+        feature_tile<PHI>(ke, ko, cs, sn, order);
+        if (base + TOK > t1) {  // (uniform) tokens past the chunk
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const bool ok = base + wave * 32 + tt * 16 + 4 * g + v < t1;
+            ke[v] = ok ? ke[v] : 0.f;
+            ko[v] = ok ? ko[v] : 0.f;
+          }
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           ze[jt] += ke[v];
           zo[jt] += ko[v];
-          be[4 * tt + v] = (bf16)ke[v];
-          bo[4 * tt + v] = (bf16)ko[v];
+          be[jt][4 * tt + v] = (bf16)ke[v];
+          bo[jt][4 * tt + v] = (bf16)ko[v];
         }
       }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_tables(base + 2 * TOK, T);
+    asm volatile("" : "+v"(last) : : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const char* Vs = lds + buf * TILE;
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Vs + vo[w]));
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Vs + vo[w] + 16 * 256));
-        const bf16x8 va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        ce[jt][w] = mfma16x16x32(va, be, ce[jt][w]);
-        co[jt][w] = mfma16x16x32(va, bo, co[jt][w]);
+    for (int w = 0; w < 8; ++w) {
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Vs + vo[w]));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(Vs + vo[w] + 16 * 256));
+      const bf16x8 va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        ce[jt][w] = mfma16x16x32(va, be[jt], ce[jt][w]);
+        co[jt][w] = mfma16x16x32(va, bo[jt], co[jt][w]);
       }
     }
   };
-  // One step: start the next step's loads, wait for this step's (the next step's stay in flight),
-  // compute.
-  auto step = [&](int base, int buf, StepRegs& cur, StepRegs& nxt) {
-    if (!kTablesAhead) load_tables(base, cur);
-    if (base + TOK < t1) {
-      issue_step(base + TOK, buf ^ 1, nxt);
-      if (kTablesAhead) load_tables(base + TOK, nxt);
-      __builtin_amdgcn_s_waitcnt((kAhead & 15) | ((kAhead >> 4) << 14) | (7 << 4) | (15 << 8));
-    } else {
-      __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
-    }
-    compute(cur, buf);
-  };
 
-  StepRegs ra, rb;
-  issue_step(t0, 0, ra);
-  if (kTablesAhead) load_tables(t0, ra);
-  int base = t0;
-  for (; base + TOK < t1; base += 2 * TOK) {
-    step(base, 0, ra, rb);
-    step(base + TOK, 1, rb, ra);
+  KRows ra, rb;
+  Tables ta, tb;
+  load_tables(t0, ta);  // (in the loop's issue order: the waits at its head assume the worse of the two)
+  issue_v(t0, 0);
+  issue_k(t0, ra);
+  __builtin_amdgcn_sched_barrier(0);
+  load_tables(t0 + TOK, tb);
+  __builtin_amdgcn_sched_barrier(0);
+  // two steps per turn without an exit between them (it costs 60 to 130 spilled registers): the second
+  // of an odd count adds zeros
+  for (int base = t0; base < t1; base += 2 * TOK) {
+    step(base, 0, ra, rb, ta);
+    step(base + TOK, 1, rb, ra, tb);
   }
-  if (base < t1) step(base, 0, ra, rb);
+  // the last look-ahead has landed before the stages are reused below (barriers follow)
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
 
   // z: the four lane groups hold different tokens of the same pair j
 #pragma unroll
@@ -401,7 +419,7 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
     float* P = part + ((long)head * n_chunks + chunk) * (long)(r * D + r);
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      const int j = 16 * (jt0 + jt) + lr;
+      const int j = jb + jt;
       if (j >= half) continue;
 #pragma unroll
       for (int w = 0; w < 8; ++w)
