@@ -324,10 +324,20 @@ __global__ __launch_bounds__(256) void cfrag_kernel(long total, int r, int RJ,
   out[2 * e + 1] = *reinterpret_cast<const uint4*>(&lo);
 }
 
+// Two forms, by the registers that three workgroups per CU leave (168):
+//  * r <= 32 (RJ = 1): u of all four channel tiles at once, each load where it is used and guarded per
+//    lane. Other workgroups hide these loads: issued unconditionally up front they make the 14B layer
+//    0.7 % slower, and so does forming u twice as below.
+//  * r = 64 (WIDE): u one channel tile at a time, once for its norm and once for the output (48 more
+//    MFMAs per wave and group), the loads up front and unconditional, from clamped addresses: invalid
+//    queries are not stored, and features of pairs past r/2 meet zero rows of the C^T fragments. Held
+//    whole, u needs 212 VGPRs and leaves two workgroups per CU (14B layer, r 64: 14.7 ms against
+//    13.3; 480p, 12 heads: 1.26 against 1.14 ms).
 template <int RJ>
 __device__ __forceinline__ void fuse_epilogue(const FuseArgs& fz, f32x16 (&acc)[4], float l,
                                               bool qvalid, long head, int N, int q, int lane,
                                               bf16* __restrict__ O) {
+  constexpr bool WIDE = RJ > 1;
   constexpr int D = 128;
   // the query index through an empty asm: the epilogue's address arithmetic is not hoisted in front
   // of the main loop, where it held registers across it (and spilled); the per-query offsets are
@@ -336,6 +346,36 @@ __device__ __forceinline__ void fuse_epilogue(const FuseArgs& fz, f32x16 (&acc)[
   const int hh = lane / 32, half = fz.r / 2;
   const int h = (int)(head % fz.H);
   const long bidx = head / fz.H;
+  const uint32_t qc = WIDE ? (uint32_t)min(q, N - 1) : (uint32_t)q;
+  // Q^n operand (query q, d = 16s + 8(l/32) .. +7), the token's gate logit, and the table entries of
+  // this lane's pairs J = 16t + 8jp + 4(l/32) + i (half is a multiple of 8: 4 pairs valid or none)
+  const bf16* Qq = fz.Qn + head * (long)N * D + qc * (uint32_t)D;
+  bf16x8 qn[8];
+  float lg = 0.f;
+  float4 c4[RJ][2], s4[RJ][2];
+  auto load_rows = [&] {
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      qn[s] = WIDE || qvalid ? *reinterpret_cast<const bf16x8*>(Qq + 16 * s + 8 * hh) : bf16x8{};
+    if (WIDE || qvalid) lg = fz.logits[bidx * N + qc];
+  };
+  auto load_tables = [&](int t) {
+#pragma unroll
+    for (int jp = 0; jp < 2; ++jp) {
+      const int J0 = 16 * t + 8 * jp + 4 * hh;
+      const uint32_t off = qc * (uint32_t)fz.ld + (uint32_t)(WIDE ? min(J0, half - 4) : J0);
+      c4[t][jp] = s4[t][jp] = float4{0.f, 0.f, 0.f, 0.f};
+      if (WIDE || (qvalid && J0 < half)) {
+        c4[t][jp] = *reinterpret_cast<const float4*>(fz.cos_tab + off);
+        s4[t][jp] = *reinterpret_cast<const float4*>(fz.sin_tab + off);
+      }
+    }
+  };
+  if constexpr (WIDE) {
+    load_rows();
+#pragma unroll
+    for (int t = 0; t < RJ; ++t) load_tables(t);
+  }
   // O^s and its RMS
   const float inv = qvalid ? 1.0f / l : 0.f;
   float ss = 0.f;
@@ -351,68 +391,59 @@ __device__ __forceinline__ void fuse_epilogue(const FuseArgs& fz, f32x16 (&acc)[
     ss = __uint_as_float(x[0]) + __uint_as_float(x[1]);
   }
   const float rs = sqrtf(ss * (1.0f / D) + fz.eps);
-  // Q^n operand (query q, d = 16s + 8(l/32) .. +7) and the token's gate logit
-  const bf16* Qq = fz.Qn + head * (long)N * D + (uint32_t)q * (uint32_t)D;
-  bf16x8 qn[8];
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-    qn[s] = qvalid ? *reinterpret_cast<const bf16x8*>(Qq + 16 * s + 8 * hh) : bf16x8{};
-  const float lg = qvalid ? fz.logits[bidx * N + q] : 0.f;
-  f32x16 u[4];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) u[w] = f32x16{};
+  if constexpr (!WIDE) load_rows();
+  // features: e in ph[4jp+i], o in ph[4jp+8+i]; hi and lo of the even and the odd coordinates
+  bf16x8 feat[RJ][2][2];  // [t][parity][hi, lo]
 #pragma unroll
   for (int t = 0; t < RJ; ++t) {
-    const int rho = lane % 32, pair = 16 * t + (rho & 15);
-    const bool pok = pair < half;
+    const int rho = lane % 32, pair = min(16 * t + (rho & 15), half - 1);
     const bf16* Pr = fz.Pq + ((long)h * fz.r + 2 * pair + (rho >> 4)) * D + 8 * hh;
     f32x16 ph = f32x16{};
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const bf16x8 pa = pok ? *reinterpret_cast<const bf16x8*>(Pr + 16 * s) : bf16x8{};
-      ph = mfma32(pa, qn[s], ph);
-    }
-    // features of this lane's pairs J = 16t + 8jp + 4(l/32) + i: e in ph[4jp+i], o in ph[4jp+8+i]
-    bf16x8 beh, bel, boh, bol;
+    for (int s = 0; s < 8; ++s)
+      ph = mfma32(*reinterpret_cast<const bf16x8*>(Pr + 16 * s), qn[s], ph);
+    if constexpr (!WIDE) load_tables(t);
 #pragma unroll
     for (int jp = 0; jp < 2; ++jp) {
-      const int J0 = 16 * t + 8 * jp + 4 * hh;  // half is a multiple of 8: 4 pairs valid or none
-      float4 c4 = {1.f, 1.f, 1.f, 1.f}, s4 = {0.f, 0.f, 0.f, 0.f};
-      if (qvalid && J0 < half) {
-        c4 = *reinterpret_cast<const float4*>(fz.cos_tab + (uint32_t)q * (uint32_t)fz.ld + J0);
-        s4 = *reinterpret_cast<const float4*>(fz.sin_tab + (uint32_t)q * (uint32_t)fz.ld + J0);
-      }
-      const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
+      const float cc[4] = {c4[t][jp].x, c4[t][jp].y, c4[t][jp].z, c4[t][jp].w};
+      const float sn[4] = {s4[t][jp].x, s4[t][jp].y, s4[t][jp].z, s4[t][jp].w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float a = silu(ph[4 * jp + i]), b = silu(ph[4 * jp + 8 + i]);
-        const float qe = a * cc[i] - b * sn[i], qo = a * sn[i] + b * cc[i];
-        beh[4 * jp + i] = (bf16)qe;
-        bel[4 * jp + i] = (bf16)(qe - (float)beh[4 * jp + i]);
-        boh[4 * jp + i] = (bf16)qo;
-        bol[4 * jp + i] = (bf16)(qo - (float)boh[4 * jp + i]);
+        const float f[2] = {a * cc[i] - b * sn[i], a * sn[i] + b * cc[i]};
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+          feat[t][sd][0][4 * jp + i] = (bf16)f[sd];
+          feat[t][sd][1][4 * jp + i] = (bf16)(f[sd] - (float)feat[t][sd][0][4 * jp + i]);
+        }
       }
     }
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd) {
-        const uint4* fr = fz.cfrag + ((((head * 4 + w) * (2 * RJ) + 2 * t + sd) * 64) + lane) * 2;
-        const uint4 fh = fr[0], fl = fr[1];
-        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&fh);
-        const bf16x8 al = *reinterpret_cast<const bf16x8*>(&fl);
-        const bf16x8& bh = sd ? boh : beh;
-        const bf16x8& bl = sd ? bol : bel;
-        u[w] = mfma32(ah, bh, u[w]);
-        u[w] = mfma32(al, bh, u[w]);
-        u[w] = mfma32(ah, bl, u[w]);
-      }
   }
+  auto u_tile = [&](int w) {  // channels 32w .. 32w + 31 of u
+    f32x16 u = f32x16{};
+#pragma unroll
+    for (int ts = 0; ts < 2 * RJ; ++ts) {
+      const uint4* fr = fz.cfrag + (((head * 4 + w) * (2 * RJ) + ts) * 64 + lane) * 2;
+      const uint4 fh = fr[0], fl = fr[1];
+      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&fh);
+      const bf16x8 al = *reinterpret_cast<const bf16x8*>(&fl);
+      const bf16x8 &bh = feat[ts / 2][ts % 2][0], &bl = feat[ts / 2][ts % 2][1];
+      u = mfma32(ah, bh, u);
+      u = mfma32(al, bh, u);
+      u = mfma32(ah, bl, u);
+    }
+    return u;
+  };
+  f32x16 u[WIDE ? 1 : 4];
   float su = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
+  for (int w = 0; w < 4; ++w) {
+    f32x16& uw = u[WIDE ? 0 : w];
+    uw = u_tile(w);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) su = fmaf(u[w][k], u[w][k], su);
+    for (int k = 0; k < 16; ++k) su = fmaf(uw[k], uw[k], su);
+    if (WIDE) __builtin_amdgcn_sched_barrier(0);  // one tile at a time
+  }
   {
     const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(su), __float_as_uint(su), false, false);
     su = __uint_as_float(x[0]) + __uint_as_float(x[1]);
@@ -420,17 +451,21 @@ __device__ __forceinline__ void fuse_epilogue(const FuseArgs& fz, f32x16 (&acc)[
   const float inv_u = rsqrtf(su * (1.0f / D) + fz.eps_lr);
   // (O^s / r_s + g O^lr) r_s  ==  O^s + (g r_s / rms(u)) u
   const float coef = sigmoid(lg) * rs * inv_u;
-  if (qvalid) {
-    bf16* Oq = O + head * (long)N * D + (uint32_t)q * (uint32_t)D;
+  bf16* Oq = O + head * (long)N * D + qc * (uint32_t)D;
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
+  for (int w = 0; w < 4; ++w) {
+    f32x16& uw = u[WIDE ? 0 : w];
+    if (WIDE) uw = u_tile(w);
+    if (qvalid) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         bf16x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = (bf16)fmaf(coef, u[w][4 * j + i], acc[w][4 * j + i]);
+        for (int i = 0; i < 4; ++i) o[i] = (bf16)fmaf(coef, uw[4 * j + i], acc[w][4 * j + i]);
         *reinterpret_cast<bf16x4*>(Oq + 32 * w + 8 * j + 4 * hh) = o;
       }
+    }
+    if (WIDE) __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -478,7 +513,7 @@ struct AttnArgs {
 // BOUND (merged lists, G > 1): the softmax reference of each wave is the bound on its scores that
 // the key-block norms give, where that bound is small enough (see the prologue).
 template <int BLK, int G, int NBUF, int TAB, int RJ, bool QUEUE, bool DQ = false, bool BOUND = false>
-__global__ __launch_bounds__(G * BLK * 2, QUEUE && RJ < 2 && !DQ ? 3 : 2) void sparse_attn_kernel(
+__global__ __launch_bounds__(G * BLK * 2, G * BLK == 128 && !DQ ? 3 : 2) void sparse_attn_kernel(
     const AttnArgs args) {
   static_assert(G == 1 || G == 2 || G == 4, "one, two or four query blocks per workgroup");
   static_assert(NBUF >= 3, "loads of later sub-tiles stay in flight during a step");
