@@ -16,6 +16,29 @@ struct Shape {
 
 inline int num_blocks(int N, int block) { return (N + block - 1) / block; }
 
+// Tokens per workgroup of the low-rank kernels, which give each (b, h) to several workgroups of
+// consecutive tokens: a multiple of `step`, at least what about `workgroups` workgroups give (and no
+// more of them than that), chosen so that whole rounds of the `slots` workgroups the chip holds cost
+// least, a round lasting as long as its chunk plus its set-up (about `step` tokens). Workgroups past a
+// whole round cost a round of their own, and the fewest rounds usually win: low-rank branch, r 64, 32760
+// tokens x 40 heads 425 us with the summary in 4.1 rounds, 383 in one; r 128, 12 heads 234 and 176.
+constexpr int kCus = 256;
+inline int chunk_tokens(const Shape& s, long workgroups, long slots, int step) {
+  const long heads = (long)s.B * s.H;
+  const long want = heads < workgroups ? workgroups / heads : 1;
+  const long least = ((s.N + want - 1) / want + step - 1) / step * step;
+  long best = least, best_cost = -1;
+  for (long len = least; len <= 8 * least; len += step) {
+    const long groups = heads * ((s.N + len - 1) / len);
+    const long cost = (groups + slots - 1) / slots * (len + step);
+    if (best_cost < 0 || cost < best_cost) {
+      best = len;
+      best_cost = cost;
+    }
+  }
+  return (int)best;
+}
+
 // rope.hip
 hipError_t launch_rope_tables(const Shape& s, int dt, int dy, int dx, double base, int ot, int oy,
                               int ox, float* cos_tab, float* sin_tab, hipStream_t st);

@@ -140,23 +140,12 @@ __device__ __forceinline__ void feature_tile(float (&e)[N], float (&o)[N], const
   if (PHI == kPaper || order == kRopeOutside) rotate();
 }
 
-// Tokens per workgroup when `heads` heads share about `workgroups` workgroups, whole steps of `step`.
-// Rounded so that there are at most `workgroups` (unless there are more heads): a few workgroups past a
-// whole number of rounds cost a round of their own.
-int chunk_tokens(const Shape& s, long workgroups, int step) {
-  const long heads = (long)s.B * s.H;
-  const long want = heads < workgroups ? workgroups / heads : 1;
-  long len = (s.N + want - 1) / want;
-  len = (len + step - 1) / step * step;
-  return (int)(len < step ? step : len);
-}
-
-int summary_chunk_len(const Shape& s) {
-  // At most 1024 workgroups: two rounds of the two per CU the chip holds at r = 32, four of one beyond.
-  // (At the 14B shape, against 2048: r = 32 314 -> 309 us, r = 64 420 -> 388 us, fewer partials to
-  // write and reduce; 512 and 4096 were slower at r = 32.)
-  // The bf16 kernel takes two steps per turn.
-  return chunk_tokens(s, 1024, s.bf16 ? 2 * kSummaryStep : kSummaryStep);
+// Tokens per summary workgroup. The chip holds two per CU at r = 32, one beyond, two for each chunk at r
+// = 128; the bf16 kernel takes two steps per turn. (Least length: at the 14B shape, r = 64, 2048
+// workgroups took 420 us, 1024 388: fewer partials to write and reduce.)
+int summary_chunk_len(const Shape& s, int r) {
+  if (!s.bf16) return chunk_tokens(s, 1024, 1024, kSummaryStep);
+  return chunk_tokens(s, 1024, r <= 32 ? 2 * kCus : r <= 64 ? kCus : kCus / 2, 2 * kSummaryStep);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -578,8 +567,8 @@ __global__ __launch_bounds__(256) void summary_f32_kernel(
 // bf16 readout, optionally fused with the gated combine
 // ------------------------------------------------------------------------------------------------
 // One workgroup per (b, h, chunk of tokens), 16 tokens per wave and step. P (fragments in registers, in
-// LDS at r = 128) and C^T (fragments in LDS) are set up once per workgroup, so chunks are long: about
-// 1024 workgroups. The next tile's Q^n and O^s rows, table entries and logit load while a tile is
+// LDS at r = 128) and C^T (fragments in LDS) are set up once per workgroup, so chunks are long: at most
+// 1024 workgroups, in whole rounds. The next tile's Q^n and O^s rows, table entries and logit load while a tile is
 // computed (tokens past the chunk re-read its last one and are not stored). r = 128 takes eight waves
 // to a workgroup: with its fragments in LDS one workgroup fills a CU, and two waves per SIMD overlap
 // one's products with the other's features.
@@ -938,7 +927,9 @@ hipError_t readout_mfma(const Shape& s, const void* Qn, const void* Pq, int r, c
                         const float* st_, int ld, int order, const float* C, float eps_lr,
                         const void* Os, const float* logits, float eps, void* Out, hipStream_t st) {
   constexpr int threads = 64 * readout_waves<JT>();
-  const int chunk_len = chunk_tokens(s, kReadoutWorkgroups, threads / 4);
+  // workgroups per CU by registers (LDS at r = 128)
+  constexpr int per_cu = JT == 1 ? 3 : JT == 2 ? 2 : 1;
+  const int chunk_len = chunk_tokens(s, kReadoutWorkgroups, per_cu * kCus, threads / 4);
   const int n_chunks = (s.N + chunk_len - 1) / chunk_len;
   const int total = s.B * s.H * n_chunks;
   hipLaunchKernelGGL((readout_mfma_kernel<JT, COMBINE, PHI>), dim3(total), dim3(threads), 0, st, s.N,
@@ -986,8 +977,7 @@ hipError_t readout_dispatch(const Shape& s, const void* Qn, const void* Pq, int 
 }  // namespace
 
 int summary_chunks(const Shape& s, int r) {
-  (void)r;
-  const int len = summary_chunk_len(s);
+  const int len = summary_chunk_len(s, r);
   return (s.N + len - 1) / len;
 }
 
@@ -998,7 +988,7 @@ size_t summary_workspace_bytes(const Shape& s, int r) {
 hipError_t launch_lowrank_summary(const Shape& s, const void* Kn, const void* V, const void* Pk,
                                   int r, const float* cos_tab, const float* sin_tab, int ld,
                                   int feat, float* C, float* z, void* ws, hipStream_t st) {
-  const int chunk_len = summary_chunk_len(s);
+  const int chunk_len = summary_chunk_len(s, r);
   const int n_chunks = (s.N + chunk_len - 1) / chunk_len;
   float* part = (float*)ws;
   hipError_t e;

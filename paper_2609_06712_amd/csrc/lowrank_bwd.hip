@@ -440,17 +440,11 @@ __global__ __launch_bounds__(256) void lr_bwd_logit_kernel(long BN, int N, int H
   dlogits[e] = s;
 }
 
-// Workgroups of each pass. The query side and the r > 32 key side hold one per CU, so this is four
-// whole rounds: each round stages P and M anew and leaves partials to add (14B 720p layer, r 64, whole
-// call: 4096 2.96 ms, 2048 2.84 ms, 1024 2.77 ms).
+// Most workgroups of each pass. The query side and the r > 32 key side hold one per CU; each stages P and
+// M anew and leaves partials to add (14B 720p layer, r 64, whole call: 4096 2.96 ms, 2048 2.84 ms, 1024
+// 2.77 ms; whole rounds of 256: see chunk_tokens).
 constexpr long kLrBwdWorkgroups = 1024;
-int lr_bwd_chunk_len(const Shape& s) {
-  const long heads = (long)s.B * s.H;
-  const long want = heads < kLrBwdWorkgroups ? kLrBwdWorkgroups / heads : 1;
-  long len = (s.N + want - 1) / want;
-  len = (len + kStep - 1) / kStep * kStep;  // whole steps of the MFMA path
-  return (int)(len < kStep ? kStep : len);
-}
+int lr_bwd_chunk_len(const Shape& s) { return chunk_tokens(s, kLrBwdWorkgroups, kCus, kStep); }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
