@@ -288,11 +288,28 @@ __global__ __launch_bounds__(BLK * 2, 2) void sparse_dq_kernel(
 // bf16 rounding dS takes next. Workgroups take a head's key blocks longest list first
 // (bwd_order_kernel) and walk each list in the bit-reversed order, so that workgroups running at
 // the same time sit on about the same query blocks and share their Q and dO rows in L2.
+//
+// Which XCD takes which key block (workgroups are dealt to the XCDs round-robin): each XCD takes
+// heads / 8 whole heads, and the key blocks of the heads that are left are dealt over all XCDs. With
+// contiguous eighths of everything instead, an XCD of a few-headed problem got the long lists of a head
+// and its neighbour the short ones (5 heads, 528 blocks of 128: 2.10 ms; 12 heads, 512 blocks of 64:
+// 1.73 ms).
 constexpr int kDkvNbuf = 4;  // LDS stages of sparse_dkv_kernel: 32 Q rows, 32 dO rows, lse/D (17 KB)
+// Workgroups of the grid, and the place (head * nb + rank) workgroup wg takes, -1 for none.
+__host__ __device__ inline int dkv_grid(int heads, int nb) {
+  return kNumXcd * (heads / kNumXcd * nb + (heads % kNumXcd * nb + kNumXcd - 1) / kNumXcd);
+}
+__host__ __device__ inline int dkv_place(int wg, int heads, int nb) {
+  const int xcd = wg % kNumXcd, i = wg / kNumXcd, whole = heads / kNumXcd * nb;
+  if (i < whole) return xcd * whole + i;
+  const int d = (i - whole) * kNumXcd + xcd;
+  return d < heads % kNumXcd * nb ? kNumXcd * whole + d : -1;
+}
+
 template <int BLK, int NBUF>
 __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void sparse_dkv_kernel(
-    int N, int nb, int total, const int32_t* __restrict__ rev, float scale_log2, float scale,
+    int N, int nb, int heads, const int32_t* __restrict__ rev, float scale_log2, float scale,
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float2* __restrict__ lseD, const int32_t* __restrict__ order,
     float* __restrict__ dK, float* __restrict__ dV) {
@@ -307,7 +324,8 @@ void sparse_dkv_kernel(
   __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE + 2 * PBUF];
 
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
-  const int L = xcd_remap(blockIdx.x, total);
+  const int L = dkv_place(blockIdx.x, heads, nb);
+  if (L < 0) return;
   const long head = L / nb;
   const int J = ((const_i32)order)[L];  // key blocks of one head, longer lists first
   const int tid = threadIdx.x, lane = tid % 64, hh = lane / 32;
@@ -516,7 +534,8 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
                        idx, keep, sl, scale, (const bf16*)Qr, (const bf16*)Kr, (const bf16*)V,
                        (const bf16*)dOs, (const float2*)lseD, dQ);
   }
-  hipLaunchKernelGGL((sparse_dkv_kernel<BLK, kDkvNbuf>), dim3(total), dim3(BLK * 4), 0, st, s.N, nb, total,
+  hipLaunchKernelGGL((sparse_dkv_kernel<BLK, kDkvNbuf>), dim3(dkv_grid((int)heads, nb)), dim3(BLK * 4), 0,
+                     st, s.N, nb, (int)heads,
                      (const int32_t*)rev, sl, scale, (const bf16*)Qr, (const bf16*)Kr,
                      (const bf16*)V, (const bf16*)dOs, (const float2*)lseD, (const int32_t*)order,
                      dK, dV);
