@@ -121,13 +121,12 @@ hipError_t launch_lowrank_backward(const Shape& s, const void* Qn, const void* K
                                    void* dOs, float* dQn, float* dKn, float* dV, float* dPq,
                                    float* dPk, float* dlogits, void* ws, hipStream_t st);
 
-// sparse_attn.hip: dQ^r of the block-sparse attention on the paired, queued attention kernel
-// (bf16, d 128, block 64: dq_supported); lseD: per query {log-sum-exp (log2), D = dO^s . O^s};
-// ws: sparse_workspace_bytes(s, 64, keep).
-bool dq_supported(const Shape& s, int block);
-hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int keep,
-                            const int32_t* idx, float scale, const void* dO, const void* lseD,
-                            float* dQ, void* ws, hipStream_t st);
+// sparse_attn.hip: dQ^r of the block-sparse attention on the attention kernel (bf16, d 128, block 64:
+// paired and queued, or 128); lseD: per query {log-sum-exp (log2), D = dO^s . O^s}; ws:
+// sparse_workspace_bytes(s, block, keep).
+hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
+                            int keep, const int32_t* idx, float scale, const void* dO,
+                            const void* lseD, float* dQ, void* ws, hipStream_t st);
 
 // sparse_bwd.hip: gradients of the block-sparse attention (bf16, d 128, block 64 or 128, at most
 // kBwdMaxBlocks blocks per head: the transposed lists are built through one LDS word per block);

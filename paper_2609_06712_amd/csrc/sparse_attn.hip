@@ -1196,18 +1196,21 @@ size_t fuse_workspace_bytes(const Shape& s, int r) {
 
 bool fuse_supported(const Shape& s, int r) { return s.bf16 && s.d == 128 && r >= 16 && r <= 64; }
 
-bool dq_supported(const Shape& s, int block) {
-  return s.bf16 && s.d == 128 && block == 64;
-}
-
-hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int keep,
-                            const int32_t* idx, float scale, const void* dO, const void* lseD,
-                            float* dQ, void* ws, hipStream_t st) {
+hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
+                            int keep, const int32_t* idx, float scale, const void* dO,
+                            const void* lseD, float* dQ, void* ws, hipStream_t st) {
+  const DqArgs dq{(const bf16*)dO, (const float2*)lseD, dQ};
+  const FuseArgs none{};
+  if (block == 128) {
+    if (keep <= kTable)
+      return launch_bf16_tab<128, 1, 3, kTable, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
+                                                         nullptr, none, nullptr, st, dq);
+    return launch_bf16_tab<128, 1, 3, 0, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
+                                                  nullptr, none, nullptr, st, dq);
+  }
   Groups gr;
   const hipError_t e = prepare_groups<true>(s, keep, idx, ws, 0, st, gr);
   if (e != hipSuccess) return e;
-  const DqArgs dq{(const bf16*)dO, (const float2*)lseD, dQ};
-  const FuseArgs none{};
   if (gr.stride - 1 <= kTable)
     return launch_bf16_tab<64, 2, 3, kTable, 0, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs,
                                                       scale, nullptr, none, gr.queue, st, dq);

@@ -4,27 +4,27 @@
 // block lists are constant (the selection is piecewise constant in Q^r, K^r).
 //
 // With P = exp(S*scale - lse) and D_q = sum_c dO^s_qc O^s_qc:  dP = dO V^T,  dS = P (dP - D),
-// dQ = scale dS K,  dK = scale dS^T Q,  dV = P^T dO.  Two kernels, each recomputing S and P:
-//   sparse_dq_kernel   per query block, walking its own list (as the forward): Q and dO of the wave's
-//                      32 queries in registers, K and V sub-tiles through three LDS stages;
+// dQ = scale dS K,  dK = scale dS^T Q,  dV = P^T dO.  Two passes, each recomputing S and P:
+//   dQ                 the forward's attention kernel in its dQ mode, per query block (or pair) over its
+//                      own list (a kernel of its own, which handed dS to the transposed product through
+//                      LDS, took 0.93 ms where this takes 0.88: 5 heads, 67545 tokens, blocks of 128);
 //   sparse_dkv_kernel  per key block, walking the query blocks that selected it (lists transposed by
 //                      bwd_reverse_kernel) in 32-query steps: one role of waves holds the keys' K
 //                      (S, P, dV), the other their V (dP, dS, dK) and takes P from the first one
 //                      step later; Q and dO rows (and the queries' lse and D) through four LDS
 //                      stages.
 // Products on v_mfma_f32_32x32x16_bf16. S and dP come out with one lane per key and the 32 queries
-// in its registers; the products that contract over keys (dQ) or queries (dK, dV) take their other
-// operand through the transposing LDS read ds_read_b64_tr_b16, in the order the registers hold the
-// contracted index (as the forward's P V). dQ needs dS with one lane per query: each wave passes its
-// dS tile through 2 KB of LDS. Tiles are stored with a swizzle that keeps both the row reads and the
-// transposing reads free of bank conflicts. Gradients are fp32.
+// in its registers; the products that contract over queries (dK, dV) take their other operand through
+// the transposing LDS read ds_read_b64_tr_b16, in the order the registers hold the contracted index (as
+// the forward's P V). Tiles are stored with a swizzle that keeps both the row reads and the transposing
+// reads free of bank conflicts. Gradients are fp32.
 #include "common.h"
 #include "launch.h"
 
 namespace rola {
 namespace {
 
-constexpr int kBSub = 32;      // keys (dQ) or queries (dK, dV) per sub-tile
+constexpr int kBSub = 32;     // queries per sub-tile
 constexpr int kLsePad = 128;  // zero entries after the packed lse/D array: a sub-tile of the last
                               // query block reads up to block - 1 entries past the last query
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -124,156 +124,6 @@ __global__ __launch_bounds__(256) void bwd_order_kernel(int nb, int chunks,
   int rank = 0;
   for (int K = 0; K < nb; ++K) rank += len[K] > e || (len[K] == e && K < J);
   order[head * nb + rank] = J;
-}
-
-// ---- dQ: one workgroup per (b, h, query block), BLK/32 waves of 32 queries -------------------------
-template <int BLK, int NBUF>
-__global__ __launch_bounds__(BLK * 2, 2) void sparse_dq_kernel(
-    int N, int nb, int total, const int32_t* __restrict__ lists, int keep, float scale_log2,
-    float scale, const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
-    const bf16* __restrict__ dO, const float2* __restrict__ lseD, float* __restrict__ dQ) {
-  constexpr int D = 128, NW = BLK / 32;
-  constexpr int TILE = kBSub * D * 2, STAGE = 2 * TILE;
-  constexpr int DMA_PER_WAVE = TILE / 1024 / NW, SUBS = BLK / kBSub;
-  constexpr int SPITCH = 72;  // bytes per row of the dS^T scratch tile (32 queries + 4 pad)
-  __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE];
-  __shared__ __attribute__((aligned(16))) char scr[NW][kBSub * SPITCH];
-
-  const int L = xcd_remap(blockIdx.x, total);
-  const int I = L % nb;
-  const long head = L / nb;
-  const int tid = threadIdx.x, lane = tid % 64, hh = lane / 32;
-  const int wave = wave_uniform(tid / 64);
-  const int qrow0 = I * BLK + wave * 32;  // the wave's first query
-  const int q = qrow0 + lane % 32;        // A-operand row of this lane (and column of dQ^T)
-  const bool qvalid = q < N;
-  const long hoff = head * (long)N * D;
-  const char* Kh = reinterpret_cast<const char*>(K + hoff);
-  const char* Vh = reinterpret_cast<const char*>(V + hoff);
-  typedef const __attribute__((address_space(4))) int32_t* const_i32;
-  const const_i32 slist = (const_i32)(lists + (head * nb + I) * (long)keep);
-  const int T = keep * SUBS;
-
-  bf16x8 qf[8], df[8];
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    qf[s] = qvalid ? *reinterpret_cast<const bf16x8*>(Q + hoff + (long)q * D + 16 * s + 8 * hh) : bf16x8{};
-    df[s] = qvalid ? *reinterpret_cast<const bf16x8*>(dO + hoff + (long)q * D + 16 * s + 8 * hh) : bf16x8{};
-  }
-  // lse and D of the rows 8j + 4(l/32) + i the S tiles hand this lane; +inf lse for rows past N
-  float lse[16], dsum[16];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = qrow0 + 8 * j + 4 * hh + i;
-      const float2 v = r < N ? lseD[head * (long)N + r] : make_float2(INFINITY, 0.f);
-      lse[4 * j + i] = v.x;
-      dsum[4 * j + i] = v.y;
-    }
-  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0): nothing of this waits in the loop
-
-  f32x16 acc[4];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) acc[w] = f32x16{};
-
-  uint32_t dsrc[DMA_PER_WAVE];
-#pragma unroll
-  for (int i = 0; i < DMA_PER_WAVE; ++i) {
-    const int row = 4 * (wave * DMA_PER_WAVE + i) + lane / 16, pos = lane % 16;
-    dsrc[i] = row * D * 2 + ((pos ^ bw_swizzle(row)) << 4);
-  }
-  const uint32_t lds0 = lds_address(lds);
-  auto key0 = [&](int t) {
-    const int J = slist[t / SUBS];
-    return (unsigned)J < (unsigned)nb ? J * BLK + (t % SUBS) * kBSub : -1;
-  };
-  auto issue = [&](int k0, int buf) {  // 2 * DMA_PER_WAVE loads per wave, always
-    k0 = max(k0, 0);
-    const uint32_t dst = lds0 + buf * STAGE;
-#pragma unroll
-    for (int i = 0; i < DMA_PER_WAVE; ++i) {
-      const uint32_t slot = (wave * DMA_PER_WAVE + i) * 1024;
-      const int r = 4 * (wave * DMA_PER_WAVE + i) + lane / 16;
-      const uint32_t rowoff = (uint32_t)(min(k0 + r, N - 1) - r) * (D * 2);  // rows past N: N-1
-      dma16(Kh, rowoff + dsrc[i], dst + slot);
-      dma16(Vh, rowoff + dsrc[i], dst + TILE + slot);
-    }
-  };
-  char* sc = scr[wave];
-
-  constexpr int PER_STEP = 2 * DMA_PER_WAVE;
-  int issued = 0;
-#pragma unroll
-  for (int j = 0; j < NBUF - 1; ++j)
-    if (j < T) issue(key0(j), j), ++issued;
-  for (int t = 0; t < T;) {
-#pragma unroll
-    for (int b = 0; b < NBUF; ++b) {
-      if (t >= T) break;
-      if (issued == t + NBUF - 1) {
-        constexpr int allowed = PER_STEP * (NBUF - 2);
-        __builtin_amdgcn_s_waitcnt((allowed & 15) | ((allowed >> 4) << 14) | (7 << 4) | (15 << 8));
-      } else {
-        __builtin_amdgcn_s_waitcnt(0);
-      }
-      __syncthreads();
-      if (issued < T) issue(key0(issued), (b + NBUF - 1) % NBUF), ++issued;
-      const int k0 = key0(t);
-      if (k0 >= 0 && k0 < N) {
-        const char* Kt = lds + b * STAGE;
-        const char* Vt = Kt + TILE;
-        f32x16 S = f32x16{}, dP = f32x16{};
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          S = mfma32(qf[s], row_frag(Kt, lane % 32, s, hh), S);
-          dP = mfma32(df[s], row_frag(Vt, lane % 32, s, hh), dP);
-        }
-        // dS with one lane per key (column l%32); rows 8j + 4(l/32) + i are queries
-        const bool kvalid = k0 + lane % 32 < N;
-        bf16x4 ds4[4];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const float e = __builtin_amdgcn_exp2f(fmaf(S[k], scale_log2, -lse[k]));
-          const float p = kvalid ? e : 0.f;
-          ds4[k / 4][k % 4] = (bf16)(p * (dP[k] - dsum[k]));
-        }
-        // dS^T row-major [key][query] in the wave's scratch, then read back transposed
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<bf16x4*>(sc + (lane % 32) * SPITCH + 2 * (8 * j + 4 * hh)) = ds4[j];
-        asm volatile("" ::: "memory");  // the reads below follow the writes (one wave, in order)
-        bf16x8 dsf[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int i16 = lane % 16, g1 = (lane / 16) & 1;
-          bf16x4 part[2];
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const int row = 16 * u + 8 * half + 4 * hh + i16 / 4;
-            part[half] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                (lds_bf16x4*)(sc + row * SPITCH + 2 * (16 * g1 + 4 * (i16 & 3))));
-          }
-          dsf[u] = __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7);
-        }
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-#pragma unroll
-          for (int u = 0; u < 2; ++u) acc[w] = mfma32(tr_frag(Kt, w, u, lane), dsf[u], acc[w]);
-      }
-      ++t;
-    }
-  }
-  if (qvalid) {  // dQ^T: lane = query, rows = channels 32w + 8j + 4(l/32) + i
-    float* dq = dQ + hoff + (long)q * D;
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<float4*>(dq + 32 * w + 8 * j + 4 * hh) =
-            make_float4(acc[w][4 * j] * scale, acc[w][4 * j + 1] * scale, acc[w][4 * j + 2] * scale,
-                        acc[w][4 * j + 3] * scale);
-  }
 }
 
 // ---- dK, dV: one workgroup per (b, h, key block) ------------------------------------------------
@@ -489,8 +339,8 @@ void sparse_dkv_kernel(
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workspace: [lse, D per query][bitmaps][transposed lists][key-block order][with dq_supported: the
-// attention workspace of the dQ pass (pairs, merged lists, queue counters)].
+// Workspace: [lse, D per query][bitmaps][transposed lists][key-block order][the attention
+// workspace of the dQ pass (pairs, merged lists, queue counters; none with 128-token blocks)].
 struct BwdWs {
   size_t lsed, bits, rev, order, dq;
 };
@@ -498,7 +348,7 @@ BwdWs bwd_layout(const Shape& s, int block, int keep) {
   const size_t heads = (size_t)s.B * s.H, nb = num_blocks(s.N, block), words = (nb + 31) / 32;
   return {align256((heads * s.N + kLsePad) * sizeof(float2)), align256(heads * nb * words * 4),
           align256(heads * nb * (nb + 1) * 4), align256(heads * nb * 4),
-          dq_supported(s, block) ? align256(sparse_workspace_bytes(s, block, keep)) : 0};
+          align256(sparse_workspace_bytes(s, block, keep))};
 }
 
 template <int BLK>
@@ -523,17 +373,11 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
   const int ochunks = (nb + 255) / 256;
   hipLaunchKernelGGL(bwd_order_kernel, dim3((unsigned)(heads * ochunks)), dim3(256),
                      nb * sizeof(int32_t), st, nb, ochunks, (const int32_t*)rev, order);
-  const int total = (int)(heads * nb);
   const float sl = scale * 1.4426950408889634f;
-  if (dq_supported(s, BLK)) {  // dQ on the paired, queued attention kernel
-    const hipError_t e2 = launch_sparse_dq(s, Qr, Kr, V, keep, idx, scale, dOs, lseD, dQ,
-                                           (char*)ws + lay.lsed + lay.bits + lay.rev + lay.order, st);
-    if (e2 != hipSuccess) return e2;
-  } else {
-    hipLaunchKernelGGL((sparse_dq_kernel<BLK, 3>), dim3(total), dim3(BLK * 2), 0, st, s.N, nb, total,
-                       idx, keep, sl, scale, (const bf16*)Qr, (const bf16*)Kr, (const bf16*)V,
-                       (const bf16*)dOs, (const float2*)lseD, dQ);
-  }
+  // dQ on the attention kernel (block 64: paired, queued)
+  const hipError_t e2 = launch_sparse_dq(s, Qr, Kr, V, BLK, keep, idx, scale, dOs, lseD, dQ,
+                                         (char*)ws + lay.lsed + lay.bits + lay.rev + lay.order, st);
+  if (e2 != hipSuccess) return e2;
   hipLaunchKernelGGL((sparse_dkv_kernel<BLK, kDkvNbuf>), dim3(dkv_grid((int)heads, nb)), dim3(BLK * 4), 0,
                      st, s.N, nb, (int)heads,
                      (const int32_t*)rev, sl, scale, (const bf16*)Qr, (const bf16*)Kr,
