@@ -215,6 +215,39 @@ def test_bf16_long_merged_lists_sampled():
     _sampled(w, heads=[0, 1], count=6)
 
 
+@pytest.mark.parametrize("d,split,grid,offset", [
+    (128, (44, 42, 42), (3, 5, 97), (0, 0, 0)), (128, (44, 42, 42), (1, 1, 500), (1, -5, 7)),
+    (128, (44, 42, 42), (37, 1, 1), (0, 0, 0)), (128, (2, 2, 124), (2, 3, 67), (0, 0, 0)),
+    (64, (28, 18, 18), (3, 3, 230), (0, 0, 0)), (64, (60, 2, 2), (5, 7, 2), (0, 2, 0))])
+def test_rope_tables_edges(d, split, grid, offset):
+    """Row groups and x pieces of the table kernel: every entry within one fp32 rounding of cos / sin
+    of the exact angle."""
+    prob = R.problem(1, 1, math.prod(grid), d, grid, "f32")
+    cos, sin = R.rola_rope_tables(prob, split, offset=offset)
+    ocos, osin = O.rope_tables(*grid, split, offset=offset)
+    np.testing.assert_allclose(T.to_np(cos), ocos, rtol=2.0 ** -23, atol=2e-15 * 1e4)
+    np.testing.assert_allclose(T.to_np(sin), osin, rtol=2.0 ** -23, atol=2e-15 * 1e4)
+
+
+@pytest.mark.parametrize("dtype,d,B,H,grid", [("bf16", 128, 1, 1, (1, 3, 5)), ("bf16", 128, 3, 3, (2, 9, 11)),
+                                              ("f32", 64, 1, 5, (3, 5, 7)), ("f32", 128, 2, 17, (1, 1, 1)),
+                                              ("bf16", 128, 1, 13, (11, 30, 52))])
+def test_rope_apply_heads(dtype, d, B, H, grid):
+    """Head groups and batches of the rotation (remainders of eight and four), against the oracle."""
+    split = (28, 18, 18) if d == 64 else (44, 42, 42)
+    w = synth.TINY.replace(grid=grid, H=H, B=B, d_h=d, dtype=dtype, split=split)
+    N = w.N
+    X = torch.randn((B, H, N, d), generator=torch.Generator().manual_seed(H)).to(synth.torch_dtype(dtype))
+    prob = R.problem(B, H, N, d, grid, dtype)
+    cos, sin = R.rola_rope_tables(prob, split)
+    got = T.to_np(R.rola_rope_apply(X.cuda(), cos, sin, grid))
+    want = O.rotate(X.double().numpy(), *O.rope_tables(*grid, split))
+    # fp32 products and one rounding to the type: |x| + |y| of the pair bounds each term
+    pair = np.abs(X.double().numpy()).reshape(B, H, N, d // 2, 2).sum(-1).repeat(2, -1)
+    ulp = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -22
+    assert np.all(np.abs(got - want) <= ulp * np.abs(want) + 2.0 ** -21 * pair)
+
+
 @pytest.mark.parametrize("dtype,grid,block", [("bf16", (3, 10, 13), 64), ("bf16", (3, 10, 13), 128),
                                               ("f32", (4, 8, 8), 32)])
 def test_dense_reference_kernel(dtype, grid, block):
