@@ -87,43 +87,60 @@ __host__ __device__ inline int rev_walk_bits(int nb) {
 }
 
 // Transposed lists: rev[head][J] = count, then the query blocks I that selected J in walk order.
-// One wave per (head, 32 key blocks): the bitmap column of the 32 key blocks over every query block
-// goes to LDS (nb words), then lane j < 32 collects key block 32w + j's list.
-__global__ __launch_bounds__(64) void bwd_reverse_kernel(int nb, int words, int kb,
-                                                         const uint32_t* __restrict__ bits,
-                                                         int32_t* __restrict__ rev) {
-  extern __shared__ uint32_t col[];  // [nb]: bit j of col[I] = query block I selected J = 32w + j
+// One workgroup per (head, 32 key blocks): the bitmap column of the 32 key blocks goes to LDS in walk
+// order ([1 << kb] words), then each wave collects a key block at a time, 64 walk positions per step
+// (ballot and prefix count). With one lane per key block walking all positions the serial chain took
+// 47 us at 12 heads of 512 blocks and 55 at 5 of 528; 12 and 20 now.
+__global__ __launch_bounds__(256) void bwd_reverse_kernel(int nb, int words, int kb,
+                                                          const uint32_t* __restrict__ bits,
+                                                          int32_t* __restrict__ rev) {
+  extern __shared__ uint32_t col[];  // [1 << kb]: bit j of col[p] = query block brev(p) selected 32w + j
   const long head = blockIdx.x / words;
-  const int w = (int)(blockIdx.x % words), lane = threadIdx.x;
-  for (int I = lane; I < nb; I += 64) col[I] = bits[(head * nb + I) * words + w];
+  const int w = (int)(blockIdx.x % words), tid = threadIdx.x, lane = tid % 64;
+  const int np = 1 << kb;
+  auto block_at = [&](int p) { return (int)(__brev((unsigned)p) >> (32 - kb)); };  // an involution
+  for (int I = tid; I < np; I += 256)
+    col[block_at(I)] = I < nb ? bits[(head * nb + I) * words + w] : 0u;
   __syncthreads();
-  const int J = 32 * w + lane;
-  if (lane >= 32 || J >= nb) return;
-  int32_t* out = rev + (head * nb + J) * (long)(nb + 1);
-  int cnt = 0;
-  for (int p = 0; p < (1 << kb); ++p) {
-    const int I = (int)(__brev((unsigned)p) >> (32 - kb));
-    if (I < nb && ((col[I] >> lane) & 1u)) out[1 + cnt++] = I;
+  for (int j = wave_uniform(tid / 64); j < 32; j += 4) {
+    const int J = 32 * w + j;
+    if (J >= nb) break;
+    int32_t* out = rev + (head * nb + J) * (long)(nb + 1);
+    int cnt = 0;
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      const int p = p0 + lane;
+      const bool has = p < np && ((col[p] >> j) & 1u);
+      const uint64_t m = __ballot(has);
+      if (has) out[1 + cnt + __popcll(m & ((1ull << lane) - 1))] = block_at(p);
+      cnt += __popcll(m);
+    }
+    if (lane == 0) out[0] = cnt;
   }
-  out[0] = cnt;
 }
 
 // Order of the key blocks for the dK/dV workgroups: longer lists first (equal lengths by ascending
-// J), order[head][rank] = J. One workgroup per (head, 256 key blocks): every list length of the
-// head goes to LDS, and each thread ranks one key block against all of them.
-__global__ __launch_bounds__(256) void bwd_order_kernel(int nb, int chunks,
-                                                        const int32_t* __restrict__ rev,
-                                                        int32_t* __restrict__ order) {
+// J), order[head][rank] = J. One workgroup per (head, 64 key blocks): every list length of the head
+// goes to LDS, and four threads rank one key block against a quarter of them each.
+constexpr int kOrderBlocks = 64;
+__global__ __launch_bounds__(4 * kOrderBlocks) void bwd_order_kernel(int nb, int chunks,
+                                                                     const int32_t* __restrict__ rev,
+                                                                     int32_t* __restrict__ order) {
   extern __shared__ int32_t len[];  // [nb]
+  __shared__ int32_t part[4][kOrderBlocks];
   const long head = blockIdx.x / chunks;
-  const int J = (int)(blockIdx.x % chunks) * 256 + threadIdx.x;
-  for (int K = threadIdx.x; K < nb; K += 256) len[K] = rev[(head * nb + K) * (long)(nb + 1)];
+  const int tid = threadIdx.x, jl = tid % kOrderBlocks, quarter = wave_uniform(tid / kOrderBlocks);
+  const int J = (int)(blockIdx.x % chunks) * kOrderBlocks + jl;
+  for (int K = tid; K < nb; K += 4 * kOrderBlocks) len[K] = rev[(head * nb + K) * (long)(nb + 1)];
   __syncthreads();
-  if (J >= nb) return;
-  const int e = len[J];
+  const int e = len[min(J, nb - 1)];
+  const int per = (nb + 3) / 4, k1 = min(nb, (quarter + 1) * per);
   int rank = 0;
-  for (int K = 0; K < nb; ++K) rank += len[K] > e || (len[K] == e && K < J);
-  order[head * nb + rank] = J;
+#pragma unroll 8
+  for (int K = quarter * per; K < k1; ++K) rank += len[K] > e || (len[K] == e && K < J);
+  part[quarter][jl] = rank;
+  __syncthreads();
+  if (quarter == 0 && J < nb)
+    order[head * nb + part[0][jl] + part[1][jl] + part[2][jl] + part[3][jl]] = J;
 }
 
 // ---- dK, dV: one workgroup per (b, h, key block) ------------------------------------------------
@@ -367,11 +384,11 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
                      st, rows, (const bf16*)Os, (const bf16*)dOs, lse, lseD);
   hipLaunchKernelGGL(bwd_bits_kernel, dim3((unsigned)(heads * nb)), dim3(64), words * sizeof(uint32_t),
                      st, nb, keep, words, idx, bits);
-  hipLaunchKernelGGL(bwd_reverse_kernel, dim3((unsigned)(heads * words)), dim3(64),
-                     nb * sizeof(uint32_t), st, nb, words, rev_walk_bits(nb), (const uint32_t*)bits,
-                     rev);
-  const int ochunks = (nb + 255) / 256;
-  hipLaunchKernelGGL(bwd_order_kernel, dim3((unsigned)(heads * ochunks)), dim3(256),
+  const int kb = rev_walk_bits(nb);
+  hipLaunchKernelGGL(bwd_reverse_kernel, dim3((unsigned)(heads * words)), dim3(256),
+                     sizeof(uint32_t) << kb, st, nb, words, kb, (const uint32_t*)bits, rev);
+  const int ochunks = (nb + kOrderBlocks - 1) / kOrderBlocks;
+  hipLaunchKernelGGL(bwd_order_kernel, dim3((unsigned)(heads * ochunks)), dim3(4 * kOrderBlocks),
                      nb * sizeof(int32_t), st, nb, ochunks, (const int32_t*)rev, order);
   const float sl = scale * 1.4426950408889634f;
   // dQ on the attention kernel (block 64: paired, queued)

@@ -117,6 +117,32 @@ def test_sparse_backward_uneven_transposed_lists(block):
             assert torch.count_nonzero(dk[0, h, rows]) == 0 and torch.count_nonzero(dv[0, h, rows]) == 0
 
 
+@pytest.mark.parametrize("grid,block,H,B", [((3, 20, 33), 64, 3, 3), ((5, 17, 31), 128, 10, 1),
+                                            ((1, 9, 7), 64, 1, 1)])
+def test_sparse_backward_heads_over_xcds(grid, block, H, B):
+    """Key blocks dealt over the XCDs (whole heads plus a remainder: 9 and 10 heads; 1 head), and
+    transposed lists of block counts off the powers of two and the 64-position steps, against the
+    gradient oracle."""
+    w = synth.WAN_1_3B_480P.replace(grid=grid, H=H, B=B, block=block, sparsity=0.8)
+    d = {k: v.cuda() for k, v in synth.make_inputs(w, 21).items()}
+    g = w.grid
+    prob = R.problem(w.B, w.H, w.N, w.d_h, g, w.dtype)
+    cos, sin = R.rola_rope_tables(prob, w.split)
+    qr = R.rola_rope_apply(d["Qn"], cos, sin, g)
+    kr = R.rola_rope_apply(d["Kn"], cos, sin, g)
+    idx = R.rola_block_select(qr, kr, g, block, w.sparsity)
+    os_, lse = R.rola_sparse_attn_lse(qr, kr, d["V"], g, block, w.sparsity, idx)
+    dos = torch.randn(qr.shape, generator=torch.Generator().manual_seed(4)).to(torch.bfloat16).cuda()
+    dq, dk, dv = R.rola_sparse_attn_backward(qr, kr, d["V"], g, block, w.sparsity, idx, os_, lse, dos)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(H):
+            want = G.sparse_attention_grads(_f64(qr[b, h]), _f64(kr[b, h]), _f64(d["V"][b, h]),
+                                            idx[b, h].cpu().numpy(), block, w.d_h ** -0.5, _f64(dos[b, h]))
+            for n, t in (("dqr", dq), ("dkr", dk), ("dv", dv)):
+                assert _rel(_f64(t[b, h]), want[n]) <= 1e-2, (b, h, n)
+
+
 def test_sparse_backward_many_groups():
     """200 heads of 390 tokens: 800 (head, pair) groups, more than the chip holds at once, so the dQ
     pass's resident workgroups each take several groups from the work queues. Sampled heads against
