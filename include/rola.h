@@ -274,6 +274,16 @@ rola_status rola_sparse_attn_backward(const rola_problem* p, const void* Qr, con
                                       const int32_t* blk_idx, float softmax_scale, const void* Os,
                                       const float* lse, const void* dOs, float* dQr, float* dKr,
                                       float* dV, void* ws, size_t ws_bytes, hipStream_t stream);
+/* The same gradients carried through the main-path rotation and added to what the low-rank branch left
+ * in dQn, dKn and dV (fp32 [B, H, N, d_h], read and written): dQn += R(p)^T dQ^r, dKn += R(p)^T dK^r, dV +=
+ * dV of the sparse branch, i.e. rola_sparse_attn_backward followed by three
+ * rola_rope_backward_accumulate calls, without dQ^r, dK^r and the branch's dV in memory. Tables and
+ * rope_ld as in rola_rope_apply; N rope_ld < 2^31 (ROLA_ERR_UNSUPPORTED beyond). */
+rola_status rola_sparse_attn_backward_accumulate(
+    const rola_problem* p, const void* Qr, const void* Kr, const void* V, int32_t block,
+    double sparsity, const int32_t* blk_idx, float softmax_scale, const void* Os, const float* lse,
+    const void* dOs, const float* cos_tab, const float* sin_tab, int32_t rope_ld, float* dQn,
+    float* dKn, float* dV, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* ---- backward of the low-rank branch, the fusion and the gate (fine-tuning, Sec. 4.5) ----------
  * rola_lowrank_backward: gradients of <dO, O> with O = (O^s / r_s + sigma(logit) RMSNorm(q~^T C)) r_s

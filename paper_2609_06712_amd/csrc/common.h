@@ -96,6 +96,50 @@ __device__ __forceinline__ void rope_pair(float a, float b, float c, float s, fl
   y = fmaf(a, s, b * c);
 }
 
+// Stores 128 channels of a gradient row from the accumulator layout of a 32x32 tile set (this lane: row
+// r, channels 32w + 8j + 4 hh .. +3 in acc[w][4j ..]), scaled by f. With ADD it is added to the row, after
+// the transposed rotation R(p)^T of its pairs when `cos_row` (this row's table entries) is not null.
+template <bool ADD>
+__device__ __forceinline__ void store_grad_row(float* row, const f32x16 (&acc)[4], float f, int hh,
+                                               const float* cos_row, const float* sin_row) {
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    float4 old[4];
+    float2 c[4], s[4];
+    if constexpr (ADD) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int ch = 32 * w + 8 * j + 4 * hh;
+        old[j] = *reinterpret_cast<const float4*>(row + ch);
+        c[j] = make_float2(1.f, 1.f);
+        s[j] = make_float2(0.f, 0.f);
+        if (cos_row) {  // uniform
+          c[j] = *reinterpret_cast<const float2*>(cos_row + ch / 2);
+          s[j] = *reinterpret_cast<const float2*>(sin_row + ch / 2);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float a = acc[w][4 * j] * f, b = acc[w][4 * j + 1] * f;
+      const float d = acc[w][4 * j + 2] * f, e = acc[w][4 * j + 3] * f;
+      float4 o = make_float4(a, b, d, e);
+      if constexpr (ADD) {
+        o = old[j];
+        if (cos_row) {
+          o.x += a * c[j].x + b * s[j].x;
+          o.y += b * c[j].x - a * s[j].x;
+          o.z += d * c[j].y + e * s[j].y;
+          o.w += e * c[j].y - d * s[j].y;
+        } else {
+          o.x += a, o.y += b, o.z += d, o.w += e;
+        }
+      }
+      *reinterpret_cast<float4*>(row + 32 * w + 8 * j + 4 * hh) = o;
+    }
+  }
+}
+
 // SiLU and the logistic gate with a hardware reciprocal (1 ulp) instead of an IEEE divide.
 __device__ __forceinline__ float sigmoid(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 __device__ __forceinline__ float silu(float x) { return x * sigmoid(x); }

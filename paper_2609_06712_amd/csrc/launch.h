@@ -121,12 +121,20 @@ hipError_t launch_lowrank_backward(const Shape& s, const void* Qn, const void* K
                                    void* dOs, float* dQn, float* dKn, float* dV, float* dPq,
                                    float* dPk, float* dlogits, void* ws, hipStream_t st);
 
+// Rotary tables of the accumulating form of the sparse backward: with cos_tab set, the gradients of Q^r
+// and K^r are rotated back (R(p)^T) and added to the outputs, dV is added; otherwise they are stored.
+struct GradTables {
+  const float* cos_tab = nullptr;
+  const float* sin_tab = nullptr;
+  int ld = 0;
+};
 // sparse_attn.hip: dQ^r of the block-sparse attention on the attention kernel (bf16, d 128, block 64:
 // paired and queued, or 128); lseD: per query {log-sum-exp (log2), D = dO^s . O^s}; ws:
 // sparse_workspace_bytes(s, block, keep).
 hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
                             int keep, const int32_t* idx, float scale, const void* dO,
-                            const void* lseD, float* dQ, void* ws, hipStream_t st);
+                            const void* lseD, const GradTables& acc, float* dQ, void* ws,
+                            hipStream_t st);
 
 // sparse_bwd.hip: gradients of the block-sparse attention (bf16, d 128, block 64 or 128, at most
 // kBwdMaxBlocks blocks per head: the transposed lists are built through one LDS word per block);
@@ -135,8 +143,9 @@ constexpr int kBwdMaxBlocks = 16384;
 size_t sparse_backward_workspace_bytes(const Shape& s, int block, int keep);
 hipError_t launch_sparse_backward(const Shape& s, const void* Qr, const void* Kr, const void* V,
                                   int block, int keep, const int32_t* idx, float scale,
-                                  const void* Os, const float* lse, const void* dOs, float* dQ,
-                                  float* dK, float* dV, void* ws, hipStream_t st);
+                                  const void* Os, const float* lse, const void* dOs,
+                                  const GradTables& acc, float* dQ, float* dK, float* dV, void* ws,
+                                  hipStream_t st);
 
 // lowrank.hip
 int summary_chunks(const Shape& s, int r);

@@ -472,41 +472,60 @@ size_t rola_sparse_backward_workspace_bytes(const rola_problem* p, int32_t block
       s, block, rola_keep_blocks(rola::num_blocks(s.N, block), sparsity));
 }
 
+// Both sparse backward calls; acc: tables for the accumulating form (null otherwise).
+static rola_status sparse_backward(const rola_problem* p, const void* Qr, const void* Kr, const void* V,
+                                   int32_t block, double sparsity, const int32_t* blk_idx,
+                                   float softmax_scale, const void* Os, const float* lse,
+                                   const void* dOs, const rola::GradTables* acc, float* dQ, float* dK,
+                                   float* dV, void* ws, size_t ws_bytes, hipStream_t stream,
+                                   const char* fn) {
+  rola::Shape s;
+  TRY(check_problem(p, fn, &s));
+  TRY(check_block(s, block, fn));
+  TRY(check_sparsity(sparsity, fn));
+  if (!s.bf16) return fail(ROLA_ERR_UNSUPPORTED, "%s: built for the bf16 path", fn);
+  if (rola::num_blocks(s.N, block) > rola::kBwdMaxBlocks)
+    return fail(ROLA_ERR_UNSUPPORTED, "%s: %d blocks per head, at most %d", fn,
+                rola::num_blocks(s.N, block), rola::kBwdMaxBlocks);
+  const Named ptrs[] = {{Qr, "Qr"}, {Kr, "Kr"}, {V, "V"}, {blk_idx, "blk_idx"}, {Os, "Os"},
+                        {lse, "lse"}, {dOs, "dOs"}, {dQ, "dQ"}, {dK, "dK"}, {dV, "dV"}, {ws, "ws"}};
+  for (const Named& q : ptrs)
+    if (!aligned(q.p))
+      return fail(ROLA_ERR_INVALID_ARGUMENT, "%s: %s is null or not 16-byte aligned", fn, q.name);
+  if (acc) {
+    TRY(check_tables(acc->cos_tab, acc->sin_tab, acc->ld, s.d / 2, fn));
+    if ((unsigned __int128)s.N * (unsigned)acc->ld > (unsigned __int128)((1ll << 31) - 1))
+      return fail(ROLA_ERR_UNSUPPORTED, "%s: N*rope_ld must be below 2^31", fn);
+  }
+  if (!(softmax_scale > 0.f) || !isfinite(softmax_scale))
+    return fail(ROLA_ERR_INVALID_ARGUMENT, "%s: softmax_scale must be finite and positive", fn);
+  const int keep = rola_keep_blocks(rola::num_blocks(s.N, block), sparsity);
+  const size_t need = rola::sparse_backward_workspace_bytes(s, block, keep);
+  if (ws_bytes < need)
+    return fail(ROLA_ERR_WORKSPACE, "%s: workspace %zu bytes, need %zu", fn, ws_bytes, need);
+  return hip_status(rola::launch_sparse_backward(s, Qr, Kr, V, block, keep, blk_idx, softmax_scale,
+                                                 Os, lse, dOs, acc ? *acc : rola::GradTables{}, dQ, dK,
+                                                 dV, ws, stream),
+                    fn);
+}
+
 rola_status rola_sparse_attn_backward(const rola_problem* p, const void* Qr, const void* Kr,
                                       const void* V, int32_t block, double sparsity,
                                       const int32_t* blk_idx, float softmax_scale, const void* Os,
                                       const float* lse, const void* dOs, float* dQr, float* dKr,
                                       float* dV, void* ws, size_t ws_bytes, hipStream_t stream) {
-  rola::Shape s;
-  TRY(check_problem(p, __func__, &s));
-  TRY(check_block(s, block, __func__));
-  TRY(check_sparsity(sparsity, __func__));
-  if (!s.bf16) return fail(ROLA_ERR_UNSUPPORTED, "%s: built for the bf16 path", __func__);
-  if (rola::num_blocks(s.N, block) > rola::kBwdMaxBlocks)
-    return fail(ROLA_ERR_UNSUPPORTED, "%s: %d blocks per head, at most %d", __func__,
-                rola::num_blocks(s.N, block), rola::kBwdMaxBlocks);
-  REQUIRE_PTR(Qr);
-  REQUIRE_PTR(Kr);
-  REQUIRE_PTR(V);
-  REQUIRE_PTR(blk_idx);
-  REQUIRE_PTR(Os);
-  REQUIRE_PTR(lse);
-  REQUIRE_PTR(dOs);
-  REQUIRE_PTR(dQr);
-  REQUIRE_PTR(dKr);
-  REQUIRE_PTR(dV);
-  REQUIRE_PTR(ws);
-  if (!(softmax_scale > 0.f) || !isfinite(softmax_scale))
-    return fail(ROLA_ERR_INVALID_ARGUMENT, "%s: softmax_scale must be finite and positive", __func__);
-  const int keep = rola_keep_blocks(rola::num_blocks(s.N, block), sparsity);
-  const size_t need = rola::sparse_backward_workspace_bytes(s, block, keep);
-  if (ws_bytes < need)
-    return fail(ROLA_ERR_WORKSPACE, "%s: workspace %zu bytes, need %zu", __func__, ws_bytes, need);
-  if (reinterpret_cast<uintptr_t>(ws) % 16)
-    return fail(ROLA_ERR_INVALID_ARGUMENT, "%s: ws must be 16-byte aligned", __func__);
-  return hip_status(rola::launch_sparse_backward(s, Qr, Kr, V, block, keep, blk_idx, softmax_scale,
-                                                 Os, lse, dOs, dQr, dKr, dV, ws, stream),
-                    __func__);
+  return sparse_backward(p, Qr, Kr, V, block, sparsity, blk_idx, softmax_scale, Os, lse, dOs, nullptr,
+                         dQr, dKr, dV, ws, ws_bytes, stream, __func__);
+}
+
+rola_status rola_sparse_attn_backward_accumulate(
+    const rola_problem* p, const void* Qr, const void* Kr, const void* V, int32_t block,
+    double sparsity, const int32_t* blk_idx, float softmax_scale, const void* Os, const float* lse,
+    const void* dOs, const float* cos_tab, const float* sin_tab, int32_t rope_ld, float* dQn,
+    float* dKn, float* dV, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const rola::GradTables acc{cos_tab, sin_tab, rope_ld};
+  return sparse_backward(p, Qr, Kr, V, block, sparsity, blk_idx, softmax_scale, Os, lse, dOs, &acc, dQn,
+                         dKn, dV, ws, ws_bytes, stream, __func__);
 }
 
 size_t rola_sparse_combine_workspace_bytes(const rola_problem* p, int32_t block, double sparsity,

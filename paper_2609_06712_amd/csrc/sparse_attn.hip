@@ -917,14 +917,12 @@ __global__ __launch_bounds__(G * BLK * 2, G * BLK == 128 && !DQ ? 3 : 2) void sp
     if constexpr (DQ) {  // dQ^T: lane = query, rows = channels 32w + 8j + 4(l/32) + i
       if (qvalid) {
         float* dq = ap->dQ + head * (long)N * D + (uint32_t)q * (uint32_t)D;
-        const float sc = ap->scale;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            *reinterpret_cast<float4*>(dq + 32 * w + 8 * jj + 4 * hh) =
-                make_float4(acc[w][4 * jj] * sc, acc[w][4 * jj + 1] * sc, acc[w][4 * jj + 2] * sc,
-                            acc[w][4 * jj + 3] * sc);
+        if (fz.cos_tab) {  // dQ^n += R(p)^T dQ^r
+          const uint32_t off = (uint32_t)q * (uint32_t)fz.ld;
+          store_grad_row<true>(dq, acc, ap->scale, hh, fz.cos_tab + off, fz.sin_tab + off);
+        } else {
+          store_grad_row<false>(dq, acc, ap->scale, hh, nullptr, nullptr);
+        }
       }
       return;
     }
@@ -1198,24 +1196,28 @@ bool fuse_supported(const Shape& s, int r) { return s.bf16 && s.d == 128 && r >=
 
 hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, const void* V, int block,
                             int keep, const int32_t* idx, float scale, const void* dO,
-                            const void* lseD, float* dQ, void* ws, hipStream_t st) {
+                            const void* lseD, const GradTables& acc, float* dQ, void* ws,
+                            hipStream_t st) {
   const DqArgs dq{(const bf16*)dO, (const float2*)lseD, dQ};
-  const FuseArgs none{};
+  FuseArgs fz{};  // no epilogue of the forward; the tables of the accumulating form
+  fz.cos_tab = acc.cos_tab;
+  fz.sin_tab = acc.sin_tab;
+  fz.ld = acc.ld;
   if (block == 128) {
     if (keep <= kTable)
       return launch_bf16_tab<128, 1, 3, kTable, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
-                                                         nullptr, none, nullptr, st, dq);
+                                                         nullptr, fz, nullptr, st, dq);
     return launch_bf16_tab<128, 1, 3, 0, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
-                                                  nullptr, none, nullptr, st, dq);
+                                                  nullptr, fz, nullptr, st, dq);
   }
   Groups gr;
   const hipError_t e = prepare_groups<true>(s, keep, idx, ws, 0, st, gr);
   if (e != hipSuccess) return e;
   if (gr.stride - 1 <= kTable)
     return launch_bf16_tab<64, 2, 3, kTable, 0, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs,
-                                                      scale, nullptr, none, gr.queue, st, dq);
+                                                      scale, nullptr, fz, gr.queue, st, dq);
   return launch_bf16_tab<64, 2, 3, 0, 0, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs, scale,
-                                               nullptr, none, gr.queue, st, dq);
+                                               nullptr, fz, gr.queue, st, dq);
 }
 
 bool plan_used(const Shape& s, int block) { return s.bf16 && block == 64 && kB64Group > 1; }

@@ -179,7 +179,7 @@ void sparse_dkv_kernel(
     int N, int nb, int heads, const int32_t* __restrict__ rev, float scale_log2, float scale,
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const bf16* __restrict__ dO, const float2* __restrict__ lseD, const int32_t* __restrict__ order,
-    float* __restrict__ dK, float* __restrict__ dV) {
+    GradTables acc_tab, float* __restrict__ dK, float* __restrict__ dV) {
   constexpr int D = 128, NKW = BLK / 32, NW = 2 * NKW;
   constexpr int TILE = kBSub * D * 2;          // 32 rows of 256 bytes
   constexpr int STAGE = 2 * TILE + 1024;       // Q, dO, then lse/D of the 32 queries (256 B used)
@@ -343,14 +343,13 @@ void sparse_dkv_kernel(
   if (kvalid) {  // dV^T (role 0), dK^T (role 1): lane = key, rows = channels 32w + 8j + 4(l/32) + i
     float* out = (role ? dK : dV) + hoff + (long)key * D;
     const float f = role ? scale : 1.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = 32 * w + 8 * j + 4 * hh;
-        *reinterpret_cast<float4*>(out + c) = make_float4(acc[w][4 * j] * f, acc[w][4 * j + 1] * f,
-                                                          acc[w][4 * j + 2] * f, acc[w][4 * j + 3] * f);
-      }
+    if (acc_tab.cos_tab) {  // dK^n += R(p)^T dK^r, dV += dV
+      const uint32_t off = (uint32_t)key * (uint32_t)acc_tab.ld;
+      store_grad_row<true>(out, acc, f, hh, role ? acc_tab.cos_tab + off : nullptr,
+                           role ? acc_tab.sin_tab + off : nullptr);
+    } else {
+      store_grad_row<false>(out, acc, f, hh, nullptr, nullptr);
+    }
   }
 }
 
@@ -371,7 +370,8 @@ BwdWs bwd_layout(const Shape& s, int block, int keep) {
 template <int BLK>
 hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void* V, int keep,
                       const int32_t* idx, float scale, const void* Os, const float* lse,
-                      const void* dOs, float* dQ, float* dK, float* dV, void* ws, hipStream_t st) {
+                      const void* dOs, const GradTables& acc, float* dQ, float* dK, float* dV, void* ws,
+                      hipStream_t st) {
   const int nb = num_blocks(s.N, BLK), words = (nb + 31) / 32;
   const long heads = (long)s.B * s.H, rows = heads * s.N;
   const BwdWs lay = bwd_layout(s, BLK, keep);
@@ -392,14 +392,14 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
                      nb * sizeof(int32_t), st, nb, ochunks, (const int32_t*)rev, order);
   const float sl = scale * 1.4426950408889634f;
   // dQ on the attention kernel (block 64: paired, queued)
-  const hipError_t e2 = launch_sparse_dq(s, Qr, Kr, V, BLK, keep, idx, scale, dOs, lseD, dQ,
+  const hipError_t e2 = launch_sparse_dq(s, Qr, Kr, V, BLK, keep, idx, scale, dOs, lseD, acc, dQ,
                                          (char*)ws + lay.lsed + lay.bits + lay.rev + lay.order, st);
   if (e2 != hipSuccess) return e2;
   hipLaunchKernelGGL((sparse_dkv_kernel<BLK, kDkvNbuf>), dim3(dkv_grid((int)heads, nb)), dim3(BLK * 4), 0,
                      st, s.N, nb, (int)heads,
                      (const int32_t*)rev, sl, scale, (const bf16*)Qr, (const bf16*)Kr,
                      (const bf16*)V, (const bf16*)dOs, (const float2*)lseD, (const int32_t*)order,
-                     dK, dV);
+                     acc, dK, dV);
   return hipGetLastError();
 }
 
@@ -415,11 +415,12 @@ size_t sparse_backward_workspace_bytes(const Shape& s, int block, int keep) {
 
 hipError_t launch_sparse_backward(const Shape& s, const void* Qr, const void* Kr, const void* V,
                                   int block, int keep, const int32_t* idx, float scale,
-                                  const void* Os, const float* lse, const void* dOs, float* dQ,
-                                  float* dK, float* dV, void* ws, hipStream_t st) {
+                                  const void* Os, const float* lse, const void* dOs,
+                                  const GradTables& acc, float* dQ, float* dK, float* dV, void* ws,
+                                  hipStream_t st) {
   if (block == 64)
-    return launch_bwd<64>(s, Qr, Kr, V, keep, idx, scale, Os, lse, dOs, dQ, dK, dV, ws, st);
-  return launch_bwd<128>(s, Qr, Kr, V, keep, idx, scale, Os, lse, dOs, dQ, dK, dV, ws, st);
+    return launch_bwd<64>(s, Qr, Kr, V, keep, idx, scale, Os, lse, dOs, acc, dQ, dK, dV, ws, st);
+  return launch_bwd<128>(s, Qr, Kr, V, keep, idx, scale, Os, lse, dOs, acc, dQ, dK, dV, ws, st);
 }
 
 }  // namespace rola

@@ -69,6 +69,8 @@ SIGNATURES = {
     "rola_sparse_backward_workspace_bytes": (_sz, [_PP, _i32, _f64]),
     "rola_sparse_attn_backward": (_i32, [_PP, _p, _p, _p, _i32, _f64, _p, _f32, _p, _p, _p, _p, _p,
                                          _p, _p, _sz, _p]),
+    "rola_sparse_attn_backward_accumulate": (_i32, [_PP, _p, _p, _p, _i32, _f64, _p, _f32, _p, _p, _p,
+                                                    _p, _p, _i32, _p, _p, _p, _p, _sz, _p]),
     "rola_sparse_attn_combine": (_i32, [_PP, _p, _p, _p, _i32, _f64, _p, _f32, _p, _p, _i32, _p, _p,
                                         _i32, _p, _f32, _p, _f32, _p, _p, _p, _sz, _p]),
     "rola_sparse_plan": (_i32, [_PP, _i32, _f64, _p, _i32, _p, _sz, _p]),
@@ -730,6 +732,33 @@ def rola_sparse_attn_backward(Qr, Kr, V, grid, block, sparsity, blk_idx, Os, lse
                                          _ptr(dOs), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(ws),
                                          ws.numel(), _stream(stream)), "rola_sparse_attn_backward")
     return dQ, dK, dV
+
+
+def rola_sparse_attn_backward_accumulate(Qr, Kr, V, grid, block, sparsity, blk_idx, Os, lse, dOs, cos,
+                                         sin, dQn, dKn, dV, scale=None, ws=None, stream=None):
+    """dQn += R(p)^T dQ^r, dKn += R(p)^T dK^r and dV += dV of rola_sparse_attn_backward, in place on
+    fp32 [B, H, N, d_h] tensors; returns (dQn, dKn, dV)."""
+    a = _Args()
+    a.act(Qr, "Qr")
+    for t, name in ((Kr, "Kr"), (V, "V"), (Os, "Os"), (dOs, "dOs")):
+        a.act(t, name, Qr)
+    a.blk_idx(blk_idx, Qr, block, sparsity)
+    a.tensor(lse, "lse", Qr.shape[:3], torch.float32)
+    ld = a.tables(cos, sin, Qr, Qr.shape[3] // 2)
+    for t, name in ((dQn, "dQn"), (dKn, "dKn"), (dV, "dV")):
+        a.tensor(t, name, Qr.shape, torch.float32)
+    prob = problem_of(Qr, grid)
+    scale = prob.d_h ** -0.5 if scale is None else scale
+    if ws is None:
+        need = LIB.rola_sparse_backward_workspace_bytes(ctypes.byref(prob), block, sparsity)
+        ws = torch.empty(max(need, 16), dtype=torch.uint8, device=Qr.device)
+    a.workspace(ws)
+    a.done()
+    _check(LIB.rola_sparse_attn_backward_accumulate(
+        ctypes.byref(prob), _ptr(Qr), _ptr(Kr), _ptr(V), block, sparsity, _ptr(blk_idx), scale,
+        _ptr(Os), _ptr(lse), _ptr(dOs), _ptr(cos), _ptr(sin), ld, _ptr(dQn), _ptr(dKn), _ptr(dV),
+        _ptr(ws), ws.numel(), _stream(stream)), "rola_sparse_attn_backward_accumulate")
+    return dQn, dKn, dV
 
 
 def rola_lowrank_backward(Qn, Kn, V, Pq, Pk, r, cos, sin, C, Os, logits, dO, grid, eps_lr=1e-6,

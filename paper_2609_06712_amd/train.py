@@ -36,10 +36,8 @@ def backward(Qn, Kn, V, Pq, Pk, logits, saved, dO):
     cos, sin = saved["cos"], saved["sin"]
     dOs, dQn, dKn, dV, dPq, dPk, dlog = R.rola_lowrank_backward(
         Qn, Kn, V, Pq, Pk, r, cos, sin, saved["C"], saved["os"], logits, dO, g)
-    dQr, dKr, dVs = R.rola_sparse_attn_backward(saved["qr"], saved["kr"], V, g, saved["block"],
-                                                saved["sparsity"], saved["idx"], saved["os"],
-                                                saved["lse"], dOs)
-    R.rola_rope_backward_accumulate(dQr, cos, sin, g, dQn)           # dQ^n += R(p)^T dQ^r
-    R.rola_rope_backward_accumulate(dKr, cos, sin, g, dKn)           # dK^n += R(p)^T dK^r
-    R.rola_rope_backward_accumulate(dVs, cos, sin, g, dV, rotate=False)
+    # dQ^n += R(p)^T dQ^r, dK^n += R(p)^T dK^r, dV += the sparse branch's share
+    R.rola_sparse_attn_backward_accumulate(saved["qr"], saved["kr"], V, g, saved["block"],
+                                           saved["sparsity"], saved["idx"], saved["os"], saved["lse"],
+                                           dOs, cos, sin, dQn, dKn, dV)
     return dict(dQn=dQn, dKn=dKn, dV=dV, dPq=dPq, dPk=dPk, dlogits=dlog)

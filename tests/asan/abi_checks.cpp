@@ -71,6 +71,9 @@ int main(void) {
   EXPECT(ROLA_ERR_UNSUPPORTED, rola_dense_attn(&ok, F(1), F(2), F(3), 96, 0.1f, F(4), 0));
   EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_dense_attn(&ok, F(1), F(2), F(3), 64, 0.1f, F(1), 0));
   EXPECT(ROLA_ERR_WORKSPACE, rola_sparse_attn_backward(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(8), (float*)F(9), (float*)F(10), F(11), 16, 0));
+  EXPECT(ROLA_ERR_WORKSPACE, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(12), (float*)F(13), 64, (float*)F(8), (float*)F(9), (float*)F(10), F(11), 16, 0));
+  EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(12), (float*)F(13), 60, (float*)F(8), (float*)F(9), (float*)F(10), F(11), (size_t)1 << 40, 0));
+  EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), nullptr, (float*)F(13), 64, (float*)F(8), (float*)F(9), (float*)F(10), F(11), (size_t)1 << 40, 0));
 
   // attention + readout + combine
   EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_combine(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), F(6), 31, T, T, 64, (float*)F(7), 1e-6f, (float*)F(8), 1e-6f, NULL, F(9), F(10), BIG, 0));

@@ -317,6 +317,36 @@ def test_module_backward(grid, s):
     assert _rel(_f64(gr["dlogits"][0]), tot["dlogits"]) <= 2e-2
 
 
+@pytest.mark.parametrize("grid,block", [((3, 10, 13), 64), ((3, 10, 13), 128), ((4, 8, 16), 64)])
+def test_sparse_backward_accumulate(grid, block):
+    """The accumulating sparse backward against the plain one followed by the rotation's backward: the
+    same products added to the same values, up to the fusing of three multiply-adds per element."""
+    w = synth.WAN_1_3B_480P.replace(grid=grid, H=3, B=2, block=block, sparsity=0.5)
+    d = {k: v.cuda() for k, v in synth.make_inputs(w, 22).items()}
+    g = w.grid
+    prob = R.problem(w.B, w.H, w.N, w.d_h, g, w.dtype)
+    cos, sin = R.rola_rope_tables(prob, w.split)
+    qr = R.rola_rope_apply(d["Qn"], cos, sin, g)
+    kr = R.rola_rope_apply(d["Kn"], cos, sin, g)
+    idx = R.rola_block_select(qr, kr, g, block, w.sparsity)
+    os_, lse = R.rola_sparse_attn_lse(qr, kr, d["V"], g, block, w.sparsity, idx)
+    gen = torch.Generator().manual_seed(5)
+    dos = torch.randn(qr.shape, generator=gen).to(torch.bfloat16).cuda()
+    base = [torch.randn(qr.shape, generator=gen).cuda() for _ in range(3)]
+    args = (qr, kr, d["V"], g, block, w.sparsity, idx, os_, lse, dos)
+    grads = R.rola_sparse_attn_backward(*args)
+    want = [t.clone() for t in base]
+    for i, (dy, dx) in enumerate(zip(grads, want)):
+        R.rola_rope_backward_accumulate(dy, cos, sin, g, dx, rotate=i < 2)
+    got = R.rola_sparse_attn_backward_accumulate(*args, cos, sin, *base)
+    torch.cuda.synchronize()
+    for i, (x, y, dy, b) in enumerate(zip(got, want, grads, base)):
+        assert x is b
+        # each term is rounded at most twice more in one form than in the other
+        bound = 2.0 ** -22 * (y.abs() + dy.abs().unflatten(-1, (-1, 2)).sum(-1).repeat_interleave(2, -1))
+        assert bool(((x - y).abs() <= bound).all()), i
+
+
 def test_rope_backward_accumulate():
     """dX += R(p)^T dY (the gradient through the main-path rotation) and dX += dY, against the
     oracle's rotation by the negated angle (R(p)^T = R(-p)) in fp64, on a ragged 3x10x13 grid."""
