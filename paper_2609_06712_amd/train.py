@@ -18,9 +18,10 @@ from . import rola as R
 def forward(Qn, Kn, V, Pq, Pk, logits, grid, split, block=64, sparsity=0.9, r=32, base=10000.0):
     prob = R.problem_of(Qn, grid)
     cos, sin = R.rola_rope_tables(prob, split, base)
-    qr = R.rola_rope_apply(Qn, cos, sin, grid)
-    kr = R.rola_rope_apply(Kn, cos, sin, grid)
-    idx = R.rola_block_select(qr, kr, grid, block, sparsity)
+    # the rotation fused with the selection's pooling: bitwise rola_rope_apply and rola_block_select
+    qr, qbar = R.rola_rope_pool(Qn, cos, sin, grid, block)
+    kr, kbar = R.rola_rope_pool(Kn, cos, sin, grid, block)
+    idx = R.rola_block_select_pooled(qbar, kbar, kr, grid, block, sparsity)
     os_, lse = R.rola_sparse_attn_lse(qr, kr, V, grid, block, sparsity, idx)
     C, _ = R.rola_lowrank_summary(Kn, V, Pk, r, cos, sin, grid, want_z=False)
     out = R.rola_lowrank_readout_combine(Qn, Pq, r, cos, sin, C, os_, logits, grid)
