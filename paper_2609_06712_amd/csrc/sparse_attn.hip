@@ -58,28 +58,32 @@ __device__ __forceinline__ int v_swizzle(int row) { return 2 * ((0x6530 >> (4 * 
 // and where each group's walk starts (walk_start); each query block sums its own selections only,
 // bitwise as the one-block path does when given them in the same order.
 constexpr int kPairWindow = 64;  // candidate partners of a query block: the next 64 blocks
-constexpr int kPairRows = 128;   // bitmap rows one overlap workgroup holds (64 blocks + window)
+constexpr int kPairRows = 128;   // bitmap rows an overlap workgroup holds at most (64 blocks + window)
 
 // Row stride (words) of the membership bitmaps in LDS: odd, so a wave reading one word of 64
 // consecutive rows hits 64 distinct banks.
 __host__ __device__ inline int pair_row_stride(int nb) { return ((nb + 31) >> 5) | 1; }
 
-// Candidate preference of every query block, one workgroup per (head, chunk of 64 query blocks).
-// The membership bitmaps of the chunk's blocks and of the 64 after them are built in LDS from the
-// lists (out-of-range entries dropped); lane d of a wave then intersects row I with row I+1+d and
-// ranks the 64 candidates by overlap, larger first, the nearer first on equal overlap, candidates
-// past the last block after all others. pref[head][chunk][k][r] = offset d of the k-th choice of
-// query block chunk*64 + r: k-major, so that the greedy pass reads its column per lane.
-__global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nchunks,
+// Candidate preference of every query block, one workgroup per (head, part of a chunk of 64 query
+// blocks: `per` of them, 16 or 64). The membership bitmaps of the part's blocks and of the 64 after
+// them are built in LDS from the lists (out-of-range entries dropped); lane d of a wave then intersects
+// row I with row I+1+d and ranks the 64 candidates by overlap, larger first, the nearer first on equal
+// overlap, candidates past the last block after all others. pref[head][chunk][k][r] = offset d of the
+// k-th choice of query block chunk*64 + r: k-major, so that the greedy pass reads its column per lane.
+__global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nchunks, int per,
                                                         const int32_t* __restrict__ idx,
                                                         uint8_t* __restrict__ pref) {
-  extern __shared__ uint32_t bits[];  // [kPairRows][rs]
+  extern __shared__ uint32_t bits[];  // [per + kPairWindow][rs]
   const int words = (nb + 31) >> 5, rs = pair_row_stride(nb);
-  const long head = blockIdx.x / nchunks;
-  const int chunk = (int)(blockIdx.x % nchunks), I0 = chunk * kPairWindow;
-  const int rows = min(kPairRows, nb - I0);
+  const int parts = kPairWindow / per;
+  const long part = blockIdx.x;  // (head, chunk, part of the chunk)
+  const long head = part / (nchunks * parts);
+  const int chunk = (int)(part / parts % nchunks), r0 = (int)(part % parts) * per;
+  const int I0 = chunk * kPairWindow + r0;
+  if (I0 >= nb) return;
+  const int cap = per + kPairWindow, rows = min(cap, nb - I0);
   const int tid = threadIdx.x;
-  for (int w = tid; w < kPairRows * rs; w += 256) bits[w] = 0u;
+  for (int w = tid; w < cap * rs; w += 256) bits[w] = 0u;
   __syncthreads();
   const int32_t* sel = idx + (head * nb + I0) * (long)keep;  // rows I0 .. I0+rows-1, contiguous
   for (int e = tid; e < rows * keep; e += 256) {
@@ -88,8 +92,8 @@ __global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nc
   }
   __syncthreads();
   const int d = tid % 64;
-  uint8_t* out = pref + (head * nchunks + chunk) * (long)(kPairWindow * kPairWindow);
-  for (int i = tid / 64; i < kPairWindow && I0 + i < nb; i += 4) {  // wave-uniform bounds
+  uint8_t* out = pref + (head * nchunks + chunk) * (long)(kPairWindow * kPairWindow) + r0;
+  for (int i = tid / 64; i < per && I0 + i < nb; i += 4) {  // wave-uniform bounds
     int key = 63 - d - 64;  // past the last block: below every valid candidate
     if (I0 + i + 1 + d < nb) {  // then row i+1+d < rows
       const uint32_t* a = bits + i * rs;
@@ -104,6 +108,10 @@ __global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nc
     out[rank * kPairWindow + i] = (uint8_t)d;
   }
 }
+// Query blocks per overlap workgroup: a quarter chunk where whole chunks are fewer than two workgroups
+// per CU (it builds 80 bitmap rows for 16 blocks instead of 128 for 64; 12 heads of 512 blocks 26 -> 12
+// us, 24 of 132 17 -> 9; with 40 heads of 1182 whole chunks fill the chip).
+inline int pair_rank_rows(int heads, int nchunks) { return heads * nchunks < 2 * kCus ? 16 : 64; }
 
 // Greedy pairing, one wave per head: query blocks are visited in ascending order; a block not yet
 // taken is paired with the untaken block among its next 64 that it ranks first, or stays alone
@@ -111,9 +119,12 @@ __global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nc
 // is always free when I is visited: every block but possibly the last gets a partner, which makes
 // exactly ceil(nb / 2) groups. pairs[head][g] = I | J << 16 (J = nb: no partner), in the order the
 // groups are formed. Lane k holds the k-th choices of a chunk's 64 blocks (64 bytes in registers,
-// the next chunk loading meanwhile); a step is a ballot over the lanes whose choice is still free
-// and a find-first-set. The table is gathered in LDS and written out at the end, so no store
-// shares the memory counter with the chunk loads.
+// the next chunk loading meanwhile); a step is a mask of the lanes whose choice is still free and a
+// find-first-set. Bound by that chain of scalar work, so a chunk whose candidates all exist (every one
+// but the last two) takes steps with nothing else on it: one branch (is the block taken?), the lane's
+// candidate bit prepared off the chain, and the comparison's mask used as it comes. 512 blocks: 43 us
+// with bounds checks and a rebuilt mask in every step, 20 now. The table is gathered in LDS and written
+// out at the end, so no store shares the memory counter with the chunk loads.
 constexpr int kMaxPairGroups = 2032;  // ceil(4064 / 2): the most query blocks pairing serves
 __global__ __launch_bounds__(64) void pair_greedy_kernel(int nb, int ngroups, int nchunks,
                                                          const uint8_t* __restrict__ pref,
@@ -136,24 +147,45 @@ __global__ __launch_bounds__(64) void pair_greedy_kernel(int nb, int ngroups, in
     const uint32_t w[16] = {cur[0].x, cur[0].y, cur[0].z, cur[0].w, cur[1].x, cur[1].y,
                             cur[1].z, cur[1].w, cur[2].x, cur[2].y, cur[2].z, cur[2].w,
                             cur[3].x, cur[3].y, cur[3].z, cur[3].w};
+    const int I0 = c * kPairWindow;
+    // lane's choice for row r, and the bit of `taken` it stands on (d = 63: none, block I+64 is free)
+    auto choice = [&](int r) { return (w[r / 4] >> (8 * (r % 4))) & 0xFFu; };
+    auto free_lanes = [&](uint32_t d, uint64_t t) {
+      return __builtin_amdgcn_uicmpl((2ull << d) & t, 0ull, 32 /* == */);
+    };
+    if (I0 + 2 * kPairWindow <= nb) {
 #pragma unroll
-    for (int r = 0; r < kPairWindow; ++r) {
-      const int I = c * kPairWindow + r;
-      if (I < nb) {
-        if (taken & 1) {
-          taken >>= 1;
-        } else {
-          const int d = (w[r / 4] >> (8 * (r % 4))) & 0xFF;  // this lane's choice
-          const bool free_d = I + 1 + d < nb && !(((taken >> d) >> 1) & 1);
-          const uint64_t m = __ballot(free_d);
-          taken >>= 1;
+      for (int r = 0; r < kPairWindow; ++r) {
+        const uint64_t t = taken;
+        taken >>= 1;
+        if (!(t & 1)) {  // (one-sided: an else branch costs the step a second jump)
+          const uint32_t d = choice(r);
+          const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(free_lanes(d, t)));
+          taken |= 1ull << dd;
+          tbl[g++] = (I0 + r) | ((I0 + r + 1 + dd) << 16);  // every lane stores the same value
+        }
+      }
+    } else {
+#pragma unroll 1
+      for (int r = 0; r < kPairWindow && I0 + r < nb; ++r) {
+        const int I = I0 + r;
+        const uint64_t t = taken;
+        taken >>= 1;
+        if (!(t & 1)) {
+          uint32_t d = 0;  // choice(r), r not a constant here
+#pragma unroll
+          for (int q = 0; q < 16; ++q) d = r / 4 == q ? w[q] : d;
+          d = (d >> (8 * (r % 4))) & 0xFFu;
+          // candidates past the last block are ranked after all others: the first nb - 1 - I lanes
+          const int valid = min(64, nb - 1 - I);
+          const uint64_t m = valid > 0 ? free_lanes(d, t) & (~0ull >> (64 - valid)) : 0ull;
           int partner = nb;
           if (m) {
-            const int dd = __builtin_amdgcn_readlane(d, (int)__builtin_ctzll(m));
+            const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(m));
             partner = I + 1 + dd;
             taken |= 1ull << dd;
           }
-          if (g < ngroups) tbl[g] = I | (partner << 16);  // every lane stores the same value
+          if (g < ngroups) tbl[g] = I | (partner << 16);
           ++g;
         }
       }
@@ -1158,9 +1190,10 @@ hipError_t prepare_groups(const Shape& s, int keep, const int32_t* idx, void* ws
   gr = groups_in(s, keep, ws);
   if (gr.pairs) {
     const int nchunks = (nb + kPairWindow - 1) / kPairWindow;
-    hipLaunchKernelGGL(pair_rank_kernel, dim3(nchunks * heads), dim3(256),
-                       kPairRows * pair_row_stride(nb) * sizeof(uint32_t), st, nb, keep, nchunks,
-                       idx, (uint8_t*)gr.lists);
+    const int per = pair_rank_rows(heads, nchunks);
+    hipLaunchKernelGGL(pair_rank_kernel, dim3(nchunks * heads * (kPairWindow / per)), dim3(256),
+                       (per + kPairWindow) * pair_row_stride(nb) * sizeof(uint32_t), st, nb, keep,
+                       nchunks, per, idx, (uint8_t*)gr.lists);
     hipLaunchKernelGGL(pair_greedy_kernel, dim3(heads), dim3(64), 0, st, nb, ngroups, nchunks,
                        (const uint8_t*)gr.lists, gr.pairs);
   }

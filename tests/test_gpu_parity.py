@@ -377,6 +377,29 @@ def test_overlap_pairing(lists_kind, s):
     assert torch.equal(shared, single)
 
 
+@pytest.mark.parametrize("N,H,s", [(20450, 2, 0.9), (8191, 3, 0.95), (64 * 128, 1, 0.5), (8256, 171, 0.9),
+                                   (190, 2, 0.5)])
+def test_overlap_pairing_sizes(N, H, s):
+    """The pair table of the plan against the greedy matching, on random lists: several chunks of 64
+    query blocks of which all candidates exist (320 blocks), chunk ends on and off the last block (128,
+    130), and both splits of the overlap pass (171 heads of three chunks take whole chunks)."""
+    grid = (1, 1, N)
+    like = torch.empty((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
+    prob = R.problem_of(like, grid)
+    nb = O.num_blocks(N, 64)
+    keep = O.keep_blocks(nb, s)
+    rng = np.random.default_rng(N)
+    lists = np.stack([np.stack([np.sort(rng.permutation(nb)[:keep]) for _ in range(nb)]) for _ in range(H)])
+    idx = torch.from_numpy(lists[None].astype(np.int32)).cuda()
+    ws = torch.empty(R.sparse_combine_workspace_bytes(prob, 64, s, 32), dtype=torch.uint8, device="cuda")
+    R.rola_sparse_plan(idx, like, grid, 64, s, 32, ws)
+    torch.cuda.synchronize()
+    ng = (nb + 1) // 2
+    table = ws[8 * 256: 8 * 256 + H * ng * 4].view(torch.int32).cpu().numpy().reshape(H, ng)
+    for h in range(0, H, max(1, H // 3)):
+        assert np.array_equal(table[h].astype(np.int64), _greedy_pairs(lists[h], nb)), h
+
+
 def test_work_queue_full_size():
     """At the 14B 720p size the attention kernel runs as resident workgroups that claim (head,
     pair) groups from per-XCD counters: 23640 groups, far more than the chip holds at once, so
