@@ -23,7 +23,9 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Block means of Q^r or K^r, one workgroup per (b, h, block), 16 threads of 8 channels per token
-// row. Summation order: per thread over its tokens in order, then over the 16 threads in order.
+// row. Summation order: per thread over its tokens in order, then over the 16 threads in order. With X2
+// the second half of grid.x pools X2 into out2: both tensors of a selection in one launch (5 us of a
+// small call).
 // Sum of x over the G consecutive lanes that share one row (G = 8 or 16, lanes aligned to G).
 __device__ __forceinline__ float row_group_sum(float x, int G) {
   for (int off = G / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, G);
@@ -42,11 +44,15 @@ __device__ __forceinline__ void block_norm_max(float sq, float* out) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void pool_kernel(int N, int d, int block, const T* __restrict__ X,
-                                                   float* __restrict__ out, float* __restrict__ nmax) {
-  const int I = blockIdx.x, nb = gridDim.x;
+__global__ __launch_bounds__(256) void pool_kernel(int N, int d, int block, int nb,
+                                                   const T* __restrict__ X, float* __restrict__ out,
+                                                   float* __restrict__ nmax, const T* __restrict__ X2,
+                                                   float* __restrict__ out2) {
+  const bool second = (int)blockIdx.x >= nb;
+  const int I = blockIdx.x - (second ? nb : 0);
+  if (second) out = out2;
   const long head = (long)blockIdx.z * gridDim.y + blockIdx.y;
-  const T* xh = X + head * (long)N * d;
+  const T* xh = (second ? X2 : X) + head * (long)N * d;
   const int G = d / 8, L = 256 / G;
   const int g = threadIdx.x % G, lane = threadIdx.x / G;
   const int n0 = I * block, n1 = min(N, n0 + block);
@@ -521,15 +527,17 @@ void launch_topk(int nb, int keep, int B, int H, const float* S, int32_t* idx, h
   return launch_topk_reg<kTopkMaxSlots>(nb, keep, rows, S, idx, st);
 }
 
+// X2, means2: optionally a second tensor in the same launch (without nmax).
 hipError_t launch_pool(const Shape& s, const void* X, int block, float* means, hipStream_t st,
-                       float* nmax = nullptr) {
-  const dim3 grid(num_blocks(s.N, block), s.H, s.B);
+                       float* nmax = nullptr, const void* X2 = nullptr, float* means2 = nullptr) {
+  const int nb = num_blocks(s.N, block);
+  const dim3 grid(X2 ? 2 * nb : nb, s.H, s.B);
   if (s.bf16)
-    hipLaunchKernelGGL(pool_kernel<bf16>, grid, dim3(256), 0, st, s.N, s.d, block, (const bf16*)X,
-                       means, nmax);
+    hipLaunchKernelGGL(pool_kernel<bf16>, grid, dim3(256), 0, st, s.N, s.d, block, nb, (const bf16*)X,
+                       means, nmax, (const bf16*)X2, means2);
   else
-    hipLaunchKernelGGL(pool_kernel<float>, grid, dim3(256), 0, st, s.N, s.d, block, (const float*)X,
-                       means, nmax);
+    hipLaunchKernelGGL(pool_kernel<float>, grid, dim3(256), 0, st, s.N, s.d, block, nb,
+                       (const float*)X, means, nmax, (const float*)X2, means2);
   return hipGetLastError();
 }
 
@@ -601,8 +609,7 @@ hipError_t launch_block_select(const Shape& s, const void* Qr, const void* Kr, i
   float* qbar = (float*)w;
   float* kbar = (float*)(w + align_up(heads * nb * s.d * sizeof(float)));
   float* S = (float*)(w + 2 * align_up(heads * nb * s.d * sizeof(float)));
-  hipError_t e = launch_pool(s, Qr, block, qbar, st);
-  if (e == hipSuccess) e = launch_pool(s, Kr, block, kbar, st);
+  hipError_t e = launch_pool(s, Qr, block, qbar, st, nullptr, Kr, kbar);
   if (e == hipSuccess) e = launch_select_pooled(s, qbar, kbar, block, keep, idx, S, st);
   return e;
 }

@@ -231,18 +231,57 @@ __host__ __device__ inline int walk_start(int L, int total, int period, int E) {
   return (int)((long long)(i % period) * E / period);
 }
 
+// C^T fragments of the fused epilogue: entry (head, w, t, s, lane) = {hi, lo} of the 8 values
+// C[2J + s][32w + l%32], J = 16t + 8(m/4) + 4(l/32) + m%4 for m = 0..7 (zero for J >= r/2).
+struct CfragJob {
+  long total;      // entries
+  int r, RJ;
+  const float* C;  // [B, H, r, 128]
+  uint4* out;
+};
+__device__ __forceinline__ void cfrag_entry(const CfragJob& job, long e) {
+  if (e >= job.total) return;
+  const int lane = (int)(e % 64), RJ = job.RJ;
+  const int ts = (int)((e / 64) % (2 * RJ)), w = (int)((e / (64 * 2 * RJ)) % 4);
+  const long head = e / (64L * 2 * RJ * 4);
+  const int t = ts / 2, sd = ts % 2, half = job.r / 2;
+  const int c = 32 * w + lane % 32, h = lane / 32;
+  const float* Ch = job.C + head * (long)job.r * 128;
+  bf16x8 hi, lo;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int J = 16 * t + 8 * (m / 4) + 4 * h + m % 4;
+    const float v = J < half ? Ch[(long)(2 * J + sd) * 128 + c] : 0.f;
+    hi[m] = (bf16)v;
+    lo[m] = (bf16)(v - (float)hi[m]);
+  }
+  job.out[2 * e] = *reinterpret_cast<const uint4*>(&hi);
+  job.out[2 * e + 1] = *reinterpret_cast<const uint4*>(&lo);
+}
+__global__ __launch_bounds__(256) void cfrag_kernel(const CfragJob job) {
+  cfrag_entry(job, (long)blockIdx.x * 256 + threadIdx.x);
+}
+inline unsigned cfrag_blocks(const CfragJob& job) { return (unsigned)((job.total + 255) / 256); }
+
 // G query blocks share a workgroup of the attention kernel: G consecutive ones, or with G = 2 and
 // a pair table the two that pair_greedy_kernel matched. For each (b, h, group) this writes the
 // entry count and then the union of the G block lists in walk order (above), rotated to start at
 // walk_start, each entry J | (bit i: query block i of the group selected J) << 16. Built through
 // bitmaps indexed by walk position, so the lists may come in any order; out-of-range entries are
-// dropped, as the attention skips them.
+// dropped, as the attention skips them. Workgroups past the `total` groups make the C^T fragments (a
+// launch of their own costs 5 us, a twentieth of a small layer).
 template <int G>
-__global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int ngroups, int stride,
+__global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int ngroups, int total,
+                                                          int stride,
                                                           const int32_t* __restrict__ idx,
                                                           const int32_t* __restrict__ pairs,
                                                           int32_t* __restrict__ out,
-                                                          int* __restrict__ queue, int period) {
+                                                          int* __restrict__ queue, int period,
+                                                          const CfragJob job) {
+  if ((int)blockIdx.x >= total) {
+    cfrag_entry(job, (long)(blockIdx.x - total) * 256 + threadIdx.x);
+    return;
+  }
   extern __shared__ uint32_t sh[];
   const int kb = walk_bits(nb);
   const int words = walk_words(nb);
@@ -288,7 +327,7 @@ __global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int 
   int32_t* o = out + gp * (long)stride;
   const int E = scan[255];
   if (tid == 255) o[0] = E;
-  const int e0 = walk_start((int)gp, (int)gridDim.x, period, E);
+  const int e0 = walk_start((int)gp, total, period, E);
   int pos = scan[tid] - cnt - e0;  // rotated position of this thread's first entry
   if (pos < 0) pos += E;
   for (int w = w0; w < w1; ++w) {
@@ -302,6 +341,89 @@ __global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int 
       for (int b = 0; b < G; ++b) mask |= ((m[b] >> bit) & 1u) << b;
       o[1 + pos] = walk_pos(w * 32 + bit, kb) | (int)(mask << 16);  // the reversal is its own inverse
       if (++pos == E) pos = 0;
+    }
+  }
+}
+
+// The whole plan of a head of at most 64 blocks in one workgroup: pair_rank_kernel, pair_greedy_kernel and
+// group_union_kernel's results (the same pairs and lists), from one 64-bit word per query block, the
+// walk positions of its key blocks. Small calls are bound by launches and their latencies: 390 tokens x
+// 12 heads, three launches of 3-4 us each, 4 us in one. Workgroups past `heads` make the C^T fragments.
+constexpr int kSmallPlan = 64;
+__global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int ngroups, int heads,
+                                                         int stride, const int32_t* __restrict__ idx,
+                                                         int32_t* __restrict__ pairs,
+                                                         int32_t* __restrict__ out,
+                                                         int* __restrict__ queue, int period,
+                                                         const CfragJob job) {
+  if ((int)blockIdx.x >= heads) {
+    cfrag_entry(job, (long)(blockIdx.x - heads) * 256 + threadIdx.x);
+    return;
+  }
+  __shared__ uint32_t bits[kSmallPlan][2];                // walk positions of each query block's list
+  __shared__ uint8_t pref[kPairWindow * kPairWindow];     // [k][r]: k-th choice of query block r
+  __shared__ int32_t tbl[kSmallPlan / 2];
+  const int kb = walk_bits(nb);
+  const long head = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_uniform(tid / 64);
+  if (head == 0 && tid < kNumXcd) queue[tid * kQueueStride] = 0;
+  if (tid < 2 * kSmallPlan) bits[tid / 2][tid % 2] = 0u;
+  __syncthreads();
+  const int32_t* sel = idx + head * nb * (long)keep;
+  for (int e = tid; e < nb * keep; e += 256) {
+    const int J = sel[e];
+    if ((unsigned)J < (unsigned)nb) {
+      const int p = walk_pos(J, kb);
+      atomicOr(&bits[e / keep][p >> 5], 1u << (p & 31));
+    }
+  }
+  __syncthreads();
+  auto mask = [&](int i) { return (uint64_t)bits[i][1] << 32 | bits[i][0]; };
+  for (int i = wave; i < nb; i += 4) {  // rank the following blocks by overlap, the nearer first on ties
+    const int valid = nb - 1 - i;       // lane d < valid: candidate i + 1 + d
+    const int c = lane < valid ? __popcll(mask(i) & mask(i + 1 + lane)) : 0;
+    const int key = (c << 6) | (63 - lane);
+    int rank = 0;
+    for (int o = 0; o < valid; ++o) rank += __builtin_amdgcn_readlane(key, o) > key;
+    if (lane < valid) pref[rank * kPairWindow + i] = (uint8_t)lane;
+  }
+  __syncthreads();
+  if (wave == 0) {  // the greedy matching (pair_greedy_kernel's tail form)
+    uint64_t taken = 0;
+    int g = 0;
+    for (int r = 0; r < nb; ++r) {
+      const uint64_t t = taken;
+      taken >>= 1;
+      if (!(t & 1)) {
+        const int valid = nb - 1 - r;
+        const uint32_t d = lane < valid ? pref[lane * kPairWindow + r] : 0u;
+        const uint64_t m = valid > 0 ? __builtin_amdgcn_uicmpl((2ull << d) & t, 0ull, 32) &
+                                           (~0ull >> (64 - valid))
+                                     : 0ull;
+        int partner = nb;
+        if (m) {
+          const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(m));
+          partner = r + 1 + dd;
+          taken |= 1ull << dd;
+        }
+        if (g < ngroups) tbl[g] = r | (partner << 16);
+        ++g;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < ngroups) pairs[head * ngroups + tid] = tbl[tid];
+  for (int g = wave; g < ngroups; g += 4) {  // lane = walk position
+    const int I = tbl[g] & 0xFFFF, J = tbl[g] >> 16;
+    const uint64_t ma = mask(I), mb = J < nb ? mask(J) : 0ull, u = ma | mb;
+    const int E = __popcll(u), gp = (int)(head * ngroups) + g;
+    int32_t* o = out + gp * (long)stride;
+    if (lane == 0) o[0] = E;
+    if (u >> lane & 1) {
+      int pos = __popcll(u & ((1ull << lane) - 1)) - walk_start(gp, heads * ngroups, period, E);
+      if (pos < 0) pos += E;
+      const int members = (int)(ma >> lane & 1) | (int)(mb >> lane & 1) << 1;
+      o[1 + pos] = walk_pos(lane, kb) | members << 16;
     }
   }
 }
@@ -330,31 +452,6 @@ struct FuseArgs {
   float* lse_out;        // optional [B, H, N]: log2 of the softmax denominator of the scaled scores
   int rot_q;             // the attention's Q is Q^n, rotated in the prologue with these tables
 };
-
-// C^T fragments: entry (head, w, t, s, lane) = {hi, lo} of the 8 values C[2J + s][32w + l%32],
-// J = 16t + 8(m/4) + 4(l/32) + m%4 for m = 0..7 (zero for J >= r/2).
-__global__ __launch_bounds__(256) void cfrag_kernel(long total, int r, int RJ,
-                                                    const float* __restrict__ C,
-                                                    uint4* __restrict__ out) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= total) return;
-  const int lane = (int)(e % 64);
-  const int ts = (int)((e / 64) % (2 * RJ)), w = (int)((e / (64 * 2 * RJ)) % 4);
-  const long head = e / (64L * 2 * RJ * 4);
-  const int t = ts / 2, sd = ts % 2, half = r / 2;
-  const int c = 32 * w + lane % 32, h = lane / 32;
-  const float* Ch = C + head * (long)r * 128;
-  bf16x8 hi, lo;
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const int J = 16 * t + 8 * (m / 4) + 4 * h + m % 4;
-    const float v = J < half ? Ch[(long)(2 * J + sd) * 128 + c] : 0.f;
-    hi[m] = (bf16)v;
-    lo[m] = (bf16)(v - (float)hi[m]);
-  }
-  out[2 * e] = *reinterpret_cast<const uint4*>(&hi);
-  out[2 * e + 1] = *reinterpret_cast<const uint4*>(&lo);
-}
 
 // Two forms, by the registers that three workgroups per CU leave (168):
 //  * r <= 32 (RJ = 1): u of all four channel tiles at once, each load where it is used and guarded per
@@ -1181,13 +1278,21 @@ Groups groups_in(const Shape& s, int keep, void* ws) {
   return gr;
 }
 
+// cf: the C^T fragments to make beside them, or null.
 template <bool DQ>
 hipError_t prepare_groups(const Shape& s, int keep, const int32_t* idx, void* ws, int r,
-                          hipStream_t st, Groups& gr) {
+                          hipStream_t st, Groups& gr, const CfragJob* cf = nullptr) {
   constexpr int G = kB64Group;
   const int nb = num_blocks(s.N, 64);
   const int ngroups = (nb + G - 1) / G, heads = s.B * s.H;
   gr = groups_in(s, keep, ws);
+  const int period = walk_period<DQ ? 3 : kB64Nbuf, DQ>(gr.stride, r);
+  const CfragJob job = cf ? *cf : CfragJob{};
+  if (gr.pairs && nb <= kSmallPlan) {
+    hipLaunchKernelGGL(small_plan_kernel, dim3(heads + cfrag_blocks(job)), dim3(256), 0, st, nb, keep,
+                       ngroups, heads, gr.stride, idx, gr.pairs, gr.lists, gr.queue, period, job);
+    return hipGetLastError();
+  }
   if (gr.pairs) {
     const int nchunks = (nb + kPairWindow - 1) / kPairWindow;
     const int per = pair_rank_rows(heads, nchunks);
@@ -1197,10 +1302,10 @@ hipError_t prepare_groups(const Shape& s, int keep, const int32_t* idx, void* ws
     hipLaunchKernelGGL(pair_greedy_kernel, dim3(heads), dim3(64), 0, st, nb, ngroups, nchunks,
                        (const uint8_t*)gr.lists, gr.pairs);
   }
-  const int period = walk_period<DQ ? 3 : kB64Nbuf, DQ>(gr.stride, r);
-  hipLaunchKernelGGL(group_union_kernel<G>, dim3(ngroups * heads), dim3(256),
-                     (G * walk_words(nb) + 256) * sizeof(uint32_t), st, nb, keep, ngroups, gr.stride,
-                     idx, (const int32_t*)gr.pairs, gr.lists, gr.queue, period);
+  const int total = ngroups * heads;
+  hipLaunchKernelGGL(group_union_kernel<G>, dim3(total + cfrag_blocks(job)), dim3(256),
+                     (G * walk_words(nb) + 256) * sizeof(uint32_t), st, nb, keep, ngroups, total,
+                     gr.stride, idx, (const int32_t*)gr.pairs, gr.lists, gr.queue, period, job);
   return hipGetLastError();
 }
 
@@ -1290,13 +1395,18 @@ hipError_t launch_sparse_attn(const Shape& s, const void* Qr, const void* Kr, co
                               float* lse, bool planned) {
   FuseArgs fz{};
   fz.lse_out = lse;
-  if (lf) {  // fused epilogue: C^T fragments first (fuse_ws: fuse_workspace_bytes)
+  // C^T fragments of the fused epilogue (fuse_ws: fuse_workspace_bytes), made beside the groups where
+  // those are prepared here
+  CfragJob job{};
+  const bool grouped = s.bf16 && block == 64 && idx && ws && kB64Group > 1;
+  if (lf) {
     const int RJ = lf->r <= 32 ? 1 : 2;
-    const long total = (long)s.B * s.H * 4 * 2 * RJ * 64;
-    hipLaunchKernelGGL(cfrag_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, total,
-                       lf->r, RJ, lf->C, (uint4*)fuse_ws);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    job = CfragJob{(long)s.B * s.H * 4 * 2 * RJ * 64, lf->r, RJ, lf->C, (uint4*)fuse_ws};
+    if (!grouped || planned) {
+      hipLaunchKernelGGL(cfrag_kernel, dim3(cfrag_blocks(job)), dim3(256), 0, st, job);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
     fz = FuseArgs{(const bf16*)lf->Qn, (const bf16*)lf->Pq, lf->cos_tab, lf->sin_tab,
                   (const uint4*)fuse_ws, lf->logits, s.H, lf->r, lf->ld, lf->eps_lr, lf->eps, lse,
                   Qr == nullptr ? 1 : 0};
@@ -1308,10 +1418,11 @@ hipError_t launch_sparse_attn(const Shape& s, const void* Qr, const void* Kr, co
     if (block == 64) {
       constexpr int G = kB64Group;
       if (!idx) return launch_bf16<64, 2, 3>(s, Qr, Kr, V, nullptr, nb, 0, scale, Os, st, nullptr, fp);
-      if (ws && G > 1) {
+      if (grouped) {
         Groups gr = groups_in(s, keep, ws);
         if (!planned) {
-          const hipError_t e = prepare_groups<false>(s, keep, idx, ws, lf ? lf->r : 0, st, gr);
+          const hipError_t e = prepare_groups<false>(s, keep, idx, ws, lf ? lf->r : 0, st, gr,
+                                                     lf ? &job : nullptr);
           if (e != hipSuccess) return e;
         }
         return launch_bf16<64, G, kB64Nbuf>(s, Qr, Kr, V, gr.lists, 0, gr.stride, scale, Os, st,

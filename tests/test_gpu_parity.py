@@ -378,11 +378,13 @@ def test_overlap_pairing(lists_kind, s):
 
 
 @pytest.mark.parametrize("N,H,s", [(20450, 2, 0.9), (8191, 3, 0.95), (64 * 128, 1, 0.5), (8256, 171, 0.9),
-                                   (190, 2, 0.5)])
+                                   (190, 2, 0.5), (64, 2, 0.0), (4033, 5, 0.7), (4096, 2, 0.9),
+                                   (4097, 2, 0.9), (1000, 9, 0.0)])
 def test_overlap_pairing_sizes(N, H, s):
     """The pair table of the plan against the greedy matching, on random lists: several chunks of 64
     query blocks of which all candidates exist (320 blocks), chunk ends on and off the last block (128,
-    130), and both splits of the overlap pass (171 heads of three chunks take whole chunks)."""
+    130), both splits of the overlap pass (171 heads of three chunks take whole chunks), and the
+    one-workgroup plan of up to 64 blocks with its edges."""
     grid = (1, 1, N)
     like = torch.empty((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
     prob = R.problem_of(like, grid)
