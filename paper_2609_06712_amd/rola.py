@@ -8,6 +8,7 @@ library has not been built; there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -115,12 +116,15 @@ def _check(status: int, fn: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # the raw handle of the current stream: a torch.cuda.Stream object per call costs 3 us of a small
+    # call's 15
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def problem(B, H, N, d_h, grid, dtype) -> Problem:
@@ -134,6 +138,23 @@ def problem_of(x: torch.Tensor, grid) -> Problem:
     """Problem descriptor of a [B, H, N, d_h] activation tensor."""
     B, H, N, d = x.shape
     return problem(B, H, N, d, grid, x.dtype)
+
+
+# The entry points' own descriptors and sizes are pure functions of a few numbers that the same program
+# passes on every call: kept by value (never by tensor), bounded.
+@functools.lru_cache(maxsize=1024)
+def _cached_problem(B, H, N, d_h, T, Hs, Ws, code) -> Problem:
+    return Problem(B, H, N, d_h, T, Hs, Ws, code)
+
+
+_DTYPE_CODES = {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16}
+
+
+def _prob_of(x: torch.Tensor, grid) -> Problem:
+    """problem_of for a call's own use (shared: not to be written)."""
+    B, H, N, d = x.shape
+    T, Hs, Ws = grid
+    return _cached_problem(B, H, N, d, T, Hs, Ws, _DTYPE_CODES[x.dtype])
 
 
 # ---- argument checks ------------------------------------------------------------------------------
@@ -157,7 +178,7 @@ class _Args:
             raise ValueError(f"{name} must be a tensor")
         if x.dtype != dtype:
             raise ValueError(f"{name} must be {dtype}, got {x.dtype}")
-        if tuple(x.shape) != tuple(shape):
+        if x.shape != shape and tuple(x.shape) != tuple(shape):
             raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(x.shape)}")
         self.placed.append((x, name, inner_only))
         return x
@@ -218,7 +239,7 @@ class _Args:
         return ws
 
     def done(self):
-        device = None
+        device = None  # index of the first tensor's device
         for x, name, inner_only in self.placed:
             if inner_only:
                 if x.stride(-1) != 1:
@@ -227,18 +248,22 @@ class _Args:
                 raise ValueError(f"{name} must be contiguous")
             if not x.is_cuda:
                 raise ValueError(f"{name} must be a device tensor")
+            index = x.get_device()
             if device is None:
-                device = x.device
-            elif x.device != device:
-                raise ValueError(f"{name} is on {x.device}, the other arguments on {device}")
+                device = index
+            elif index != device:
+                raise ValueError(f"{name} is on {x.device}, the other arguments on "
+                                 f"{self.placed[0][0].device}")
 
 
 # ---- host helpers ---------------------------------------------------------------------------------
 
+@functools.lru_cache(maxsize=1024)
 def num_blocks(N: int, block: int) -> int:
     return LIB.rola_num_blocks(N, block)
 
 
+@functools.lru_cache(maxsize=1024)
 def keep_blocks(n_blocks: int, sparsity: float) -> int:
     return LIB.rola_keep_blocks(n_blocks, sparsity)
 
@@ -273,7 +298,7 @@ def rola_rope_apply(X, cos, sin, grid, out=None, stream=None):
     ld = a.tables(cos, sin, X, X.shape[3] // 2)
     out = torch.empty_like(X) if out is None else a.act(out, "out", X)
     a.done()
-    prob = problem_of(X, grid)
+    prob = _prob_of(X, grid)
     _check(LIB.rola_rope_apply(ctypes.byref(prob), _ptr(X), _ptr(cos), _ptr(sin), ld, _ptr(out),
                                _stream(stream)), "rola_rope_apply")
     return out
@@ -288,7 +313,7 @@ def rola_rope_backward_accumulate(dY, cos, sin, grid, dX, rotate=True, stream=No
     a.act(dX, "dX", dY)
     ld = a.tables(cos, sin, dY, dY.shape[3] // 2)
     a.done()
-    prob = problem_of(dY, grid)
+    prob = _prob_of(dY, grid)
     _check(LIB.rola_rope_backward_accumulate(ctypes.byref(prob), _ptr(dY), _ptr(cos), _ptr(sin), ld,
                                              1 if rotate else 0, _ptr(dX), _stream(stream)),
            "rola_rope_backward_accumulate")
@@ -299,14 +324,14 @@ def rola_block_select(Qr, Kr, grid, block, sparsity, out=None, ws=None, stream=N
     a = _Args()
     a.act(Qr, "Qr")
     a.act(Kr, "Kr", Qr)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     nb = num_blocks(prob.N, block)
     keep = keep_blocks(nb, sparsity)
     if out is None:
         out = torch.empty((prob.B, prob.H, nb, keep), dtype=torch.int32, device=Qr.device)
     a.blk_idx(out, Qr, block, sparsity)
-    need = select_workspace_bytes(prob, block)
     if ws is None:
+        need = select_workspace_bytes(prob, block)
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=Qr.device)
     a.workspace(ws)
     a.done()
@@ -340,7 +365,7 @@ def rola_rope_pool(X, cos, sin, grid, block, want_xr=True, xr=None, xbar=None, x
     if xnorm is not None:
         a.tensor(xnorm, "xnorm", shape[:3], torch.float32)
     a.done()
-    prob = problem_of(X, grid)
+    prob = _prob_of(X, grid)
     _check(LIB.rola_rope_pool(ctypes.byref(prob), _ptr(X), _ptr(cos), _ptr(sin), ld, block, _ptr(xr),
                               _ptr(xbar), _ptr(xnorm), _stream(stream)), "rola_rope_pool")
     return xr, xbar
@@ -355,13 +380,13 @@ def rola_block_select_pooled(Qbar, Kbar, like, grid, block, sparsity, out=None, 
     shape = (B, H, num_blocks(N, block), d)
     a.tensor(Qbar, "Qbar", shape, torch.float32)
     a.tensor(Kbar, "Kbar", shape, torch.float32)
-    prob = problem_of(like, grid)
+    prob = _prob_of(like, grid)
     if out is None:
         out = torch.empty((B, H, shape[2], keep_blocks(shape[2], sparsity)), dtype=torch.int32,
                           device=like.device)
     a.blk_idx(out, like, block, sparsity)
-    need = LIB.rola_select_pooled_workspace_bytes(ctypes.byref(prob), block)
     if ws is None:
+        need = LIB.rola_select_pooled_workspace_bytes(ctypes.byref(prob), block)
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=like.device)
     a.workspace(ws)
     a.done()
@@ -379,7 +404,7 @@ def rola_sparse_attn(Qr, Kr, V, grid, block, sparsity, blk_idx, scale=None, out=
     a.act(Kr, "Kr", Qr)
     a.act(V, "V", Qr)
     a.blk_idx(blk_idx, Qr, block, sparsity)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     out = torch.empty_like(Qr) if out is None else a.act(out, "out", Qr)
     if ws is None and share:
@@ -399,7 +424,7 @@ def rola_dense_attn(Qr, Kr, V, grid, block=64, scale=None, out=None, stream=None
     a.act(Qr, "Qr")
     a.act(Kr, "Kr", Qr)
     a.act(V, "V", Qr)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     out = torch.empty_like(Qr) if out is None else a.act(out, "out", Qr)
     a.done()
@@ -428,9 +453,9 @@ def rola_lowrank_summary(Kn, V, Pk, r, cos, sin, grid, C=None, z=None, ws=None, 
                          want_z=True):
     a = _Args()
     ld, C, z = _summary_args(a, Kn, V, Pk, r, cos, sin, C, z, want_z)
-    prob = problem_of(Kn, grid)
-    need = summary_workspace_bytes(prob, r)
+    prob = _prob_of(Kn, grid)
     if ws is None:
+        need = summary_workspace_bytes(prob, r)
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=Kn.device)
     a.workspace(ws)
     a.done()
@@ -452,7 +477,7 @@ def rola_lowrank_readout(Qn, Pq, r, cos, sin, C, grid, eps_lr=1e-6, out=None, st
     ld = _readout_args(a, Qn, Pq, r, cos, sin, C)
     out = torch.empty_like(Qn) if out is None else a.act(out, "out", Qn)
     a.done()
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     _check(LIB.rola_lowrank_readout(ctypes.byref(prob), _ptr(Qn), _ptr(Pq), r, _ptr(cos), _ptr(sin),
                                     ld, _ptr(C), eps_lr, _ptr(out), _stream(stream)),
            "rola_lowrank_readout")
@@ -466,7 +491,7 @@ def rola_combine(Os, Olr, logits, grid, eps=1e-6, out=None, stream=None):
     a.logits(logits, Os)
     out = torch.empty_like(Os) if out is None else a.act(out, "out", Os)
     a.done()
-    prob = problem_of(Os, grid)
+    prob = _prob_of(Os, grid)
     _check(LIB.rola_combine(ctypes.byref(prob), _ptr(Os), _ptr(Olr), _ptr(logits), eps, _ptr(out),
                             _stream(stream)), "rola_combine")
     return out
@@ -480,7 +505,7 @@ def rola_lowrank_readout_combine(Qn, Pq, r, cos, sin, C, Os, logits, grid, eps_l
     a.logits(logits, Qn)
     out = torch.empty_like(Os) if out is None else a.act(out, "out", Qn)
     a.done()
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     _check(LIB.rola_lowrank_readout_combine(ctypes.byref(prob), _ptr(Qn), _ptr(Pq), r, _ptr(cos),
                                             _ptr(sin), ld, _ptr(C), eps_lr, _ptr(Os),
                                             _ptr(logits), eps, _ptr(out), _stream(stream)),
@@ -492,9 +517,9 @@ def rola_lowrank_summary_ex(Kn, V, Pk, r, cos, sin, grid, phi="silu", rope_order
                             z=None, ws=None, stream=None, want_z=True):
     a = _Args()
     ld, C, z = _summary_args(a, Kn, V, Pk, r, cos, sin, C, z, want_z)
-    prob = problem_of(Kn, grid)
-    need = summary_workspace_bytes(prob, r)
+    prob = _prob_of(Kn, grid)
     if ws is None:
+        need = summary_workspace_bytes(prob, r)
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device=Kn.device)
     a.workspace(ws)
     a.done()
@@ -511,7 +536,7 @@ def rola_lowrank_readout_ex(Qn, Pq, r, cos, sin, C, grid, phi="silu", rope_order
     ld = _readout_args(a, Qn, Pq, r, cos, sin, C)
     out = torch.empty_like(Qn) if out is None else a.act(out, "out", Qn)
     a.done()
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     _check(LIB.rola_lowrank_readout_ex(ctypes.byref(prob), _ptr(Qn), _ptr(Pq), r, _ptr(cos),
                                        _ptr(sin), ld, _code(PHI, phi),
                                        _code(ROPE_ORDER, rope_order), _ptr(C), eps_lr, _ptr(out),
@@ -528,7 +553,7 @@ def rola_lowrank_readout_combine_ex(Qn, Pq, r, cos, sin, C, Os, logits, grid, ph
     a.logits(logits, Qn)
     out = torch.empty_like(Os) if out is None else a.act(out, "out", Qn)
     a.done()
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     _check(LIB.rola_lowrank_readout_combine_ex(ctypes.byref(prob), _ptr(Qn), _ptr(Pq), r, _ptr(cos),
                                                _ptr(sin), ld, _code(PHI, phi),
                                                _code(ROPE_ORDER, rope_order), _ptr(C), eps_lr,
@@ -544,7 +569,7 @@ def rola_lowrank_features(X, P, r, cos, sin, grid, phi="silu", rope_order="outsi
     a.act(X, "X")
     a.proj(P, "P", X, r)
     ld = a.tables(cos, sin, X, r // 2)
-    prob = problem_of(X, grid)
+    prob = _prob_of(X, grid)
     shape = (prob.B, prob.H, prob.N, r)
     if out is None:
         out = torch.empty(shape, dtype=torch.float32, device=X.device)
@@ -568,7 +593,8 @@ def rola_gate_logits(X, Wg, bg, grid, H=1, d_h=128, out=None, stream=None):
     """Gate logits X W_g + b_g of every token: X [B, N, d_model], W_g [d_model] -> fp32 [B, N]."""
     a = _Args()
     B, N, dm = _hidden(a, X, Wg)
-    prob = problem(B, H, N, d_h, grid, X.dtype)
+    T, Hs, Ws = grid
+    prob = _cached_problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[X.dtype])
     if out is None:
         out = torch.empty((B, N), dtype=torch.float32, device=X.device)
     a.tensor(out, "out", (B, N), torch.float32)
@@ -609,7 +635,7 @@ def rola_sparse_attn_combine(Qr, Kr, V, grid, block, sparsity, blk_idx, Qn, Pq, 
     a = _Args()
     ld = _combine_args(a, Qr, Kr, V, block, sparsity, blk_idx, Qn, Pq, r, cos, sin, C, logits,
                        key_norm)
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     out = torch.empty_like(Qn) if out is None else a.act(out, "out", Qn)
     if ws is None:
@@ -633,7 +659,7 @@ def rola_sparse_plan(blk_idx, like, grid, block, sparsity, r, ws, stream=None):
     a.blk_idx(blk_idx, like, block, sparsity)
     a.workspace(ws)
     a.done()
-    prob = problem_of(like, grid)
+    prob = _prob_of(like, grid)
     _check(LIB.rola_sparse_plan(ctypes.byref(prob), block, sparsity, _ptr(blk_idx), r, _ptr(ws),
                                 ws.numel(), _stream(stream)), "rola_sparse_plan")
     return ws
@@ -646,7 +672,7 @@ def rola_sparse_attn_combine_planned(Qr, Kr, V, grid, block, sparsity, blk_idx, 
     a = _Args()
     ld = _combine_args(a, Qr, Kr, V, block, sparsity, blk_idx, Qn, Pq, r, cos, sin, C, logits,
                        key_norm)
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     out = torch.empty_like(Qn) if out is None else a.act(out, "out", Qn)
     a.workspace(ws)
@@ -670,7 +696,7 @@ def rola_sparse_attn_combine_noalloc(Qr, Kr, V, grid, block, sparsity, blk_idx, 
                        key_norm)
     a.act(out, "out", Qn)
     a.done()
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     _check(LIB.rola_sparse_attn_combine_noalloc(ctypes.byref(prob), _ptr(Qr), _ptr(Kr), _ptr(V),
                                                 block, sparsity, _ptr(blk_idx), scale, _ptr(Qn),
@@ -690,7 +716,7 @@ def rola_sparse_attn_lse(Qr, Kr, V, grid, block, sparsity, blk_idx, scale=None, 
     a.act(Kr, "Kr", Qr)
     a.act(V, "V", Qr)
     a.blk_idx(blk_idx, Qr, block, sparsity)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     out = torch.empty_like(Qr) if out is None else a.act(out, "out", Qr)
     if lse is None:
@@ -718,7 +744,7 @@ def rola_sparse_attn_backward(Qr, Kr, V, grid, block, sparsity, blk_idx, Os, lse
         a.act(t, name, Qr)
     a.blk_idx(blk_idx, Qr, block, sparsity)
     a.tensor(lse, "lse", Qr.shape[:3], torch.float32)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     dQ = torch.empty(Qr.shape, dtype=torch.float32, device=Qr.device)
     dK, dV = torch.empty_like(dQ), torch.empty_like(dQ)
@@ -747,7 +773,7 @@ def rola_sparse_attn_backward_accumulate(Qr, Kr, V, grid, block, sparsity, blk_i
     ld = a.tables(cos, sin, Qr, Qr.shape[3] // 2)
     for t, name in ((dQn, "dQn"), (dKn, "dKn"), (dV, "dV")):
         a.tensor(t, name, Qr.shape, torch.float32)
-    prob = problem_of(Qr, grid)
+    prob = _prob_of(Qr, grid)
     scale = prob.d_h ** -0.5 if scale is None else scale
     if ws is None:
         need = LIB.rola_sparse_backward_workspace_bytes(ctypes.byref(prob), block, sparsity)
@@ -770,7 +796,7 @@ def rola_lowrank_backward(Qn, Kn, V, Pq, Pk, r, cos, sin, C, Os, logits, dO, gri
         a.act(t, name, Qn)
     a.proj(Pk, "Pk", Qn, r)
     a.logits(logits, Qn)
-    prob = problem_of(Qn, grid)
+    prob = _prob_of(Qn, grid)
     dOs = torch.empty_like(Qn)
     f32 = dict(dtype=torch.float32, device=Qn.device)
     dQn, dKn, dV = (torch.empty(Qn.shape, **f32) for _ in range(3))
@@ -796,7 +822,8 @@ def rola_gate_logits_backward(X, Wg, dlogits, grid, H=1, d_h=128, want_dX=True, 
     a = _Args()
     B, N, dm = _hidden(a, X, Wg)
     a.tensor(dlogits, "dlogits", (B, N), torch.float32)
-    prob = problem(B, H, N, d_h, grid, X.dtype)
+    T, Hs, Ws = grid
+    prob = _cached_problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[X.dtype])
     f32 = dict(dtype=torch.float32, device=X.device)
     dX = torch.empty(X.shape, **f32) if want_dX else None
     dWg, dbg = torch.empty(dm, **f32), torch.empty(4, **f32)
