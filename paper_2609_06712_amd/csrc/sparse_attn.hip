@@ -641,9 +641,16 @@ struct AttnArgs {
 // and V tiles use the swizzle that serves both row and transposing reads (bw_swizzle).
 // BOUND (merged lists, G > 1): the softmax reference of each wave is the bound on its scores that
 // the key-block norms give, where that bound is small enough (see the prologue).
+//
+// Three four-wave workgroups fit a CU (LDS, 168 VGPRs). Every such variant reaches that; where the
+// compiler is told, it orders the code for it: the fused layer with 128-token blocks needs the bound (12
+// heads of 32,760, r 32: 909 -> 844 us), dense attention (no list) gains by it (8,400 keys 1308 -> 1293,
+// 32,760 keys 5856 -> 5796), the static walk over lists without an epilogue loses (128-token blocks,
+// 20 heads of 32,175: 1697 with two, 1710 with three).
 template <int BLK, int G, int NBUF, int TAB, int RJ, bool QUEUE, bool DQ = false, bool BOUND = false>
-__global__ __launch_bounds__(G * BLK * 2, G * BLK == 128 && !DQ ? 3 : 2) void sparse_attn_kernel(
-    const AttnArgs args) {
+__global__ __launch_bounds__(G * BLK * 2,
+                             G * BLK == 128 && !DQ && (QUEUE || RJ > 0 || TAB == 0) ? 3 : 2)
+void sparse_attn_kernel(const AttnArgs args) {
   static_assert(G == 1 || G == 2 || G == 4, "one, two or four query blocks per workgroup");
   static_assert(NBUF >= 3, "loads of later sub-tiles stay in flight during a step");
   constexpr int D = 128, WPB = BLK / 32, NW = G * WPB;
