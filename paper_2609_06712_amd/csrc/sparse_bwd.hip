@@ -12,7 +12,7 @@
 //                      bwd_reverse_kernel) in 32-query steps: one role of waves holds the keys' K
 //                      (S, P, dV), the other their V (dP, dS, dK) and takes P from the first one
 //                      step later; Q and dO rows (and the queries' lse and D) through four LDS
-//                      stages.
+//                      stages: one read back (role 1), one current, one ahead, one in flight.
 // Products on v_mfma_f32_32x32x16_bf16. S and dP come out with one lane per key and the 32 queries
 // in its registers; the products that contract over queries (dK, dV) take their other operand through
 // the transposing LDS read ds_read_b64_tr_b16, in the order the registers hold the contracted index (as
@@ -152,7 +152,18 @@ __global__ __launch_bounds__(4 * kOrderBlocks) void bwd_order_kernel(int nb, int
 // half the register file, and the compiler then moves accumulators between the two register files
 // every step), so two waves run per SIMD. A step takes 32 queries. P goes over as fp16: it lies
 // in [0, 1], where fp16's relative error (2^-11; absolute 2^-25 below 2^-14) is an eighth of the
-// bf16 rounding dS takes next. Workgroups take a head's key blocks longest list first
+// bf16 rounding dS takes next.
+//
+// What bounds it: per step a wave reads 16 KB of operands from LDS for 16 products, so the LDS and the
+// matrix cores have about the same work (140 and 128 cycles per wave and step), and all waves of a
+// workgroup leave the barrier together. Operands are therefore read a product ahead: the row operand of
+// the next step while this step's second product runs, the transposed one while the first does, and
+// the second half's softmax (or dS) between the first half's products. Read at the head of their own
+// step instead, the eight waves of a CU waited for 128 KB of LDS reads while the matrix cores idled: 12
+// heads of 512 blocks of 64 1.73 -> 1.46 ms, 5 of 528 blocks of 128 1.79 -> 1.37 (matrix cores busy 29 %
+// -> 40 %).
+//
+// Workgroups take a head's key blocks longest list first
 // (bwd_order_kernel) and walk each list in the bit-reversed order, so that workgroups running at
 // the same time sit on about the same query blocks and share their Q and dO rows in L2.
 //
@@ -161,7 +172,9 @@ __global__ __launch_bounds__(4 * kOrderBlocks) void bwd_order_kernel(int nb, int
 // contiguous eighths of everything instead, an XCD of a few-headed problem got the long lists of a head
 // and its neighbour the short ones (5 heads, 528 blocks of 128: 2.10 ms; 12 heads, 512 blocks of 64:
 // 1.73 ms).
-constexpr int kDkvNbuf = 4;  // LDS stages of sparse_dkv_kernel: 32 Q rows, 32 dO rows, lse/D (17 KB)
+// LDS stages of sparse_dkv_kernel: 32 Q rows, 32 dO rows, lse/D (17 KB). A fifth, which 128-token blocks
+// have room for, cost 1 % (5 heads of 67545 tokens).
+constexpr int kDkvNbuf = 4;
 // Workgroups of the grid, and the place (head * nb + rank) workgroup wg takes, -1 for none.
 __host__ __device__ inline int dkv_grid(int heads, int nb) {
   return kNumXcd * (heads / kNumXcd * nb + (heads % kNumXcd * nb + kNumXcd - 1) / kNumXcd);
@@ -186,7 +199,7 @@ void sparse_dkv_kernel(
   constexpr int DPW = 2 * (TILE / 1024) / NW;  // 1 KB tile loads per wave and step
   constexpr int SUBS = BLK / kBSub;            // steps per query block
   constexpr int PBUF = NKW * 2048;             // P of a step, fp16: per key tile 16 values a lane
-  constexpr int AHEAD = NBUF - 2;              // stages loaded ahead (role 1 still reads one back)
+  constexpr int AHEAD = NBUF - 3;              // stages in flight: three are read (one back, one on)
   static_assert(DPW >= 1 && 2 * (TILE / 1024) % NW == 0 && AHEAD >= 1, "64- or 128-key blocks");
   __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE + 2 * PBUF];
 
@@ -252,94 +265,118 @@ void sparse_dkv_kernel(
     if (wave == 0) dma16(lsebase, (uint32_t)(q0 * 8 + (lane % 16) * 16), dst + 2 * TILE);
   };
 
+  char* pbase = lds + NBUF * STAGE + kw * 2048 + lane * 16;  // + buffer * PBUF + u * 1024
   int issued = 0;
 #pragma unroll
-  for (int j = 0; j < AHEAD; ++j)
+  for (int j = 0; j <= AHEAD; ++j)
     if (j < T) issue(query0(j), j), ++issued;
-  char* pbase = lds + NBUF * STAGE + kw * 2048 + lane * 16;  // + buffer * PBUF + u * 1024
-  // Iteration t: role 0 takes step t (t < T), role 1 step t - 1 (t >= 1).
-  for (int t = 0; t <= T;) {
+  __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
+  __syncthreads();
+  // Iteration t: role 0 takes step t, role 1 step t - 1. Each role has a loop of its own (its stage
+  // offsets are then constants), of whole turns of NBUF iterations (an exit between them costs
+  // registers); both meet the same barriers.
+  auto walk = [&](auto role_tag) {
+    constexpr int ROLE = decltype(role_tag)::value;
+    // Row operands (Q for role 0, dO for role 1) of the wave's next step.
+    bf16x8 fa[8];
+    auto row_operands = [&](int stage) {
 #pragma unroll
-    for (int b = 0; b < NBUF; ++b) {
-      if (t > T) break;
-      // The first query of this step's tile and of the tile whose loads it issues, read from the
-      // list before the wait and the barrier (indices clamped into the list; pinned in SGPRs, or
-      // the compiler sinks the scalar loads behind the barrier).
-      int qcur = query0(max(0, min(t, T - 1))), qiss = query0(max(0, min(issued, T - 1)));
-      asm volatile("" : "+s"(qcur), "+s"(qiss));
-      if (t < T && issued == t + AHEAD) {
-        constexpr int a0 = (DPW + 1) * (AHEAD - 1), a1 = DPW * (AHEAD - 1);
-        if (wave == 0)
-          __builtin_amdgcn_s_waitcnt((a0 & 15) | ((a0 >> 4) << 14) | (7 << 4) | (15 << 8));
-        else
-          __builtin_amdgcn_s_waitcnt((a1 & 15) | ((a1 >> 4) << 14) | (7 << 4) | (15 << 8));
-      } else {
-        __builtin_amdgcn_s_waitcnt(0);
-      }
-      __syncthreads();
-      if (issued < T) issue(qiss, (b + AHEAD) % NBUF), ++issued;
-      if (role ? t >= 1 : t < T) {
-        const char* Qt = lds + (role ? (b + NBUF - 1) % NBUF : b) * STAGE;
-        const char* dOt = Qt + TILE;
-        const float2* lt = reinterpret_cast<const float2*>(Qt + 2 * TILE);
-        char* pb = pbase + ((b + role) % 2) * PBUF;  // role 0 writes step t's, role 1 reads t - 1's
-        // S (role 0) or dP (role 1): one lane per key; rows 8j + 4(l/32) + i are the step's queries
-        // All operand fragments of the step are read up front (the transposed ones do not wait
-        // for P), so that the products do not wait on LDS one fragment at a time.
-        const char* A1 = role ? dOt : Qt;
-        const char* A2 = role ? Qt : dOt;
-        bf16x8 fa[8], fb[8];
+      for (int s = 0; s < 8; ++s) fa[s] = row_frag(lds + stage * STAGE + ROLE * TILE, lane % 32, s, hh);
+    };
+    if (ROLE == 0) row_operands(0);
+    for (int t = 0; t <= T;) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) fa[s] = row_frag(A1, lane % 32, s, hh);
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-#pragma unroll
-          for (int u = 0; u < 2; ++u) fb[2 * w + u] = tr_frag(A2, w, u, lane);
-        __builtin_amdgcn_sched_barrier(0);
-        f32x16 X = f32x16{};
-#pragma unroll
-        for (int s = 0; s < 8; ++s) X = mfma32(fa[s], bf[s], X);
-        float p[16];
-        bf16x8 b2[2];
-        if (role == 0) {
-          const int q0 = qcur;
-          // The exponentials are computed unconditionally and rows past N zeroed in one uniform
-          // branch: a per-element condition around them splits the step into a basic block per
-          // element, across which no matrix instruction can be scheduled.
-#pragma unroll
-          for (int k = 0; k < 16; ++k)
-            p[k] = __builtin_amdgcn_exp2f(fmaf(X[k], scale_log2, -lt[8 * (k / 4) + 4 * hh + k % 4].x));
-          if (q0 + kBSub > N) {  // ragged last query block (uniform)
-#pragma unroll
-            for (int k = 0; k < 16; ++k) p[k] = q0 + 8 * (k / 4) + 4 * hh + k % 4 < N ? p[k] : 0.f;
-          }
-          f16x8 ph[2];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            b2[k / 8][k % 8] = (bf16)p[k];
-            ph[k / 8][k % 8] = (_Float16)p[k];
-          }
-          *reinterpret_cast<f16x8*>(pb) = ph[0];
-          *reinterpret_cast<f16x8*>(pb + 1024) = ph[1];
+      for (int b = 0; b < NBUF; ++b, ++t) {
+        // The first query of this step's tile and of the tile whose loads it issues, read from the
+        // list before the wait and the barrier (indices clamped into the list; pinned in SGPRs, or
+        // the compiler sinks the scalar loads behind the barrier).
+        int qcur = query0(max(0, min(t, T - 1))), qiss = query0(max(0, min(issued, T - 1)));
+        asm volatile("" : "+s"(qcur), "+s"(qiss));
+        if (AHEAD > 1 && issued == t + 1 + AHEAD) {  // stage t + 1 has landed
+          constexpr int a0 = (DPW + 1) * (AHEAD - 1), a1 = DPW * (AHEAD - 1);
+          if (wave == 0)
+            __builtin_amdgcn_s_waitcnt((a0 & 15) | ((a0 >> 4) << 14) | (7 << 4) | (15 << 8));
+          else
+            __builtin_amdgcn_s_waitcnt((a1 & 15) | ((a1 >> 4) << 14) | (7 << 4) | (15 << 8));
         } else {
-          const f16x8 ph0 = *reinterpret_cast<const f16x8*>(pb);
-          const f16x8 ph1 = *reinterpret_cast<const f16x8*>(pb + 1024);
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            const float pk = (float)(k < 8 ? ph0[k] : ph1[k - 8]);
-            b2[k / 8][k % 8] = (bf16)(pk * (X[k] - lt[8 * (k / 4) + 4 * hh + k % 4].y));
-          }
+          __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
         }
-        // dV^T += dO^T P (role 0) or dK^T += Q^T dS (role 1), the transposed operand in the order
-        // the registers hold the queries
+        __syncthreads();
+        if (issued < T) issue(qiss, (b + 1 + AHEAD) % NBUF), ++issued;
+        const int step = t - ROLE;
+        if (step >= 0 && step < T) {
+          const char* stage = lds + (ROLE ? (b + NBUF - 1) % NBUF : b) * STAGE;
+          const float* lt = reinterpret_cast<const float*>(stage + 2 * TILE) + ROLE;
+          char* pb = pbase + ((b + ROLE) % 2) * PBUF;  // role 0 writes step t's, role 1 reads t - 1's
+          // The transposed operand of the second product and the step's other LDS values are read
+          // while the first product runs, the next step's row operand while the second does.
+          bf16x8 fb[8];
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
+          for (int w = 0; w < 4; ++w)
 #pragma unroll
-          for (int u = 0; u < 2; ++u) acc[w] = mfma32(fb[2 * w + u], b2[u], acc[w]);
+            for (int u = 0; u < 2; ++u) fb[2 * w + u] = tr_frag(stage + (1 - ROLE) * TILE, w, u, lane);
+          float lv[16];  // lse (role 0) or D (role 1) of the step's queries
+#pragma unroll
+          for (int k = 0; k < 16; ++k) lv[k] = lt[2 * (8 * (k / 4) + 4 * hh + k % 4)];
+          // S (role 0) or dP (role 1): one lane per key; rows 8j + 4(l/32) + i are the step's queries
+          f32x16 X = f32x16{};
+#pragma unroll
+          for (int s = 0; s < 8; ++s) X = mfma32(fa[s], bf[s], X);
+          f16x8 ph[2];
+          if constexpr (ROLE == 1) {
+            ph[0] = *reinterpret_cast<const f16x8*>(pb);
+            ph[1] = *reinterpret_cast<const f16x8*>(pb + 1024);
+          }
+          __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          row_operands(ROLE ? b : (b + 1) % NBUF);
+          if (ROLE == 0 && qcur + kBSub > N) {  // ragged last query block (uniform): P = 0 past N
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+              lv[k] = qcur + 8 * (k / 4) + 4 * hh + k % 4 < N ? lv[k] : __builtin_inff();
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          // dV^T += dO^T P (role 0) or dK^T += Q^T dS (role 1), the transposed operand in the order
+          // the registers hold the queries, in two halves: the second half's P or dS is computed
+          // between the first half's products.
+          bf16x8 b2[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              if constexpr (ROLE == 0) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(X[8 * u + k], scale_log2, -lv[8 * u + k]));
+                b2[u][k] = (bf16)p;
+                ph[u][k] = (_Float16)p;
+              } else {
+                b2[u][k] = (bf16)((float)ph[u][k] * (X[8 * u + k] - lv[8 * u + k]));
+              }
+            }
+            if constexpr (ROLE == 0) *reinterpret_cast<f16x8*>(pb + 1024 * u) = ph[u];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) acc[w] = mfma32(fb[2 * w + u], b2[u], acc[w]);
+          }
+          __builtin_amdgcn_sched_group_barrier(0x402, 28, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x402, 7, 0);
+          }
+        } else if (step < 0) {
+          row_operands(0);
+        }
       }
-      ++t;
     }
-  }
+  };
+  if (role)
+    walk(std::integral_constant<int, 1>{});
+  else
+    walk(std::integral_constant<int, 0>{});
   if (kvalid) {  // dV^T (role 0), dK^T (role 1): lane = key, rows = channels 32w + 8j + 4(l/32) + i
     float* out = (role ? dK : dV) + hoff + (long)key * D;
     const float f = role ? scale : 1.f;

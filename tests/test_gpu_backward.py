@@ -143,6 +143,40 @@ def test_sparse_backward_heads_over_xcds(grid, block, H, B):
                 assert _rel(_f64(t[b, h]), want[n]) <= 1e-2, (b, h, n)
 
 
+@pytest.mark.parametrize("block,ragged", [(64, 0), (64, 37), (128, 0), (128, 101)])
+def test_sparse_backward_short_transposed_lists(block, ragged):
+    """Eleven key blocks selected by 0, 1, .., 10 query blocks: dK/dV walks of no step, of fewer steps
+    than LDS stages and of every remainder of a turn, with a whole and a ragged last query block.
+    Tolerance as the other backward tests (bf16 operands, relative error of a tensor); blocks that no
+    query selects get exactly zero."""
+    nb, keep = 11, 5
+    w = synth.WAN_1_3B_480P.replace(grid=(1, 1, nb * block - ragged), H=1, B=1, block=block, sparsity=0.55)
+    assert R.keep_blocks(nb, w.sparsity) == keep
+    left = np.full(nb, keep)
+    rows = [[] for _ in range(nb)]
+    for J in range(nb - 1, -1, -1):  # key block J goes to the J query blocks with the most room left
+        for I in np.argsort(-left, kind="stable")[:J]:
+            rows[I].append(J)
+            left[I] -= 1
+    assert not left.any()
+    idx = torch.tensor([sorted(r) for r in rows], dtype=torch.int32)[None, None].cuda()
+    d = {k: v.cuda() for k, v in synth.make_inputs(w, 8).items()}
+    q, k, v = d["Qn"], d["Kn"], d["V"]
+    os_, lse = R.rola_sparse_attn_lse(q, k, v, w.grid, block, w.sparsity, idx)
+    dos = torch.randn(q.shape, generator=torch.Generator().manual_seed(6)).to(torch.bfloat16).cuda()
+    grads = R.rola_sparse_attn_backward(q, k, v, w.grid, block, w.sparsity, idx, os_, lse, dos)
+    torch.cuda.synchronize()
+    want = G.sparse_attention_grads(_f64(q[0, 0]), _f64(k[0, 0]), _f64(v[0, 0]), idx[0, 0].cpu().numpy(),
+                                    block, w.d_h ** -0.5, _f64(dos[0, 0]))
+    for n, t in zip(("dqr", "dkr", "dv"), grads):
+        assert _rel(_f64(t[0, 0]), want[n]) <= 1e-2, n
+        for J in range(nb):  # every block by itself: a step lost in a short list shows
+            r = slice(J * block, (J + 1) * block)
+            err = np.abs(_f64(t[0, 0])[r] - want[n][r]).max()
+            assert err <= 2e-2 * np.abs(want[n]).max(), (n, J, err)
+    assert torch.count_nonzero(grads[1][0, 0, :block]) == 0 and torch.count_nonzero(grads[2][0, 0, :block]) == 0
+
+
 def test_sparse_backward_many_groups():
     """200 heads of 390 tokens: 800 (head, pair) groups, more than the chip holds at once, so the dQ
     pass's resident workgroups each take several groups from the work queues. Sampled heads against
