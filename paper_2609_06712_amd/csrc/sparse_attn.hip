@@ -979,30 +979,57 @@ void sparse_attn_kernel(const AttnArgs args) {
         if (DQ && act) {
           const char* Kt = lds + j * STAGE;
           const char* Vt = Kt + TILE;
+          // Operands are read ahead: six rows before the first product, two LDS reads behind each
+          // product, so the two chains of eight and the transposed operand of the last product do
+          // not wait on LDS; the second half's dS is computed between the first half's products (the
+          // training step with 128-token blocks 3312 -> 3290 us, 5 heads of 67545 tokens; with
+          // 64-token blocks, bound by the barriers of the merged walk, no change).
+          bf16x8 ka[8], va[8], kt[8];
           f32x16 sc = f32x16{}, dp = f32x16{};
 #pragma unroll
           for (int s = 0; s < 8; ++s) {
-            sc = mfma32(row_frag(Kt, lane % 32, s, hh), qf[s], sc);
-            dp = mfma32(row_frag(Vt, lane % 32, s, hh), df[s], dp);
+            ka[s] = row_frag(Kt, lane % 32, s, hh);
+            va[s] = row_frag(Vt, lane % 32, s, hh);
+          }
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) kt[4 * u + w] = tr_frag(Kt, w, u, lane);
+#pragma unroll
+          for (int s = 0; s < 8; ++s) {
+            sc = mfma32(ka[s], qf[s], sc);
+            dp = mfma32(va[s], df[s], dp);
+          }
+          __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);  // DS reads
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
           }
           // value k: key k0 + 8(k/4) + 4(l/32) + k%4 of this lane's query
-          float pr[16];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) pr[k] = __builtin_amdgcn_exp2f(fmaf(sc[k], scale_log2, -lse_q));
-          if (cur.k0 + kSub > N) {  // ragged last block: keys past N
+          if (cur.k0 + kSub > N) {  // ragged last block: P = 0 for keys past N
             const int lim = N - cur.k0 - 4 * hh;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) pr[k] = 8 * (k / 4) + k % 4 < lim ? pr[k] : 0.f;
+            for (int k = 0; k < 16; ++k) sc[k] = 8 * (k / 4) + k % 4 < lim ? sc[k] : -__builtin_inff();
           }
+          __builtin_amdgcn_sched_barrier(0);
           bf16x8 ds[2];
 #pragma unroll
-          for (int k = 0; k < 16; ++k) ds[k / 8][k % 8] = (bf16)(pr[k] * (dp[k] - dsum_q));
-          __builtin_amdgcn_s_setprio(1);  // as the forward's P V products (sparse backward -0.8 %)
+          for (int u = 0; u < 2; ++u) {
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
+            for (int k = 0; k < 8; ++k) {
+              const float pr = __builtin_amdgcn_exp2f(fmaf(sc[8 * u + k], scale_log2, -lse_q));
+              ds[u][k] = (bf16)(pr * (dp[8 * u + k] - dsum_q));
+            }
 #pragma unroll
-            for (int u = 0; u < 2; ++u) acc[w] = mfma32(tr_frag(Kt, w, u, lane), ds[u], acc[w]);
-          __builtin_amdgcn_s_setprio(0);
+            for (int w = 0; w < 4; ++w) acc[w] = mfma32(kt[4 * u + w], ds[u], acc[w]);
+          }
+          __builtin_amdgcn_sched_group_barrier(0x402, 36, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x402, 9, 0);
+          }
         } else if (!DQ && act) {
           bf16x8 kf[4], kg[4], vf[4], pb[2];
           load_k(j, 0, kf);
