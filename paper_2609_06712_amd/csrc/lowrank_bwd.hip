@@ -53,12 +53,31 @@ __device__ __forceinline__ float silu_grad(float y) {  // d/dy y sigmoid(y)
 // fp32 operands enter as bf16 hi + lo pairs (three products, or two against exact bf16 data), which
 // keeps them to about 2^-16 relative. Partials per chunk as in the plain kernels.
 constexpr int kStep = 64;  // tokens per workgroup step
-constexpr int kMp = 136;   // LDS row pitch (bf16) of the P and M tiles: conflict-free row reads
-constexpr int kCp = 144;   // LDS row pitch (bf16) of token-major channel tiles
-
-// LDS row pitch (bf16) of token-major coordinate tiles: conflict-free transposing reads.
-template <int JT>
-constexpr int coord_pitch() { return JT == 1 ? 48 : 72; }
+// LDS tiles hold their rows unpadded, the 16-byte chunks of a row swizzled by the row's bits so that
+// row-wise and token-major accesses do not conflict, and the transposing reads of P and M, which use one
+// half of every chunk, only as far as that makes them (two-way). Padded pitches of 136 and 144 channels
+// left two- and four-way conflicts, more than a third of the LDS's busy cycles: 40 heads, 75,600
+// tokens, r 64 both sides 2.71 -> 2.60 ms.
+//   P, M (128 channels; rows of a row read differ in bits 0, 1, 3, 4, of a transposing read in 0, 1,
+//   3): bits 0, 1, 3, 4 map to 6, 10, 1, 2.
+__device__ __forceinline__ int pm_swizzle(int row) {
+  return (2 * ((0x6530 >> (4 * (row & 3))) & 15)) ^ ((row >> 3) & 3);
+}
+//   token-major tiles (rows of a transposing read differ in bits 0, 1, 3, of a write in 0-3), by the
+//   chunks of a row: 16 (channels), 8 or 4 (coordinates, where the row's low bits already choose the
+//   banks).
+template <int CHUNKS>
+__device__ __forceinline__ int tok_swizzle(int row) {
+  static_assert(CHUNKS == 16 || CHUNKS == 8 || CHUNKS == 4, "rows of 256, 128 or 64 bytes");
+  if (CHUNKS == 16) return ((row & 3) << 1) | ((row >> 2) & 1) | (row & 8);
+  if (CHUNKS == 8) return (row & 2) | ((row >> 2) & 1) | ((row & 8) >> 1);
+  return ((row >> 2) & 1) | ((row & 8) >> 2);
+}
+// Element index of 16-byte chunk c of a token-major tile's row.
+template <int CHUNKS>
+__device__ __forceinline__ int tok_at(int row, int c) {
+  return row * (8 * CHUNKS) + 8 * (c ^ tok_swizzle<CHUNKS>(row));
+}
 
 __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -76,31 +95,32 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& 
   }
 }
 
-// Transposing read of rows row0 .. row0 + 7 of a row-major LDS tile: lane 4q + e of each 16-lane
-// group gets column col(q) + e of the eight rows (col(q) a multiple of 4).
-template <typename Col>
-__device__ __forceinline__ bf16x8 tr_read8(const bf16* tile, int pitch, int row0, Col col, int lane) {
+// Transposing read of four columns (8 bytes) of rows r and r + 4 per lane, given as the lane's pieces:
+// lane 4q + e of each 16-lane group gets element e of the pieces that lanes q, q + 4, q + 8, q + 12
+// address (rows r .. r + 3, then r + 4 .. r + 7).
+__device__ __forceinline__ bf16x8 tr_pair(const bf16* lo_piece, const bf16* hi_piece) {
   typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-  const int i16 = lane % 16;
-  const bf16* p = tile + (row0 + (i16 >> 2)) * pitch + col(i16 & 3);
-  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
-  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 4 * pitch));
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)lo_piece);
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)hi_piece);
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Operand that contracts over the rows of a row-major LDS tile: lane l gets column col0 + l%16 of
-// rows row0 .. row0 + 7, row0 given per 16-lane group.
-__device__ __forceinline__ bf16x8 tr_rows8(const bf16* tile, int pitch, int row0, int col0, int lane) {
-  return tr_read8(tile, pitch, row0, [=](int q) { return col0 + 4 * q; }, lane);
+// Operand that contracts over the rows of a token-major LDS tile: lane l gets column 16 ct + l%16 of
+// rows row0 .. row0 + 7, row0 (a multiple of 8) given per 16-lane group.
+template <int CHUNKS>
+__device__ __forceinline__ bf16x8 tr_rows8(const bf16* tile, int row0, int ct, int lane) {
+  const int i16 = lane % 16, q = i16 & 3, row = row0 + (i16 >> 2), c = 2 * ct + (q >> 1);
+  return tr_pair(tile + tok_at<CHUNKS>(row, c) + 4 * (q & 1), tile + tok_at<CHUNKS>(row + 4, c) + 4 * (q & 1));
 }
 
 // A operand of a product whose output rows are channels (F^T, dX^T): fragment w, lane 4q + e of each
 // 16-lane group, is channel 32(w/2) + 8q + 4(w%2) + e, so output lane (g, token) of fragments 2p and
 // 2p + 1 holds the consecutive channels 32p + 8g .. +7. k = the coordinates of tile rows
-// row0 .. row0 + 7.
+// row0 .. row0 + 7 (row0 a multiple of 8).
 __device__ __forceinline__ bf16x8 chan_frag(const bf16* tile, int w, int row0, int lane) {
-  const int base = 32 * (w >> 1) + 4 * (w & 1);
-  return tr_read8(tile, kMp, row0, [=](int q) { return base + 8 * q; }, lane);
+  const int i16 = lane % 16, row = row0 + (i16 >> 2);
+  const bf16* p = tile + row * kD + 8 * ((4 * (w >> 1) + (i16 & 3)) ^ pm_swizzle(row)) + 4 * (w & 1);
+  return tr_pair(p, p + 4 * kD);  // (bit 2 of the row is not part of the swizzle)
 }
 
 // Pair-major (e0..e3, o0..o3) to coordinate order (e0, o0, e1, o1, ...).
@@ -129,13 +149,13 @@ struct LrBwdArgs {
 
 template <bool KEY, int JT>
 __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
-  constexpr int D = kD, RT = 32 * JT, kRp = coord_pitch<JT>();
-  __shared__ __attribute__((aligned(16))) bf16 ps[RT * kMp];                // P
-  __shared__ __attribute__((aligned(16))) bf16 ms[2][RT * kMp];             // M hi, lo
-  __shared__ __attribute__((aligned(16))) bf16 ty[2][kStep * kRp];          // dy hi, lo [token][coord]
-  __shared__ __attribute__((aligned(16))) bf16 tx[kStep * kCp];             // x [token][channel]
-  __shared__ __attribute__((aligned(16))) bf16 tf[KEY ? 1 : 2][KEY ? 8 : kStep * kRp];  // f hi, lo
-  __shared__ __attribute__((aligned(16))) bf16 tu[KEY ? 1 : 2][KEY ? 8 : kStep * kCp];  // du hi, lo
+  constexpr int D = kD, RT = 32 * JT, CC = 4 * JT;  // CC: 16-byte chunks of a coordinate row
+  __shared__ __attribute__((aligned(16))) bf16 ps[RT * D];                // P
+  __shared__ __attribute__((aligned(16))) bf16 ms[2][RT * D];             // M hi, lo
+  __shared__ __attribute__((aligned(16))) bf16 ty[2][kStep * RT];         // dy hi, lo [token][coord]
+  __shared__ __attribute__((aligned(16))) bf16 tx[kStep * D];             // x [token][channel]
+  __shared__ __attribute__((aligned(16))) bf16 tf[KEY ? 1 : 2][KEY ? 8 : kStep * RT];  // f hi, lo
+  __shared__ __attribute__((aligned(16))) bf16 tu[KEY ? 1 : 2][KEY ? 8 : kStep * D];   // du hi, lo
   const long head = blockIdx.x / a.n_chunks;
   const int chunk = blockIdx.x % a.n_chunks, h = (int)(head % a.H);
   const long b = head / a.H;
@@ -146,7 +166,8 @@ __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
 
   // The tiles; coordinates >= r are zero rows.
   for (int e = tid; e < RT * D / 4; e += 256) {
-    const int c = e / (D / 4), ch = 4 * (e % (D / 4)), row = tile_row(c) * kMp + ch;
+    const int c = e / (D / 4), ch = 4 * (e % (D / 4)), tr = tile_row(c);
+    const int row = tr * D + 8 * ((ch / 8) ^ pm_swizzle(tr)) + ch % 8;
     float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
     bf16x4 pv = {};
     if (c < r) {
@@ -167,7 +188,8 @@ __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
   // Row operand of pair tile jt: row 16 jt + lr of the even (par 0) or odd coordinates, channels
   // 32 kc + 8g .. +7.
   auto row_op = [&](const bf16* tile, int jt, int par, int kc) {
-    return *reinterpret_cast<const bf16x8*>(tile + tile_row(2 * (16 * jt + lr) + par) * kMp + 32 * kc + 8 * g);
+    const int row = tile_row(2 * (16 * jt + lr) + par);
+    return *reinterpret_cast<const bf16x8*>(tile + row * D + 8 * ((4 * kc + g) ^ pm_swizzle(row)));
   };
   f32x4 accm[2 * JT][2], accp[2 * JT][2];  // outer products: coordinate tile rt x channel tile ct
 #pragma unroll
@@ -363,21 +385,21 @@ __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
     __syncthreads();  // the previous step's tiles are consumed
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      *reinterpret_cast<bf16x8*>(&ty[0][trow * kRp + 32 * jt + 8 * g]) = interleave(dh[jt]);
-      *reinterpret_cast<bf16x8*>(&ty[1][trow * kRp + 32 * jt + 8 * g]) = interleave(dl[jt]);
+      *reinterpret_cast<bf16x8*>(&ty[0][tok_at<CC>(trow, 4 * jt + g)]) = interleave(dh[jt]);
+      *reinterpret_cast<bf16x8*>(&ty[1][tok_at<CC>(trow, 4 * jt + g)]) = interleave(dl[jt]);
       if constexpr (!KEY) {
-        *reinterpret_cast<bf16x8*>(&tf[0][trow * kRp + 32 * jt + 8 * g]) = interleave(fh[jt]);
-        *reinterpret_cast<bf16x8*>(&tf[1][trow * kRp + 32 * jt + 8 * g]) = interleave(fl[jt]);
+        *reinterpret_cast<bf16x8*>(&tf[0][tok_at<CC>(trow, 4 * jt + g)]) = interleave(fh[jt]);
+        *reinterpret_cast<bf16x8*>(&tf[1][tok_at<CC>(trow, 4 * jt + g)]) = interleave(fl[jt]);
       }
     }
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc)
-      *reinterpret_cast<bf16x8*>(&tx[trow * kCp + 32 * kc + 8 * g]) = xf[kc];
+      *reinterpret_cast<bf16x8*>(&tx[tok_at<16>(trow, 4 * kc + g)]) = xf[kc];
     if constexpr (!KEY) {
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        *reinterpret_cast<bf16x8*>(&tu[0][trow * kCp + 32 * p + 8 * g]) = vh[p];
-        *reinterpret_cast<bf16x8*>(&tu[1][trow * kCp + 32 * p + 8 * g]) = vl[p];
+        *reinterpret_cast<bf16x8*>(&tu[0][tok_at<16>(trow, 4 * p + g)]) = vh[p];
+        *reinterpret_cast<bf16x8*>(&tu[1][tok_at<16>(trow, 4 * p + g)]) = vl[p];
       }
     }
     __syncthreads();
@@ -387,22 +409,22 @@ __global__ __launch_bounds__(256) void lr_bwd_mfma_kernel(const LrBwdArgs a) {
 #pragma unroll
       for (int rt = 0; rt < 2 * JT; ++rt) {
         if (rt >= nrt) break;
-        const bf16x8 ah = tr_rows8(ty[0], kRp, r0, 16 * rt, lane);
-        const bf16x8 al = tr_rows8(ty[1], kRp, r0, 16 * rt, lane);
+        const bf16x8 ah = tr_rows8<CC>(ty[0], r0, rt, lane);
+        const bf16x8 al = tr_rows8<CC>(ty[1], r0, rt, lane);
         bf16x8 fh2, fl2;
         if constexpr (!KEY) {
-          fh2 = tr_rows8(tf[0], kRp, r0, 16 * rt, lane);
-          fl2 = tr_rows8(tf[1], kRp, r0, 16 * rt, lane);
+          fh2 = tr_rows8<CC>(tf[0], r0, rt, lane);
+          fl2 = tr_rows8<CC>(tf[1], r0, rt, lane);
         }
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
-          const int c0 = 32 * wave + 16 * ct;
-          const bf16x8 bx = tr_rows8(tx, kCp, r0, c0, lane);
+          const int c0 = 2 * wave + ct;  // 16-channel tile
+          const bf16x8 bx = tr_rows8<16>(tx, r0, c0, lane);
           accp[rt][ct] = mfma16(ah, bx, accp[rt][ct]);
           accp[rt][ct] = mfma16(al, bx, accp[rt][ct]);
           if constexpr (!KEY) {
-            const bf16x8 uh = tr_rows8(tu[0], kCp, r0, c0, lane);
-            const bf16x8 ul = tr_rows8(tu[1], kCp, r0, c0, lane);
+            const bf16x8 uh = tr_rows8<16>(tu[0], r0, c0, lane);
+            const bf16x8 ul = tr_rows8<16>(tu[1], r0, c0, lane);
             accm[rt][ct] = mfma16(fh2, uh, accm[rt][ct]);
             accm[rt][ct] = mfma16(fh2, ul, accm[rt][ct]);
             accm[rt][ct] = mfma16(fl2, uh, accm[rt][ct]);
