@@ -76,7 +76,7 @@ __device__ __forceinline__ void feature_pair(float& e, float& o, float c, float 
 // (kPaper: SiLU with the rotation outside, compiled as the plain design; otherwise a ROLA_PHI_* value
 // with the rotation order at run time), and branch-free maps. One uniform branch per phase instead of
 // a switch and a divergent erff / tanhf per value lets the values of a tile overlap: readout at
-// r 128 with GELU inside, 39689 tokens x 12 heads: 383 us with the per-value form.
+// r 128 with GELU inside, 39689 tokens x 12 heads: 383 us with the per-value form, 132 now (with the longer chunks).
 constexpr int kPaper = -1;
 
 // GELU x Phi(x) from erfc(z) = t P(t) exp(-z^2), z = |x| / sqrt 2, t = 1 / (1 + 0.4 z): P is a degree-8
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(256) void summary_f32_kernel(
 // to a workgroup: with its fragments in LDS one workgroup fills a CU, and two waves per SIMD overlap
 // one's products with the other's features.
 // Against 256-token workgroups that waited for each pair of tiles (32760 tokens x 40 heads, with the
-// combine): r 64 294 us; r 128 with GELU inside, 39689 tokens x 12 heads: 383 us.
+// combine): r 64 294 -> 228-257 us; r 128 with GELU inside, 39689 tokens x 12 heads: 383 -> 132 us.
 constexpr int kReadoutWorkgroups = 1024;
 template <int JT>
 constexpr int readout_waves() { return JT == 4 ? 8 : 4; }

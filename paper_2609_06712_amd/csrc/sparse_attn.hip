@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void pair_rank_kernel(int nb, int keep, int nc
   }
 }
 // Query blocks per overlap workgroup: a quarter chunk where whole chunks are fewer than two workgroups
-// per CU (it builds 80 bitmap rows for 16 blocks instead of 128 for 64; 12 heads of 512 blocks 26 -> 12
+// per CU (it builds 80 bitmap rows for 16 blocks instead of 128 for 64; 12 heads of 512 blocks 26 -> 14
 // us, 24 of 132 17 -> 9; with 40 heads of 1182 whole chunks fill the chip).
 inline int pair_rank_rows(int heads, int nchunks) { return heads * nchunks < 2 * kCus ? 16 : 64; }
 
@@ -123,7 +123,7 @@ inline int pair_rank_rows(int heads, int nchunks) { return heads * nchunks < 2 *
 // find-first-set. Bound by that chain of scalar work, so a chunk whose candidates all exist (every one
 // but the last two) takes steps with nothing else on it: one branch (is the block taken?), the lane's
 // candidate bit prepared off the chain, and the comparison's mask used as it comes. 512 blocks: 43 us
-// with bounds checks and a rebuilt mask in every step, 20 now. The table is gathered in LDS and written
+// with bounds checks and a rebuilt mask in every step, 31 now. The table is gathered in LDS and written
 // out at the end, so no store shares the memory counter with the chunk loads.
 constexpr int kMaxPairGroups = 2032;  // ceil(4064 / 2): the most query blocks pairing serves
 __global__ __launch_bounds__(64) void pair_greedy_kernel(int nb, int ngroups, int nchunks,
@@ -347,8 +347,8 @@ __global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int 
 
 // The whole plan of a head of at most 64 blocks in one workgroup: pair_rank_kernel, pair_greedy_kernel and
 // group_union_kernel's results (the same pairs and lists), from one 64-bit word per query block, the
-// walk positions of its key blocks. Small calls are bound by launches and their latencies: 390 tokens x
-// 12 heads, three launches of 3-4 us each, 4 us in one. Workgroups past `heads` make the C^T fragments.
+// walk positions of its key blocks. Small calls are bound by launches and their latencies: with
+// the pooling in one launch too, a layer of 390 tokens x 12 heads 113 -> 97 us. Workgroups past `heads` make the C^T fragments.
 constexpr int kSmallPlan = 64;
 __global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int ngroups, int heads,
                                                          int stride, const int32_t* __restrict__ idx,
