@@ -1131,9 +1131,27 @@ void sparse_attn_kernel(const AttnArgs args) {
 }
 
 
+// Compute units of the current device (of device 0 if that cannot be told), cached per device.
+constexpr int kMaxDevices = 64;
+int device_cus() {
+  static std::atomic<int> cache[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) dev = -1;
+  if (dev >= 0) {
+    const int c = cache[dev].load(std::memory_order_relaxed);
+    if (c > 0) return c;
+  }
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess)
+    cus = 0;
+  (void)hipGetLastError();
+  cus = std::max(1, cus);
+  if (dev >= 0) cache[dev].store(cus, std::memory_order_relaxed);
+  return cus;
+}
+
 // Workgroups of `kernel` (threads each) that the current device holds at once, cached per device
 // in `cache` (one per kernel: every variant has the same function type).
-constexpr int kMaxDevices = 64;
 template <typename Kernel>
 int resident_workgroups(Kernel kernel, int threads, std::atomic<int> (&cache)[kMaxDevices]) {
   int dev = 0;
@@ -1142,13 +1160,11 @@ int resident_workgroups(Kernel kernel, int threads, std::atomic<int> (&cache)[kM
     const int c = cache[dev].load(std::memory_order_relaxed);
     if (c > 0) return c;
   }
-  int cus = 0, per_cu = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess)
-    cus = 0;
+  int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess)
     per_cu = 0;
   (void)hipGetLastError();
-  const int n = std::max(1, cus) * std::max(1, per_cu);
+  const int n = device_cus() * std::max(1, per_cu);
   if (dev >= 0) cache[dev].store(n, std::memory_order_relaxed);
   return n;
 }
@@ -1269,26 +1285,14 @@ SparseWs sparse_ws_layout(const Shape& s, int block, int keep) {
   return {kQueueBytes, align256(heads * ngroups * sizeof(int32_t)), lists};
 }
 
-// Period of walk_start for the merged lists of the 64-token path: resident workgroups per XCD of
-// the work-queue variant that will walk them (the table and epilogue variant launch_bf16_rj picks
-// for lists of stride - 1 entries and rank r; the dQ mode has no epilogue).
-template <int NBUF, bool DQ>
-int walk_period(int stride, int r) {
-  constexpr int G = kB64Group;
-  int n;
-  if constexpr (DQ) {
-    n = stride - 1 <= kTable ? queue_resident<64, G, NBUF, kTable, 0, true>()
-                             : queue_resident<64, G, NBUF, 0, 0, true>();
-  } else if (stride - 1 <= kTable) {
-    n = r == 0    ? queue_resident<64, G, NBUF, kTable, 0, false>()
-        : r <= 32 ? queue_resident<64, G, NBUF, kTable, 1, false>()
-                  : queue_resident<64, G, NBUF, kTable, 2, false>();
-  } else {
-    n = r == 0    ? queue_resident<64, G, NBUF, 0, 0, false>()
-        : r <= 32 ? queue_resident<64, G, NBUF, 0, 1, false>()
-                  : queue_resident<64, G, NBUF, 0, 2, false>();
-  }
-  return n / kNumXcd;
+// Period of walk_start for the merged lists of the 64-token path: about the workgroups that an XCD holds
+// of the variant that walks them, three per CU, two with the r 64 epilogue and in the dQ mode. Fixed
+// numbers, not the occupancy of the compiled kernel: the phase sets where each list starts, hence the first
+// reference max and the rounding of the probabilities, and the output must not move by 1e-3 when a
+// kernel's registers do. (The r 64 variant now reaches three per CU; phases for 96 workgroups instead of 64
+// would save it 2 % at 40 heads of 75600 tokens, 13.01 -> 12.73 ms, and nothing up to 32760.)
+int walk_period(bool dq, int r) {
+  return device_cus() / kNumXcd * (dq || r > 32 ? 2 : 3);
 }
 
 // Groups of the 64-token path in the workspace: pairs matched by overlap (or adjacent), their
@@ -1320,7 +1324,7 @@ hipError_t prepare_groups(const Shape& s, int keep, const int32_t* idx, void* ws
   const int nb = num_blocks(s.N, 64);
   const int ngroups = (nb + G - 1) / G, heads = s.B * s.H;
   gr = groups_in(s, keep, ws);
-  const int period = walk_period<DQ ? 3 : kB64Nbuf, DQ>(gr.stride, r);
+  const int period = walk_period(DQ, r);
   const CfragJob job = cf ? *cf : CfragJob{};
   if (gr.pairs && nb <= kSmallPlan) {
     hipLaunchKernelGGL(small_plan_kernel, dim3(heads + cfrag_blocks(job)), dim3(256), 0, st, nb, keep,

@@ -402,6 +402,44 @@ def test_overlap_pairing_sizes(N, H, s):
         assert np.array_equal(table[h].astype(np.int64), _greedy_pairs(lists[h], nb)), h
 
 
+@pytest.mark.parametrize("N,H,s,r", [(64 * 128, 24, 0.9, 16), (64 * 128, 24, 0.9, 32), (64 * 128, 24, 0.9, 64),
+                                     (64 * 37, 12, 0.7, 64)])
+def test_merged_lists_start_phase(N, H, s, r):
+    """Each merged list of a plan is the union of its pair's lists in walk order, rotated to the start phase
+    of the group's place in its XCD's range: the period is three workgroups per CU up to rank 32, two at
+    rank 64, whatever the kernel's occupancy (results depend on where a list starts)."""
+    grid = (1, 1, N)
+    like = torch.empty((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
+    prob = R.problem_of(like, grid)
+    nb, xcds = O.num_blocks(N, 64), 8
+    keep, ng = O.keep_blocks(nb, s), (nb + 1) // 2
+    rng = np.random.default_rng(r)
+    lists = np.stack([np.stack([np.sort(rng.permutation(nb)[:keep]) for _ in range(nb)]) for _ in range(H)])
+    idx = torch.from_numpy(lists[None].astype(np.int32)).cuda()
+    ws = torch.empty(R.sparse_combine_workspace_bytes(prob, 64, s, r), dtype=torch.uint8, device="cuda")
+    R.rola_sparse_plan(idx, like, grid, 64, s, r, ws)
+    torch.cuda.synchronize()
+    q, table = xcds * 256, -(-4 * H * ng // 256) * 256
+    pairs = ws[q: q + 4 * H * ng].view(torch.int32).cpu().numpy().reshape(H, ng)
+    stride = 2 * keep + 1
+    merged = ws[q + table: q + table + 4 * H * ng * stride].view(torch.int32).cpu().numpy().reshape(H, ng, stride)
+    kb = max(1, (nb - 1).bit_length())
+    brev = lambda J: int(format(J, f"0{kb}b")[::-1], 2)
+    period = torch.cuda.get_device_properties(0).multi_processor_count // xcds * (3 if r <= 32 else 2)
+    total = H * ng
+    per, rem = divmod(total, xcds)
+    for h in range(H):
+        for g in range(ng):
+            L = h * ng + g
+            i = L % (per + 1) if L < rem * (per + 1) else (L - rem * (per + 1)) % per
+            a, b = int(pairs[h, g]) & 0xFFFF, int(pairs[h, g]) >> 16
+            sa, sb = set(lists[h, a]), set(lists[h, b]) if b < nb else set()
+            want = [int(J) | (int(J in sa) | int(J in sb) << 1) << 16 for J in sorted(sa | sb, key=brev)]
+            e0 = i % period * len(want) // period
+            assert merged[h, g, 0] == len(want)
+            assert merged[h, g, 1:1 + len(want)].tolist() == want[e0:] + want[:e0], (h, g)
+
+
 def test_work_queue_full_size():
     """At the 14B 720p size the attention kernel runs as resident workgroups that claim (head,
     pair) groups from per-XCD counters: 23640 groups, far more than the chip holds at once, so
