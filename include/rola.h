@@ -278,7 +278,8 @@ rola_status rola_sparse_attn_backward(const rola_problem* p, const void* Qr, con
  * in dQn, dKn and dV (fp32 [B, H, N, d_h], read and written): dQn += R(p)^T dQ^r, dKn += R(p)^T dK^r, dV +=
  * dV of the sparse branch, i.e. rola_sparse_attn_backward followed by three
  * rola_rope_backward_accumulate calls, without dQ^r, dK^r and the branch's dV in memory. Tables and
- * rope_ld as in rola_rope_apply; N rope_ld < 2^31 (ROLA_ERR_UNSUPPORTED beyond). */
+ * rope_ld as in rola_rope_apply; N rope_ld < 2^31 (ROLA_ERR_UNSUPPORTED beyond). dQn, dKn and dV must not
+ * overlap each other, an input or the workspace (ROLA_ERR_INVALID_ARGUMENT). */
 rola_status rola_sparse_attn_backward_accumulate(
     const rola_problem* p, const void* Qr, const void* Kr, const void* V, int32_t block,
     double sparsity, const int32_t* blk_idx, float softmax_scale, const void* Os, const float* lse,

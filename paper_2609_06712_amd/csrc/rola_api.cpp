@@ -503,6 +503,23 @@ static rola_status sparse_backward(const rola_problem* p, const void* Qr, const 
   const size_t need = rola::sparse_backward_workspace_bytes(s, block, keep);
   if (ws_bytes < need)
     return fail(ROLA_ERR_WORKSPACE, "%s: workspace %zu bytes, need %zu", fn, ws_bytes, need);
+  if (acc) {  // read and written in place by two kernels, while other workgroups read the inputs
+    const size_t rows = (size_t)s.B * s.H * s.N, n = rows * s.d * sizeof(float);
+    const size_t tab = ((size_t)(s.N - 1) * acc->ld + s.d / 2) * sizeof(float);
+    const size_t list = (size_t)s.B * s.H * rola::num_blocks(s.N, block) * keep * sizeof(int32_t);
+    const struct {
+      const void* p;
+      size_t bytes;
+      const char* name;
+    } others[] = {{dQ, n, "dQn"}, {dK, n, "dKn"}, {dV, n, "dV"}, {Qr, n / 2, "Qr"}, {Kr, n / 2, "Kr"},
+                  {V, n / 2, "V"}, {Os, n / 2, "Os"}, {dOs, n / 2, "dOs"},
+                  {lse, rows * sizeof(float), "lse"}, {blk_idx, list, "blk_idx"},
+                  {acc->cos_tab, tab, "cos_tab"}, {acc->sin_tab, tab, "sin_tab"}, {ws, need, "ws"}};
+    for (int i = 0; i < 3; ++i)
+      for (size_t j = i + 1; j < sizeof(others) / sizeof(others[0]); ++j)
+        if (overlap(others[i].p, n, others[j].p, others[j].bytes))
+          return fail(ROLA_ERR_INVALID_ARGUMENT, "%s: %s overlaps %s", fn, others[i].name, others[j].name);
+  }
   return hip_status(rola::launch_sparse_backward(s, Qr, Kr, V, block, keep, blk_idx, softmax_scale,
                                                  Os, lse, dOs, acc ? *acc : rola::GradTables{}, dQ, dK,
                                                  dV, ws, stream),

@@ -74,6 +74,19 @@ int main(void) {
   EXPECT(ROLA_ERR_WORKSPACE, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(12), (float*)F(13), 64, (float*)F(8), (float*)F(9), (float*)F(10), F(11), 16, 0));
   EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(12), (float*)F(13), 60, (float*)F(8), (float*)F(9), (float*)F(10), F(11), (size_t)1 << 40, 0));
   EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), nullptr, (float*)F(13), 64, (float*)F(8), (float*)F(9), (float*)F(10), F(11), (size_t)1 << 40, 0));
+  // the accumulated gradients may overlap neither each other nor what the kernels read beside them
+  // (2 heads of 75600 x 128: 77,414,400 bytes each in fp32)
+#define ACC(q, k, v) rola_sparse_attn_backward_accumulate(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), (float*)F(6), F(7), (float*)F(12), (float*)F(13), 64, (float*)(q), (float*)(k), (float*)(v), F(11), BIG, 0)
+  EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(8), F(8), F(10)));
+  EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(8), F(9), F(9)));
+  EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(8), F(9), (char*)F(8) + 77414400 - 16));
+  for (int k = 1; k <= 13; ++k) {
+    if (k >= 8 && k <= 10) continue;
+    EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(k), F(9), F(10)));
+    EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(8), F(k), F(10)));
+    EXPECT(ROLA_ERR_INVALID_ARGUMENT, ACC(F(8), F(9), (char*)F(k) - 16));
+  }
+#undef ACC
 
   // attention + readout + combine
   EXPECT(ROLA_ERR_INVALID_ARGUMENT, rola_sparse_attn_combine(&ok, F(1), F(2), F(3), 64, 0.9, (int32_t*)F(4), 0.1f, F(5), F(6), 31, T, T, 64, (float*)F(7), 1e-6f, (float*)F(8), 1e-6f, NULL, F(9), F(10), BIG, 0));
