@@ -99,6 +99,13 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(
     l = l * alpha + sum;  // this lane's quarter of the keys
 #pragma unroll
     for (int w = 0; w < W; ++w) acc[w] *= alpha;
+    if (k0 + kQ > N) {  // ragged tail: V zero past the last key (P is zero there, and 0 x inf is not)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int s = 0; s < W / 4; ++s)
+          vv[i][s] = k0 + 4 * g + i < N ? vv[i][s] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll

@@ -508,11 +508,15 @@ __global__ __launch_bounds__(256) void summary_f32_kernel(
     for (int t = 0; t < CT; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float z = 0.f;  // thread: coordinate tid % 128, half the tokens of each step
   for (int b0 = t0; b0 < t1; b0 += TT) {
-    // tokens past the chunk re-read its last one and get zero features
+    // tokens past the chunk re-read its last one and get zero features and zero V (0 x inf is not 0)
     vvec v[TT / 4];
 #pragma unroll
     for (int s = 0; s < TT / 4; ++s)
       v[s] = *reinterpret_cast<const vvec*>(Vh + (long)min(b0 + 4 * s + g, t1 - 1) * D);
+    if (b0 + TT > t1) {
+#pragma unroll
+      for (int s = 0; s < TT / 4; ++s) v[s] = b0 + 4 * s + g < t1 ? v[s] : vvec(0.f);
+    }
     const int tok = b0 + 16 * wave + lr, tk = min(tok, t1 - 1);
     float4 x[D / 16];
 #pragma unroll
@@ -775,7 +779,7 @@ __global__ __launch_bounds__(64) void readout_f32_kernel(
 #pragma unroll
   for (int w = 0; w < W; ++w) u[w] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int jt = 0; jt < JT; ++jt) {
-    float4 cv[2][4][W / 4];  // C rows of the lane's pairs; pairs past r/2 meet zero features
+    float4 cv[2][4][W / 4];  // C rows of the lane's pairs, zero past r/2
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float* cr = Ch + (long)(2 * min(16 * jt + 4 * g + i, half - 1)) * D;
@@ -784,6 +788,14 @@ __global__ __launch_bounds__(64) void readout_f32_kernel(
         cv[0][i][s] = *reinterpret_cast<const float4*>(cr + 4 * s);
         cv[1][i][s] = *reinterpret_cast<const float4*>(cr + D + 4 * s);
       }
+    }
+    if (16 * jt + 16 > half) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int s = 0; s < W / 4; ++s)
+          if (16 * jt + 4 * g + i >= half)
+            cv[0][i][s] = cv[1][i][s] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     float f[2][4];
     features_f32<D>(Pq + (long)h * r * D, r, jt, x, cos_tab + (long)tk * ld, sin_tab + (long)tk * ld,

@@ -104,6 +104,31 @@ def test_f32_every_element(d, grid, H, B, block, s, r):
             _report(f"f32 d{d} {grid} block{block} r{r} b{b} h{h}", **res)
 
 
+@pytest.mark.parametrize("d,block,N,r", [(64, 32, 71, 16), (128, 64, 130, 34), (128, 128, 57, 128)])
+def test_f32_infinite_entries(d, block, N, r):
+    """Rows past the last token and pairs past r / 2 add nothing, also where the last row or pair holds
+    infinities: O^s and C get the infinity of its channel (and no NaN, as 0 x inf would give), and the
+    readout of a C that is infinite in one channel is zero in the others."""
+    grid, ch, split = (1, 1, N), 5, (28, 18, 18) if d == 64 else (44, 42, 42)
+    gen = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn((1, 2, N, d), generator=gen).cuda() for _ in range(3))
+    P = (torch.randn((2, r, d), generator=gen) / d ** 0.5).cuda()
+    v[..., N - 1, ch], v[..., N - 1, ch + 1] = math.inf, -math.inf
+    finite = torch.ones(d, dtype=torch.bool)
+    finite[ch:ch + 2] = False
+    cos, sin = R.rola_rope_tables(R.problem_of(q, grid), split)
+    o = R.rola_dense_attn(q, k, v, grid, block).cpu()
+    assert bool((o[..., ch] == math.inf).all()) and bool((o[..., ch + 1] == -math.inf).all())
+    assert bool(torch.isfinite(o[..., finite]).all())
+    C, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
+    assert bool(torch.isinf(C[..., ch:ch + 2].cpu()).all()) and bool(torch.isfinite(C.cpu()[..., finite]).all())
+    C = torch.randn((1, 2, r, d), generator=gen)
+    C[..., r - 1, ch] = math.inf
+    u = R.rola_lowrank_readout(q, P, r, cos, sin, C.cuda(), grid).cpu()
+    finite[ch + 1] = True
+    assert bool((u[..., finite] == 0).all())
+
+
 CASES = [
     # (name, grid, H, B, block, sparsity, r)
     ("ragged r32", (3, 10, 13), 2, 1, 64, 0.5, 32),
