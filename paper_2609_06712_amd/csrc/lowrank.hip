@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   const int t0 = chunk * chunk_len, t1 = min(N, t0 + chunk_len);
   // V tile DMA: lane l of 1-KB slot q (8 slots per wave) fills row 4q + l/16, position l%16 with
   // source chunk position ^ 2(row%8). Rows past the chunk re-read its last one, as do K^n rows and
-  // table entries: the features of those tokens are zeroed.
+  // table entries: the features of those tokens are zeroed, and their V rows once they are in LDS.
   const int row0 = 32 * wave + lane / 16;
   uint32_t dvp[2];  // slot i's row is row0 + 4i; its swizzle depends only on i's parity
 #pragma unroll
@@ -334,6 +334,14 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
     load_tables(base + 2 * TOK, T);
     asm volatile("" : "+v"(last) : : "memory");
     __builtin_amdgcn_sched_barrier(0);
+    if (base + TOK > t1) {  // (uniform) V past the chunk: zero as well, 0 x inf is not 0
+      int ln;  // (the lane index made here, and one register of zeros: what is more spills)
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+      float* rows = reinterpret_cast<float*>(lds + buf * TILE + wave * 8192) + ln;
+#pragma unroll 1
+      for (int row = max(0, t1 - base - 32 * wave); row < 32; ++row) rows[row * (D / 2)] = 0.f;
+      asm volatile("" : : : "memory");
+    }
     const char* Vs = lds + buf * TILE;
     typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 #pragma unroll
@@ -358,7 +366,7 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   load_tables(t0 + TOK, tb);
   __builtin_amdgcn_sched_barrier(0);
   // two steps per turn without an exit between them (it costs 60 to 130 spilled registers): the second
-  // of an odd count adds zeros
+  // of an odd count adds zeros to zeros
   for (int base = t0; base < t1; base += 2 * TOK) {
     step(base, 0, ra, rb, ta);
     step(base + TOK, 1, rb, ra, tb);

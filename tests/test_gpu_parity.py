@@ -129,6 +129,24 @@ def test_f32_infinite_entries(d, block, N, r):
     assert bool((u[..., finite] == 0).all())
 
 
+@pytest.mark.parametrize("N", [1, 128, 130, 384, 500])
+@pytest.mark.parametrize("r", [16, 64, 128])
+def test_summary_infinite_entries(N, r):
+    """The bf16 summary takes two steps of 128 tokens per turn: what lies past the last token adds
+    nothing to C, also where the last row of V holds an infinity."""
+    grid, ch = (1, 1, N), 5
+    gen = torch.Generator().manual_seed(N + r)
+    k, v = (torch.randn((1, 2, N, 128), generator=gen).to(torch.bfloat16).cuda() for _ in range(2))
+    P = (torch.randn((2, r, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16).cuda()
+    cos, sin = R.rola_rope_tables(R.problem_of(k, grid), (44, 42, 42))
+    want, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
+    v[..., N - 1, ch] = math.inf
+    C, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
+    others = torch.arange(128) != ch
+    assert bool(torch.isinf(C[..., ch].cpu()).all())
+    assert torch.equal(C.cpu()[..., others], want.cpu()[..., others])
+
+
 CASES = [
     # (name, grid, H, B, block, sparsity, r)
     ("ragged r32", (3, 10, 13), 2, 1, 64, 0.5, 32),
