@@ -141,7 +141,8 @@ def problem_of(x: torch.Tensor, grid) -> Problem:
 
 
 # The entry points' own descriptors and sizes are pure functions of a few numbers that the same program
-# passes on every call: kept by value (never by tensor), bounded.
+# passes on every call: kept by value, bounded, and only for plain ints and floats (anything else that
+# ctypes takes, such as a 0-d tensor, hashes by identity or equals an int that it is not).
 @functools.lru_cache(maxsize=1024)
 def _cached_problem(B, H, N, d_h, T, Hs, Ws, code) -> Problem:
     return Problem(B, H, N, d_h, T, Hs, Ws, code)
@@ -150,11 +151,16 @@ def _cached_problem(B, H, N, d_h, T, Hs, Ws, code) -> Problem:
 _DTYPE_CODES = {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16}
 
 
-def _prob_of(x: torch.Tensor, grid) -> Problem:
-    """problem_of for a call's own use (shared: not to be written)."""
-    B, H, N, d = x.shape
+def _prob(B, H, N, d_h, grid, dtype) -> Problem:
+    """problem() for a call's own use (shared: not to be written)."""
     T, Hs, Ws = grid
-    return _cached_problem(B, H, N, d, T, Hs, Ws, _DTYPE_CODES[x.dtype])
+    make = (_cached_problem if type(H) is type(d_h) is type(T) is type(Hs) is type(Ws) is int else Problem)
+    return make(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[dtype])
+
+
+def _prob_of(x: torch.Tensor, grid) -> Problem:
+    B, H, N, d = x.shape
+    return _prob(B, H, N, d, grid, x.dtype)
 
 
 # ---- argument checks ------------------------------------------------------------------------------
@@ -259,12 +265,24 @@ class _Args:
 # ---- host helpers ---------------------------------------------------------------------------------
 
 @functools.lru_cache(maxsize=1024)
+def _cached_num_blocks(N, block):
+    return LIB.rola_num_blocks(N, block)
+
+
 def num_blocks(N: int, block: int) -> int:
+    if type(N) is type(block) is int:
+        return _cached_num_blocks(N, block)
     return LIB.rola_num_blocks(N, block)
 
 
 @functools.lru_cache(maxsize=1024)
+def _cached_keep_blocks(n_blocks, sparsity):
+    return LIB.rola_keep_blocks(n_blocks, sparsity)
+
+
 def keep_blocks(n_blocks: int, sparsity: float) -> int:
+    if type(n_blocks) is int and type(sparsity) is float:
+        return _cached_keep_blocks(n_blocks, sparsity)
     return LIB.rola_keep_blocks(n_blocks, sparsity)
 
 
@@ -593,8 +611,7 @@ def rola_gate_logits(X, Wg, bg, grid, H=1, d_h=128, out=None, stream=None):
     """Gate logits X W_g + b_g of every token: X [B, N, d_model], W_g [d_model] -> fp32 [B, N]."""
     a = _Args()
     B, N, dm = _hidden(a, X, Wg)
-    T, Hs, Ws = grid
-    prob = _cached_problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[X.dtype])
+    prob = _prob(B, H, N, d_h, grid, X.dtype)
     if out is None:
         out = torch.empty((B, N), dtype=torch.float32, device=X.device)
     a.tensor(out, "out", (B, N), torch.float32)
@@ -822,8 +839,7 @@ def rola_gate_logits_backward(X, Wg, dlogits, grid, H=1, d_h=128, want_dX=True, 
     a = _Args()
     B, N, dm = _hidden(a, X, Wg)
     a.tensor(dlogits, "dlogits", (B, N), torch.float32)
-    T, Hs, Ws = grid
-    prob = _cached_problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[X.dtype])
+    prob = _prob(B, H, N, d_h, grid, X.dtype)
     f32 = dict(dtype=torch.float32, device=X.device)
     dX = torch.empty(X.shape, **f32) if want_dX else None
     dWg, dbg = torch.empty(dm, **f32), torch.empty(4, **f32)

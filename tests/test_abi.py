@@ -46,6 +46,24 @@ def test_keep_blocks_matches_oracle():
     assert R.keep_blocks(10, 1.0) == -1 and R.keep_blocks(0, 0.5) == -1
 
 
+def test_cached_sizes_are_kept_by_value():
+    """Block counts and descriptors are kept between calls for plain numbers only: a 0-d tensor that is
+    changed in place gives its new value, and a float stays refused where the equal int was seen."""
+    n, t = torch.tensor(100), torch.tensor(4)
+    like = torch.empty((1, 2, 100, 128), dtype=torch.bfloat16, device="meta")
+    assert R.num_blocks(n, 64) == 2 and R.keep_blocks(n, 0.9) == 10
+    assert R._prob_of(like, (t, 5, 5)).T == 4
+    n += 100
+    t += 1
+    assert R.num_blocks(n, 64) == 4 and R.keep_blocks(n, 0.9) == 20
+    assert R._prob_of(like, (t, 5, 5)).T == 5
+    R.num_blocks(100, 64), R.keep_blocks(100, 0.9), R._prob_of(like, (4, 5, 5))
+    for call in (lambda: R.num_blocks(100.0, 64), lambda: R.keep_blocks(100.0, 0.9),
+                 lambda: R._prob_of(like, (4.0, 5, 5))):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            call()
+
+
 def test_workspace_helpers():
     p = R.problem(1, 40, 75600, 128, (21, 45, 80), "bf16")
     nb = 1182
