@@ -119,12 +119,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The raw handle of a device's current stream; a torch.cuda.Stream object per call costs 3 us of a small
+# call's 15. Not part of torch's public interface: absent, the stream object gives it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    # the raw handle of the current stream: a torch.cuda.Stream object per call costs 3 us of a small
-    # call's 15
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def problem(B, H, N, d_h, grid, dtype) -> Problem:

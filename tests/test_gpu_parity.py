@@ -645,6 +645,17 @@ def test_combine_in_place_matches_out_of_place():
     assert torch.equal(os_copy2, res["out_fused"])
 
 
+def test_current_stream_handle(monkeypatch):
+    """The handle passed to the library is the current stream's, also without torch's raw accessor."""
+    side = torch.cuda.Stream()
+    for raw in (R._raw_stream, None):
+        monkeypatch.setattr(R, "_raw_stream", raw)
+        assert R._stream(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert R._stream(None) == side.cuda_stream
+        assert R._stream(side) == side.cuda_stream
+
+
 def test_plan_then_planned_attention_on_two_streams():
     """rola_sparse_plan + rola_sparse_attn_combine_planned, with the low-rank summary on a second
     stream between them (the benchmarked layer's schedule, on the 1.3B 480p layer), give bitwise the
