@@ -120,11 +120,14 @@ inline int pair_rank_rows(int heads, int nchunks) { return heads * nchunks < 2 *
 // exactly ceil(nb / 2) groups. pairs[head][g] = I | J << 16 (J = nb: no partner), in the order the
 // groups are formed. Lane k holds the k-th choices of a chunk's 64 blocks (64 bytes in registers,
 // the next chunk loading meanwhile); a step is a mask of the lanes whose choice is still free and a
-// find-first-set. Bound by that chain of scalar work, so a chunk whose candidates all exist (every one
-// but the last two) takes steps with nothing else on it: one branch (is the block taken?), the lane's
-// candidate bit prepared off the chain, and the comparison's mask used as it comes. 512 blocks: 43 us
-// with bounds checks and a rebuilt mask in every step, 31 now. The table is gathered in LDS and written
-// out at the end, so no store shares the memory counter with the chunk loads.
+// find-first-set. Bound by that chain of scalar work, so a step has nothing else on it: one branch (is
+// the block taken?), the lane's candidate bit prepared off the chain, and the comparison's mask used as it
+// comes. Chunks with candidates past the last block take the same steps: those are ranked after all
+// others, so one is chosen only where no other is free, and then stands for "no partner"; rows past the
+// last block count as taken. 512 blocks: 43 us with bounds checks and a rebuilt mask in every step, 31
+// now. 132 blocks, two of whose three chunks have such candidates: with checked steps there the plan
+// of 12 heads took 26.6 us, 20.1 now. The table is gathered in LDS and written out at the end, so no store
+// shares the memory counter with the chunk loads.
 constexpr int kMaxPairGroups = 2032;  // ceil(4064 / 2): the most query blocks pairing serves
 __global__ __launch_bounds__(64) void pair_greedy_kernel(int nb, int ngroups, int nchunks,
                                                          const uint8_t* __restrict__ pref,
@@ -141,53 +144,25 @@ __global__ __launch_bounds__(64) void pair_greedy_kernel(int nb, int ngroups, in
   };
   fetch(0, cur);
   uint64_t taken = 0;  // bit k: block I+k already has a partner
-  int g = 0;
+  int g = 0;           // at most one block stays alone, so ceil(nb / 2) = ngroups entries
   for (int c = 0; c < nchunks; ++c) {
     fetch(min(c + 1, nchunks - 1), nxt);  // unconditional: a fixed count of loads in flight
     const uint32_t w[16] = {cur[0].x, cur[0].y, cur[0].z, cur[0].w, cur[1].x, cur[1].y,
                             cur[1].z, cur[1].w, cur[2].x, cur[2].y, cur[2].z, cur[2].w,
                             cur[3].x, cur[3].y, cur[3].z, cur[3].w};
     const int I0 = c * kPairWindow;
-    // lane's choice for row r, and the bit of `taken` it stands on (d = 63: none, block I+64 is free)
-    auto choice = [&](int r) { return (w[r / 4] >> (8 * (r % 4))) & 0xFFu; };
-    auto free_lanes = [&](uint32_t d, uint64_t t) {
-      return __builtin_amdgcn_uicmpl((2ull << d) & t, 0ull, 32 /* == */);
-    };
-    if (I0 + 2 * kPairWindow <= nb) {
+    if (nb - I0 < kPairWindow) taken |= ~0ull << (nb - I0);
 #pragma unroll
-      for (int r = 0; r < kPairWindow; ++r) {
-        const uint64_t t = taken;
-        taken >>= 1;
-        if (!(t & 1)) {  // (one-sided: an else branch costs the step a second jump)
-          const uint32_t d = choice(r);
-          const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(free_lanes(d, t)));
-          taken |= 1ull << dd;
-          tbl[g++] = (I0 + r) | ((I0 + r + 1 + dd) << 16);  // every lane stores the same value
-        }
-      }
-    } else {
-#pragma unroll 1
-      for (int r = 0; r < kPairWindow && I0 + r < nb; ++r) {
-        const int I = I0 + r;
-        const uint64_t t = taken;
-        taken >>= 1;
-        if (!(t & 1)) {
-          uint32_t d = 0;  // choice(r), r not a constant here
-#pragma unroll
-          for (int q = 0; q < 16; ++q) d = r / 4 == q ? w[q] : d;
-          d = (d >> (8 * (r % 4))) & 0xFFu;
-          // candidates past the last block are ranked after all others: the first nb - 1 - I lanes
-          const int valid = min(64, nb - 1 - I);
-          const uint64_t m = valid > 0 ? free_lanes(d, t) & (~0ull >> (64 - valid)) : 0ull;
-          int partner = nb;
-          if (m) {
-            const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(m));
-            partner = I + 1 + dd;
-            taken |= 1ull << dd;
-          }
-          if (g < ngroups) tbl[g] = I | (partner << 16);
-          ++g;
-        }
+    for (int r = 0; r < kPairWindow; ++r) {
+      const uint64_t t = taken;
+      taken >>= 1;
+      if (!(t & 1)) {  // (one-sided: an else branch costs the step a second jump)
+        // lane's choice for row r; the bit of `taken` it stands on (d = 63: none, block I+64 is free)
+        const uint32_t d = (w[r / 4] >> (8 * (r % 4))) & 0xFFu;
+        const uint64_t free = __builtin_amdgcn_uicmpl((2ull << d) & t, 0ull, 32 /* == */);
+        const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(free));
+        taken |= 1ull << dd;
+        tbl[g++] = (I0 + r) | (min(I0 + r + 1 + dd, nb) << 16);  // every lane stores the same value
       }
     }
 #pragma unroll
@@ -388,7 +363,7 @@ __global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int n
     if (lane < valid) pref[rank * kPairWindow + i] = (uint8_t)lane;
   }
   __syncthreads();
-  if (wave == 0) {  // the greedy matching (pair_greedy_kernel's tail form)
+  if (wave == 0) {  // the greedy matching (pair_greedy_kernel's)
     uint64_t taken = 0;
     int g = 0;
     for (int r = 0; r < nb; ++r) {

@@ -422,11 +422,12 @@ def test_overlap_pairing(lists_kind, s):
 
 @pytest.mark.parametrize("N,H,s", [(20450, 2, 0.9), (8191, 3, 0.95), (64 * 128, 1, 0.5), (8256, 171, 0.9),
                                    (190, 2, 0.5), (64, 2, 0.0), (4033, 5, 0.7), (4096, 2, 0.9),
-                                   (4097, 2, 0.9), (1000, 9, 0.0)])
+                                   (4097, 2, 0.9), (1000, 9, 0.0), (64 * 65, 3, 0.9), (64 * 127, 3, 0.8),
+                                   (64 * 129, 2, 0.0), (64 * 191, 2, 0.97), (64 * 48, 3, 0.6), (64 * 63, 2, 0.0)])
 def test_overlap_pairing_sizes(N, H, s):
     """The pair table of the plan against the greedy matching, on random lists: several chunks of 64
-    query blocks of which all candidates exist (320 blocks), chunk ends on and off the last block (128,
-    130), both splits of the overlap pass (171 heads of three chunks take whole chunks), and the
+    query blocks of which all candidates exist (320 blocks), chunk ends on and off the last block (65, 127 to
+    130, 191), both splits of the overlap pass (171 heads of three chunks take whole chunks), and the
     one-workgroup plan of up to 64 blocks with its edges."""
     grid = (1, 1, N)
     like = torch.empty((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
