@@ -320,10 +320,28 @@ __global__ __launch_bounds__(256) void group_union_kernel(int nb, int keep, int 
   }
 }
 
+// Max over the wave's 64 lanes.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  const int old = 0;  // every lane has a source
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(old, (int)x, 0xB1, 15, 15, false));   // lane ^ 1
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(old, (int)x, 0x4E, 15, 15, false));   // lane ^ 2
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(old, (int)x, 0x141, 15, 15, false));  // mirror 8 lanes
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(old, (int)x, 0x140, 15, 15, false));  // mirror 16 lanes
+  const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = max(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return max(b[0], b[1]);
+}
+
 // The whole plan of a head of at most 64 blocks in one workgroup: pair_rank_kernel, pair_greedy_kernel and
 // group_union_kernel's results (the same pairs and lists), from one 64-bit word per query block, the
 // walk positions of its key blocks. Small calls are bound by launches and their latencies: with
-// the pooling in one launch too, a layer of 390 tokens x 12 heads 113 -> 97 us. Workgroups past `heads` make the C^T fragments.
+// the pooling in one launch too, a layer of 390 tokens x 12 heads 113 -> 97 us.
+// The pairing holds block L's word in lane L and takes, per block without a partner, the largest overlap
+// over the wave: no ranking of all candidates, whose 64 compares per block made this kernel slower than
+// the three from 48 blocks on. Plan of 12 heads, three kernels / ranked / now: 33 blocks 16.1 / 12.3 / 6.2
+// us, 47 19.6 / 18.8 / 7.7, 64 23.4 / 28.7 / 9.8 (past 64 a row no longer fits one word). Workgroups past
+// `heads` make the C^T fragments.
 constexpr int kSmallPlan = 64;
 __global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int ngroups, int heads,
                                                          int stride, const int32_t* __restrict__ idx,
@@ -335,8 +353,7 @@ __global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int n
     cfrag_entry(job, (long)(blockIdx.x - heads) * 256 + threadIdx.x);
     return;
   }
-  __shared__ uint32_t bits[kSmallPlan][2];                // walk positions of each query block's list
-  __shared__ uint8_t pref[kPairWindow * kPairWindow];     // [k][r]: k-th choice of query block r
+  __shared__ uint32_t bits[kSmallPlan][2];  // walk positions of each query block's list
   __shared__ int32_t tbl[kSmallPlan / 2];
   const int kb = walk_bits(nb);
   const long head = blockIdx.x;
@@ -353,41 +370,26 @@ __global__ __launch_bounds__(256) void small_plan_kernel(int nb, int keep, int n
     }
   }
   __syncthreads();
-  auto mask = [&](int i) { return (uint64_t)bits[i][1] << 32 | bits[i][0]; };
-  for (int i = wave; i < nb; i += 4) {  // rank the following blocks by overlap, the nearer first on ties
-    const int valid = nb - 1 - i;       // lane d < valid: candidate i + 1 + d
-    const int c = lane < valid ? __popcll(mask(i) & mask(i + 1 + lane)) : 0;
-    const int key = (c << 6) | (63 - lane);
-    int rank = 0;
-    for (int o = 0; o < valid; ++o) rank += __builtin_amdgcn_readlane(key, o) > key;
-    if (lane < valid) pref[rank * kPairWindow + i] = (uint8_t)lane;
-  }
-  __syncthreads();
-  if (wave == 0) {  // the greedy matching (pair_greedy_kernel's)
-    uint64_t taken = 0;
-    int g = 0;
-    for (int r = 0; r < nb; ++r) {
-      const uint64_t t = taken;
-      taken >>= 1;
-      if (!(t & 1)) {
-        const int valid = nb - 1 - r;
-        const uint32_t d = lane < valid ? pref[lane * kPairWindow + r] : 0u;
-        const uint64_t m = valid > 0 ? __builtin_amdgcn_uicmpl((2ull << d) & t, 0ull, 32) &
-                                           (~0ull >> (64 - valid))
-                                     : 0ull;
-        int partner = nb;
-        if (m) {
-          const int dd = __builtin_amdgcn_readlane((int)d, (int)__builtin_ctzll(m));
-          partner = r + 1 + dd;
-          taken |= 1ull << dd;
-        }
-        if (g < ngroups) tbl[g] = r | (partner << 16);
-        ++g;
+  if (wave == 0) {
+    const uint32_t b0 = bits[lane][0], b1 = bits[lane][1];
+    uint64_t open = nb < 64 ? (1ull << nb) - 1 : ~0ull;  // blocks without a partner
+    for (int g = 0; open; ++g) {  // at most one block stays alone: ngroups turns
+      const int I = (int)__builtin_ctzll(open);
+      open &= open - 1;
+      int partner = nb;
+      if (open) {  // the largest overlap among the open blocks, all after I; the nearest on ties
+        const uint32_t c = __popc(b0 & __builtin_amdgcn_readlane(b0, I)) +
+                           __popc(b1 & __builtin_amdgcn_readlane(b1, I));
+        const uint32_t key = (open >> lane) & 1 ? (c << 6 | (63 - lane)) + 1 : 0u;
+        partner = 63 - (wave_uniform((int)wave_max(key) - 1) & 63);
+        open &= ~(1ull << partner);
       }
+      tbl[g] = I | (partner << 16);  // every lane stores the same value
     }
   }
   __syncthreads();
   if (tid < ngroups) pairs[head * ngroups + tid] = tbl[tid];
+  auto mask = [&](int i) { return (uint64_t)bits[i][1] << 32 | bits[i][0]; };
   for (int g = wave; g < ngroups; g += 4) {  // lane = walk position
     const int I = tbl[g] & 0xFFFF, J = tbl[g] >> 16;
     const uint64_t ma = mask(I), mb = J < nb ? mask(J) : 0ull, u = ma | mb;
