@@ -430,20 +430,20 @@ struct FuseArgs {
   int rot_q;             // the attention's Q is Q^n, rotated in the prologue with these tables
 };
 
-// Two forms, by the registers that three workgroups per CU leave (168):
-//  * r <= 32 (RJ = 1): u of all four channel tiles at once, each load where it is used and guarded per
-//    lane. Other workgroups hide these loads: issued unconditionally up front they make the 14B layer
-//    0.7 % slower, and so does forming u twice as below.
-//  * r = 64 (WIDE): u one channel tile at a time, once for its norm and once for the output (48 more
+// Two forms:
+//  * u of all four channel tiles at once, each load where it is used and guarded per lane. At r <= 32
+//    (RJ = 1) three workgroups per CU have the registers for it (168), and other workgroups hide these
+//    loads: issued unconditionally up front they make the 14B layer 0.7 % slower, and so does forming u
+//    twice as below. At r 64 it takes 188 to 198 VGPRs and leaves two workgroups per CU.
+//  * WIDE (r 64): u one channel tile at a time, once for its norm and once for the output (48 more
 //    MFMAs per wave and group), the loads up front and unconditional, from clamped addresses: invalid
-//    queries are not stored, and features of pairs past r/2 meet zero rows of the C^T fragments. Held
-//    whole, u needs 212 VGPRs and leaves two workgroups per CU (14B layer, r 64: 14.7 ms against
-//    13.3; 480p, 12 heads: 1.26 against 1.14 ms).
-template <int RJ>
+//    queries are not stored, and features of pairs past r/2 meet zero rows of the C^T fragments. Three
+//    workgroups per CU (14B layer: 14.7 ms with two, 13.3 with three; 480p, 12 heads: 1.26 and 1.14 ms),
+//    but 3 to 10 us more for each group: wide_epilogue says where it pays.
+template <int RJ, bool WIDE>
 __device__ __forceinline__ void fuse_epilogue(const FuseArgs& fz, f32x16 (&acc)[4], float l,
                                               bool qvalid, long head, int N, int q, int lane,
                                               bf16* __restrict__ O) {
-  constexpr bool WIDE = RJ > 1;
   constexpr int D = 128;
   // the query index through an empty asm: the epilogue's address arithmetic is not hoisted in front
   // of the main loop, where it held registers across it (and spilled); the per-query offsets are
@@ -620,13 +620,14 @@ struct AttnArgs {
 // the key-block norms give, where that bound is small enough (see the prologue).
 //
 // Three four-wave workgroups fit a CU (LDS, 168 VGPRs). Every such variant reaches that; where the
-// compiler is told, it orders the code for it: the fused layer with 128-token blocks needs the bound (12
+// compiler is told, it orders the code for it (the r 64 epilogue that keeps u whole holds two): the fused layer with 128-token blocks needs the bound (12
 // heads of 32,760, r 32: 909 -> 844 us), dense attention (no list) gains by it (8,400 keys 1308 -> 1293,
 // 32,760 keys 5856 -> 5796), the static walk over lists without an epilogue loses (128-token blocks,
 // 20 heads of 32,175: 1697 with two, 1710 with three).
-template <int BLK, int G, int NBUF, int TAB, int RJ, bool QUEUE, bool DQ = false, bool BOUND = false>
+template <int BLK, int G, int NBUF, int TAB, int RJ, bool WIDE, bool QUEUE, bool DQ = false,
+          bool BOUND = false>
 __global__ __launch_bounds__(G * BLK * 2,
-                             G * BLK == 128 && !DQ && (QUEUE || RJ > 0 || TAB == 0) ? 3 : 2)
+                             G * BLK == 128 && !DQ && (RJ < 2 || WIDE) && (QUEUE || RJ > 0 || TAB == 0) ? 3 : 2)
 void sparse_attn_kernel(const AttnArgs args) {
   static_assert(G == 1 || G == 2 || G == 4, "one, two or four query blocks per workgroup");
   static_assert(NBUF >= 3, "loads of later sub-tiles stay in flight during a step");
@@ -1073,7 +1074,7 @@ void sparse_attn_kernel(const AttnArgs args) {
     if (fz.lse_out && qvalid && hh == 0)  // sum_k exp2(x_k - m) = l: log2 sum exp2 x = m + log2 l
       fz.lse_out[head * (long)N + q] = m + __log2f(l);
     if constexpr (RJ > 0) {
-      fuse_epilogue<RJ>(fz, acc, l, qvalid, head, N, q, lane, O);
+      fuse_epilogue<RJ, WIDE>(fz, acc, l, qvalid, head, N, q, lane, O);
       return;
     }
     if (qvalid) {
@@ -1154,15 +1155,15 @@ struct DqArgs {
 };
 
 // Resident workgroups of the work-queue variant of sparse_attn_kernel (a cache per variant).
-template <int BLK, int G, int NBUF, int TAB, int RJ, bool DQ, bool BOUND = false>
+template <int BLK, int G, int NBUF, int TAB, int RJ, bool WIDE, bool DQ, bool BOUND = false>
 int queue_resident() {
   static std::atomic<int> cache[kMaxDevices];
-  return resident_workgroups(sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, true, DQ, BOUND>, G * BLK * 2,
+  return resident_workgroups(sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, WIDE, true, DQ, BOUND>, G * BLK * 2,
                              cache);
 }
 
 // queue: kNumXcd zeroed counters, or nullptr for the static grid of one workgroup per group.
-template <int BLK, int G, int NBUF, int TAB, int RJ, bool DQ = false, bool BOUND = false>
+template <int BLK, int G, int NBUF, int TAB, int RJ, bool WIDE = false, bool DQ = false, bool BOUND = false>
 hipError_t launch_bf16_tab(const Shape& s, const void* Qr, const void* Kr, const void* V,
                            const int32_t* lists, int list_len, int list_stride,
                            const int32_t* pairs, float scale, void* Os, const FuseArgs& fz,
@@ -1177,11 +1178,11 @@ hipError_t launch_bf16_tab(const Shape& s, const void* Qr, const void* Kr, const
                    (const bf16*)Qr, (const bf16*)Kr, (const bf16*)V, (bf16*)Os, fz, queue,
                    dq.dO, dq.lseD, dq.dQ, scale, fz.rot_q, knorm};
   if (queue) {
-    const int grid = std::min(total, queue_resident<BLK, G, NBUF, TAB, RJ, DQ, BOUND>());
-    hipLaunchKernelGGL((sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, true, DQ, BOUND>), dim3(grid),
+    const int grid = std::min(total, queue_resident<BLK, G, NBUF, TAB, RJ, WIDE, DQ, BOUND>());
+    hipLaunchKernelGGL((sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, WIDE, true, DQ, BOUND>), dim3(grid),
                        dim3(threads), 0, st, a);
   } else {
-    hipLaunchKernelGGL((sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, false, DQ>), dim3(total),
+    hipLaunchKernelGGL((sparse_attn_kernel<BLK, G, NBUF, TAB, RJ, WIDE, false, DQ>), dim3(total),
                        dim3(threads), 0, st, a);
   }
   return hipGetLastError();
@@ -1190,7 +1191,7 @@ hipError_t launch_bf16_tab(const Shape& s, const void* Qr, const void* Kr, const
 // Lists of up to kTable entries go through the LDS table; longer ones through scalar loads.
 constexpr int kTable = 1024;
 // knorm (merged lists with a work queue and a fused epilogue only): the BOUND variant.
-template <int BLK, int G, int NBUF, int RJ>
+template <int BLK, int G, int NBUF, int RJ, bool WIDE = false>
 hipError_t launch_bf16_rj(const Shape& s, const void* Qr, const void* Kr, const void* V,
                           const int32_t* lists, int list_len, int list_stride, float scale,
                           void* Os, const int32_t* pairs, const FuseArgs& fz, int* queue,
@@ -1199,19 +1200,35 @@ hipError_t launch_bf16_rj(const Shape& s, const void* Qr, const void* Kr, const 
   if constexpr (G > 1 && RJ > 0) {
     if (knorm && lists && queue) {
       if (max_len <= kTable)
-        return launch_bf16_tab<BLK, G, NBUF, kTable, RJ, false, true>(
+        return launch_bf16_tab<BLK, G, NBUF, kTable, RJ, WIDE, false, true>(
             s, Qr, Kr, V, lists, list_len, list_stride, pairs, scale, Os, fz, queue, st, DqArgs{},
             knorm);
-      return launch_bf16_tab<BLK, G, NBUF, 0, RJ, false, true>(
+      return launch_bf16_tab<BLK, G, NBUF, 0, RJ, WIDE, false, true>(
           s, Qr, Kr, V, lists, list_len, list_stride, pairs, scale, Os, fz, queue, st, DqArgs{},
           knorm);
     }
   }
   if (lists && max_len <= kTable)
-    return launch_bf16_tab<BLK, G, NBUF, kTable, RJ>(s, Qr, Kr, V, lists, list_len, list_stride,
+    return launch_bf16_tab<BLK, G, NBUF, kTable, RJ, WIDE>(s, Qr, Kr, V, lists, list_len, list_stride,
                                                      pairs, scale, Os, fz, queue, st);
-  return launch_bf16_tab<BLK, G, NBUF, 0, RJ>(s, Qr, Kr, V, lists, list_len, list_stride, pairs,
+  return launch_bf16_tab<BLK, G, NBUF, 0, RJ, WIDE>(s, Qr, Kr, V, lists, list_len, list_stride, pairs,
                                               scale, Os, fz, queue, st);
+}
+
+// Which r 64 epilogue (fuse_epilogue) a call of `groups` workgroups takes. Three per CU save rounds of the
+// chip, and a round of them lasts 4/3 as long as one of two: calls of up to three rounds of three take the
+// form with the fewer such units, longer ones the third workgroup. Forming u twice is not hidden behind
+// short lists: beyond one round it needs 384 keys per query; with 128-token blocks, where a third workgroup
+// is worth less, 2048, and 1280 in one round. Two / three per CU, us:
+//   blocks of 64: 384 groups 47.5 / 51.2, 768 96.8 / 81.6, 960 72.5 / 82.1, 2528 520 / 478, 2640 of 192 keys
+//   174 / 186;
+//   of 128: 384 groups 55.4 / 65.9, 528 (1664 keys) 113 / 101, 768 (768 keys) 73.8 / 77.6, 1584 (1664 keys)
+//   245 / 251, 2280 (2432 keys) 455 / 429, 5000 (768 keys) 424 / 469, 10240 (6528 keys) 4420 / 4298.
+bool wide_epilogue(int block, int groups, int keep) {
+  const int two = (groups + 2 * kCus - 1) / (2 * kCus), three = (groups + 3 * kCus - 1) / (3 * kCus);
+  if (three <= 3 && 4 * three > 3 * two) return false;
+  const int least = block == 64 ? (three == 1 ? 0 : 384) : (three == 1 ? 1280 : 2048);
+  return keep * block >= least;
 }
 
 // fz.r == 0: plain attention (O^s); otherwise the fused epilogue with RJ = r / 32 tiles (r 16 -> 1).
@@ -1227,8 +1244,12 @@ hipError_t launch_bf16(const Shape& s, const void* Qr, const void* Kr, const voi
   if (fz->r <= 32)
     return launch_bf16_rj<BLK, G, NBUF, 1>(s, Qr, Kr, V, lists, list_len, list_stride, scale, Os,
                                            pairs, *fz, queue, st, knorm);
-  return launch_bf16_rj<BLK, G, NBUF, 2>(s, Qr, Kr, V, lists, list_len, list_stride, scale, Os,
-                                         pairs, *fz, queue, st, knorm);
+  const int nb = num_blocks(s.N, BLK), keep = G > 1 && lists ? (list_stride - 1) / G : list_len;
+  if (wide_epilogue(BLK, (nb + G - 1) / G * s.H * s.B, keep))
+    return launch_bf16_rj<BLK, G, NBUF, 2, true>(s, Qr, Kr, V, lists, list_len, list_stride, scale, Os,
+                                                 pairs, *fz, queue, st, knorm);
+  return launch_bf16_rj<BLK, G, NBUF, 2, false>(s, Qr, Kr, V, lists, list_len, list_stride, scale, Os,
+                                                pairs, *fz, queue, st, knorm);
 }
 
 // Query blocks per workgroup when a workspace for the merged lists is given.
@@ -1358,18 +1379,18 @@ hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, cons
   fz.ld = acc.ld;
   if (block == 128) {
     if (keep <= kTable)
-      return launch_bf16_tab<128, 1, 3, kTable, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
+      return launch_bf16_tab<128, 1, 3, kTable, 0, false, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
                                                          nullptr, fz, nullptr, st, dq);
-    return launch_bf16_tab<128, 1, 3, 0, 0, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
+    return launch_bf16_tab<128, 1, 3, 0, 0, false, true>(s, Qr, Kr, V, idx, keep, keep, nullptr, scale,
                                                   nullptr, fz, nullptr, st, dq);
   }
   Groups gr;
   const hipError_t e = prepare_groups<true>(s, keep, idx, ws, 0, st, gr);
   if (e != hipSuccess) return e;
   if (gr.stride - 1 <= kTable)
-    return launch_bf16_tab<64, 2, 3, kTable, 0, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs,
+    return launch_bf16_tab<64, 2, 3, kTable, 0, false, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs,
                                                       scale, nullptr, fz, gr.queue, st, dq);
-  return launch_bf16_tab<64, 2, 3, 0, 0, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs, scale,
+  return launch_bf16_tab<64, 2, 3, 0, 0, false, true>(s, Qr, Kr, V, gr.lists, 0, gr.stride, gr.pairs, scale,
                                                nullptr, fz, gr.queue, st, dq);
 }
 

@@ -646,6 +646,32 @@ def test_combine_in_place_matches_out_of_place():
     assert torch.equal(os_copy2, res["out_fused"])
 
 
+@pytest.mark.parametrize("N,H,block,s", [(6400, 12, 128, 0.8), (6305, 13, 128, 0.8), (3003, 24, 64, 0.9)])
+def test_r64_epilogue_forms(N, H, block, s):
+    """The r 64 epilogue that forms its low-rank output twice (calls of about one round of three workgroups
+    per CU and beyond) against the one that keeps it whole (few groups): one head at a time is bitwise what
+    all heads together give with 128-token blocks, whose lists are walked as they come; with 64-token
+    blocks, where a list's start depends on the call, the two differ by the rounding of bf16
+    probabilities and of the output."""
+    grid = (1, 1, N)
+    gen = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn((1, H, N, 128), generator=gen).to(torch.bfloat16).cuda() for _ in range(3))
+    P = (torch.randn((H, 64, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16).cuda()
+    C = torch.randn((1, H, 64, 128), generator=gen).cuda()
+    lg = torch.randn((1, N), generator=gen).cuda()
+    cos, sin = R.rola_rope_tables(R.problem_of(q, grid), (44, 42, 42))
+    idx = R.rola_block_select(q, k, grid, block, s)
+    out = R.rola_sparse_attn_combine(q, k, v, grid, block, s, idx, q, P, 64, cos, sin, C, lg)
+    for h in range(0, H, 4):
+        one = [t[:, h:h + 1].contiguous() for t in (q, k, v, idx, C)]
+        want = R.rola_sparse_attn_combine(*one[:3], grid, block, s, one[3], one[0], P[h:h + 1].contiguous(),
+                                          64, cos, sin, one[4], lg)
+        if block == 128:
+            assert torch.equal(out[:, h:h + 1], want), h
+        else:
+            assert (out[:, h:h + 1].float() - want.float()).norm() <= 4e-3 * want.float().norm(), h
+
+
 def test_current_stream_handle(monkeypatch):
     """The handle passed to the library is the current stream's, also without torch's raw accessor."""
     side = torch.cuda.Stream()
