@@ -142,10 +142,17 @@ __device__ __forceinline__ void feature_tile(float (&e)[N], float (&o)[N], const
 
 // Tokens per summary workgroup. The chip holds two per CU at r = 32, one beyond, two for each chunk at r
 // = 128; the bf16 kernel takes two steps per turn. (Least length: at the 14B shape, r = 64, 2048
-// workgroups took 420 us, 1024 388: fewer partials to write and reduce.)
+// workgroups took 420 us, 1024 388: fewer partials to write and reduce.) Calls that fit the chip with one
+// step per workgroup take chunks of one step and the kernel's form without a turn of two, whose second
+// step would mostly add zeros: 2 heads of 320 tokens, r 16 10.0 -> 8.2 us, r 64 18.1 -> 14.7. Not with two
+// workgroups to a CU (304 of them, r 32: 15.3 against 13.4 in turns of two), nor past 96 partials to add
+// (116, r 16: 12.1 against 11.5).
 int summary_chunk_len(const Shape& s, int r) {
   if (!s.bf16) return chunk_tokens(s, 1024, 1024, kSummaryStep);
-  return chunk_tokens(s, 1024, r <= 32 ? 2 * kCus : r <= 64 ? kCus : kCus / 2, 2 * kSummaryStep);
+  const long slots = r <= 32 ? 2 * kCus : r <= 64 ? kCus : kCus / 2;
+  const long steps = (s.N + kSummaryStep - 1) / kSummaryStep;
+  if (steps <= 96 && s.B * s.H * steps <= (r <= 64 ? kCus : kCus / 2)) return kSummaryStep;
+  return chunk_tokens(s, 1024, slots, 2 * kSummaryStep);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -154,7 +161,8 @@ int summary_chunk_len(const Shape& s, int r) {
 // split = 2: each (b, h, chunk) is served by two workgroups, one per half of the pair tiles (r = 128
 // as two r = 64 halves: one workgroup holding all four tiles spills). The two sit eight launch
 // slots apart, i.e. on the same XCD at about the same time, so the second reads K^n and V from L2.
-template <int JT, int PHI>
+// ONE: chunks of a single step.
+template <int JT, int PHI, bool ONE>
 __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
     int N, int H, int r, int chunk_len, int n_chunks, int total, int split, int ld, int order,
     const bf16* __restrict__ Kn, const bf16* __restrict__ V, const bf16* __restrict__ Pk,
@@ -288,10 +296,12 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
       }
   };
   auto step = [&](int base, int buf, const KRows& cur, KRows& nxt, Tables& T) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the reads of the stage V goes into are done
-    issue_v(base + TOK, buf ^ 1);
-    issue_k(base + TOK, nxt);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!ONE) {
+      asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the reads of the stage V goes into are done
+      issue_v(base + TOK, buf ^ 1);
+      issue_k(base + TOK, nxt);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     bf16x8 be[JT], bo[JT];
     float last = 0.f;
 #pragma unroll
@@ -331,15 +341,23 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_tables(base + 2 * TOK, T);
+    if constexpr (!ONE) load_tables(base + 2 * TOK, T);
     asm volatile("" : "+v"(last) : : "memory");
     __builtin_amdgcn_sched_barrier(0);
     if (base + TOK > t1) {  // (uniform) V past the chunk: zero as well, 0 x inf is not 0
-      int ln;  // (the lane index made here, and one register of zeros: what is more spills)
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-      float* rows = reinterpret_cast<float*>(lds + buf * TILE + wave * 8192) + ln;
+      const int first = max(0, t1 - base - 32 * wave);  // of the wave's rows
+      if constexpr (ONE) {
+        if (first == 0) return;  // no token of this wave's in the step
+        for (int row = first + lane / 16; row < 32; row += 4)
+          *reinterpret_cast<uint4*>(lds + buf * TILE + wave * 8192 + row * (D * 2) + 16 * (lane % 16)) =
+              make_uint4(0u, 0u, 0u, 0u);
+      } else {
+        int ln;  // (the lane index made here, and one register of zeros: what is more spills)
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+        float* rows = reinterpret_cast<float*>(lds + buf * TILE + wave * 8192) + ln;
 #pragma unroll 1
-      for (int row = max(0, t1 - base - 32 * wave); row < 32; ++row) rows[row * (D / 2)] = 0.f;
+        for (int row = first; row < 32; ++row) rows[row * (D / 2)] = 0.f;
+      }
       asm volatile("" : : : "memory");
     }
     const char* Vs = lds + buf * TILE;
@@ -363,13 +381,17 @@ __global__ __launch_bounds__(256, JT == 1 ? 2 : 1) void summary_mfma_kernel(
   issue_v(t0, 0);
   issue_k(t0, ra);
   __builtin_amdgcn_sched_barrier(0);
-  load_tables(t0 + TOK, tb);
-  __builtin_amdgcn_sched_barrier(0);
-  // two steps per turn without an exit between them (it costs 60 to 130 spilled registers): the second
-  // of an odd count adds zeros to zeros
-  for (int base = t0; base < t1; base += 2 * TOK) {
-    step(base, 0, ra, rb, ta);
-    step(base + TOK, 1, rb, ra, tb);
+  if constexpr (ONE) {
+    step(t0, 0, ra, rb, ta);
+  } else {
+    load_tables(t0 + TOK, tb);
+    __builtin_amdgcn_sched_barrier(0);
+    // two steps per turn without an exit between them (it costs 60 to 130 spilled registers): the second
+    // of an odd count adds zeros to zeros
+    for (int base = t0; base < t1; base += 2 * TOK) {
+      step(base, 0, ra, rb, ta);
+      step(base + TOK, 1, rb, ra, tb);
+    }
   }
   // the last look-ahead has landed before the stages are reused below (barriers follow)
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
@@ -923,7 +945,9 @@ hipError_t summary_mfma(const Shape& s, const void* Kn, const void* V, const voi
   const int total = s.B * s.H * n_chunks;
   const int split = r > 32 * JT ? 2 : 1;  // r = 128 on the two-tile kernel
   const unsigned grid = split == 2 ? (unsigned)((total + 7) / 8 * 16) : (unsigned)total;
-  hipLaunchKernelGGL((summary_mfma_kernel<JT, PHI>), dim3(grid), dim3(256), 0, st, s.N, s.H, r,
+  const auto kernel = chunk_len == kSummaryStep ? summary_mfma_kernel<JT, PHI, true>
+                                                : summary_mfma_kernel<JT, PHI, false>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, s.N, s.H, r,
                      chunk_len, n_chunks, total, split, ld, order, (const bf16*)Kn, (const bf16*)V,
                      (const bf16*)Pk, ct, st_, part);
   return hipGetLastError();

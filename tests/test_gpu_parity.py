@@ -129,17 +129,27 @@ def test_f32_infinite_entries(d, block, N, r):
     assert bool((u[..., finite] == 0).all())
 
 
-@pytest.mark.parametrize("N", [1, 128, 130, 384, 500])
+@pytest.mark.parametrize("N,H", [(1, 2), (128, 2), (130, 2), (384, 2), (500, 2), (128, 300), (130, 140),
+                                 (384, 100), (2560, 2), (12300, 2)])
 @pytest.mark.parametrize("r", [16, 64, 128])
-def test_summary_infinite_entries(N, r):
-    """The bf16 summary takes two steps of 128 tokens per turn: what lies past the last token adds
-    nothing to C, also where the last row of V holds an infinity."""
-    grid, ch = (1, 1, N), 5
+def test_summary_infinite_entries(N, H, r):
+    """Chunks of one step of 128 tokens (few workgroups) and turns of two steps, with few and many partials:
+    C against 64 bits, up to the features' bf16 rounding; and what lies past the last token adds nothing,
+    also where the last row of V holds an infinity."""
+    grid, ch, split = (1, 1, N), 5, (44, 42, 42)
     gen = torch.Generator().manual_seed(N + r)
-    k, v = (torch.randn((1, 2, N, 128), generator=gen).to(torch.bfloat16).cuda() for _ in range(2))
-    P = (torch.randn((2, r, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16).cuda()
-    cos, sin = R.rola_rope_tables(R.problem_of(k, grid), (44, 42, 42))
+    k, v = (torch.randn((1, H, N, 128), generator=gen).to(torch.bfloat16).cuda() for _ in range(2))
+    P = (torch.randn((H, r, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16).cuda()
+    cos, sin = R.rola_rope_tables(R.problem_of(k, grid), split)
     want, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
+    h = H - 1
+    f = torch.nn.functional.silu(k[0, h].double().cpu() @ P[h].double().cpu().t())
+    e, o, c, s = f[:, 0::2], f[:, 1::2], *(t[:, :r // 2].double().cpu() for t in (cos, sin))
+    f = torch.stack((e * c - o * s, e * s + o * c), -1).flatten(-2)
+    C64 = f.t() @ v[0, h].double().cpu()
+    # each feature is rounded to bf16 once (2^-9); the rest is fp32
+    bound = 2.0 ** -8.9 * (f.abs().t() @ v[0, h].double().cpu().abs()) + 1e-6
+    assert bool(((want[0, h].double().cpu() - C64).abs() <= bound).all())
     v[..., N - 1, ch] = math.inf
     C, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
     others = torch.arange(128) != ch
