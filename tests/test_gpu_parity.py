@@ -147,8 +147,11 @@ def test_summary_infinite_entries(N, H, r):
     e, o, c, s = f[:, 0::2], f[:, 1::2], *(t[:, :r // 2].double().cpu() for t in (cos, sin))
     f = torch.stack((e * c - o * s, e * s + o * c), -1).flatten(-2)
     C64 = f.t() @ v[0, h].double().cpu()
-    # each feature is rounded to bf16 once (2^-9); the rest is fp32
-    bound = 2.0 ** -8.9 * (f.abs().t() @ v[0, h].double().cpu().abs()) + 1e-6
+    # each feature is rounded to bf16's 8 bits once (at most 2^-8 of it); features and sums are fp32: up to
+    # about 2^-20 for the feature (128 products, SiLU, rotation), 2^-24 per addition
+    pair = f.abs().unflatten(-1, (-1, 2)).sum(-1).repeat_interleave(2, -1)
+    va = v[0, h].double().cpu().abs()
+    bound = (2.0 ** -8 + N * 2.0 ** -24) * (f.abs().t() @ va) + 2.0 ** -19 * (pair.t() @ va)
     assert bool(((want[0, h].double().cpu() - C64).abs() <= bound).all())
     v[..., N - 1, ch] = math.inf
     C, _ = R.rola_lowrank_summary(k, v, P, r, cos, sin, grid)
