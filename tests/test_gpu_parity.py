@@ -274,10 +274,14 @@ def test_bf16_long_merged_lists_sampled():
 @pytest.mark.parametrize("d,split,grid,offset", [
     (128, (44, 42, 42), (3, 5, 97), (0, 0, 0)), (128, (44, 42, 42), (1, 1, 500), (1, -5, 7)),
     (128, (44, 42, 42), (37, 1, 1), (0, 0, 0)), (128, (2, 2, 124), (2, 3, 67), (0, 0, 0)),
-    (64, (28, 18, 18), (3, 3, 230), (0, 0, 0)), (64, (60, 2, 2), (5, 7, 2), (0, 2, 0))])
+    (64, (28, 18, 18), (3, 3, 230), (0, 0, 0)), (64, (60, 2, 2), (5, 7, 2), (0, 2, 0)),
+    (128, (44, 42, 42), (3, 23, 97), (0, 0, 0)), (128, (44, 42, 42), (1, 1, 5000), (1, -5, 7)),
+    (128, (44, 42, 42), (4701, 1, 1), (0, 0, 0)), (128, (2, 2, 124), (7, 11, 67), (0, 0, 0)),
+    (128, (44, 42, 42), (1, 32, 128), (0, 0, 0)), (128, (44, 42, 42), (1, 4097, 1), (0, 0, 0)),
+    (64, (28, 18, 18), (3, 13, 230), (0, 0, 0)), (64, (60, 2, 2), (53, 80, 2), (0, 2, 0))])
 def test_rope_tables_edges(d, split, grid, offset):
-    """Row groups and x pieces of the table kernel: every entry within one fp32 rounding of cos / sin
-    of the exact angle."""
+    """One thread per entry (up to 4096 tokens of d_h 128), row groups and x pieces of the shared form: every
+    entry within one fp32 rounding of cos / sin of the exact angle."""
     prob = R.problem(1, 1, math.prod(grid), d, grid, "f32")
     cos, sin = R.rola_rope_tables(prob, split, offset=offset)
     ocos, osin = O.rope_tables(*grid, split, offset=offset)
