@@ -28,13 +28,18 @@ inline int chunk_tokens(const Shape& s, long workgroups, long slots, int step) {
   const long want = heads < workgroups ? workgroups / heads : 1;
   const long least = ((s.N + want - 1) / want + step - 1) / step * step;
   long best = least, best_cost = -1;
-  for (long len = least; len <= 8 * least; len += step) {
-    const long groups = heads * ((s.N + len - 1) / len);
+  // of the lengths that give the same number of chunks the shortest costs least: one step per number, up
+  // to one chunk or 8 times the least length (every multiple of `step` was tried before, also past N: a
+  // thousand 64-bit divisions per call from 1024 heads on, three or four times per call)
+  for (long len = least; len <= 8 * least;) {
+    const long chunks = (s.N + len - 1) / len, groups = heads * chunks;
     const long cost = (groups + slots - 1) / slots * (len + step);
     if (best_cost < 0 || cost < best_cost) {
       best = len;
       best_cost = cost;
     }
+    if (chunks == 1) break;
+    len = ((s.N + chunks - 2) / (chunks - 1) + step - 1) / step * step;
   }
   return (int)best;
 }

@@ -64,6 +64,31 @@ def test_cached_sizes_are_kept_by_value():
             call()
 
 
+def test_summary_chunks_follow_the_cost_of_whole_rounds():
+    """The chunk length of the summary (seen through its workspace: one partial of r d_h + r floats per
+    chunk) against a search of every multiple of the step up to eight times the least length: the fewest
+    round-lengths of the workgroups that the chip holds, the shortest such chunk."""
+    def chunks(heads, N, r, bf16):
+        cus = 256
+        step, slots = (256, 2 * cus if r <= 32 else cus if r <= 64 else cus // 2) if bf16 else (128, 1024)
+        steps = -(-N // 128)
+        if bf16 and steps <= 96 and heads * steps <= (cus if r <= 64 else cus // 2):
+            return steps
+        want = 1024 // heads if heads < 1024 else 1
+        least = -(--(-N // want) // step) * step
+        cost = lambda n: -(-heads * -(-N // n) // slots) * (n + step)
+        return -(-N // min(range(least, 8 * least + 1, step), key=lambda n: (cost(n), n)))
+
+    for B, H in ((1, 1), (1, 3), (2, 12), (1, 40), (1, 100), (3, 171), (2, 1100)):
+        for grid in ((1, 1, 1), (3, 10, 13), (1, 16, 16), (21, 20, 20), (21, 30, 52), (19, 45, 79)):
+            for r in (16, 64, 128):
+                for dt in ("bf16", "f32"):
+                    N = grid[0] * grid[1] * grid[2]
+                    p = R.problem(B, H, N, 128, grid, dt)
+                    want = chunks(B * H, N, r, dt == "bf16") * B * H * (r * 128 + r) * 4
+                    assert R.summary_workspace_bytes(p, r) == want, (B, H, N, r, dt)
+
+
 def test_workspace_helpers():
     p = R.problem(1, 40, 75600, 128, (21, 45, 80), "bf16")
     nb = 1182
