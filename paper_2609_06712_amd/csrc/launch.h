@@ -18,22 +18,26 @@ inline int num_blocks(int N, int block) { return (N + block - 1) / block; }
 
 // Tokens per workgroup of the low-rank kernels, which give each (b, h) to several workgroups of
 // consecutive tokens: a multiple of `step`, at least what about `workgroups` workgroups give (and no
-// more of them than that), chosen so that whole rounds of the `slots` workgroups the chip holds cost
-// least, a round lasting as long as its chunk plus its set-up (about `step` tokens). Workgroups past a
-// whole round cost a round of their own, and the fewest rounds usually win: low-rank branch, r 64, 32760
-// tokens x 40 heads 425 us with the summary in 4.1 rounds, 383 in one; r 128, 12 heads 234 and 176.
+// more of them than that), chosen so that whole rounds of `slots` workgroups cost least, a round lasting
+// as long as its chunk plus its set-up (about `step` tokens). A round is one workgroup per CU, also where a
+// CU holds two or three: they share its bandwidth and its SIMDs, so what counts is the CU with the most of
+// them (summary, r 32, 36 heads of 2079 tokens: 324 workgroups 20.4 us, 180 of twice the length 16.4; readout,
+// r 16, 12 heads of 8400: 528 22.3, 396 19.9, 228 18.9; 40 heads of 32760, r 64: the branch 425 us with the
+// summary in 4.1 rounds, 383 in one). `alone`: what a token costs, in sixteenths, in a round that a CU which
+// could hold `per_cu` workgroups has to itself, with nothing to hide its latencies.
 constexpr int kCus = 256;
-inline int chunk_tokens(const Shape& s, long workgroups, long slots, int step) {
+inline int chunk_tokens(const Shape& s, long workgroups, long slots, int step, int per_cu = 1,
+                        int alone = 16) {
   const long heads = (long)s.B * s.H;
   const long want = heads < workgroups ? workgroups / heads : 1;
   const long least = ((s.N + want - 1) / want + step - 1) / step * step;
   long best = least, best_cost = -1;
-  // of the lengths that give the same number of chunks the shortest costs least: one step per number, up
-  // to one chunk or 8 times the least length (every multiple of `step` was tried before, also past N: a
-  // thousand 64-bit divisions per call from 1024 heads on, three or four times per call)
+  // of the lengths that give the same number of chunks the shortest costs least: one turn per number, up
+  // to one chunk or 8 times the least length (a turn per multiple of `step` came to a thousand 64-bit
+  // divisions per call with 1024 heads)
   for (long len = least; len <= 8 * least;) {
-    const long chunks = (s.N + len - 1) / len, groups = heads * chunks;
-    const long cost = (groups + slots - 1) / slots * (len + step);
+    const long chunks = (s.N + len - 1) / len, rounds = (heads * chunks + slots - 1) / slots;
+    const long cost = (len + step) * (16 * rounds + (per_cu > 1 && rounds % per_cu == 1 ? alone - 16 : 0));
     if (best_cost < 0 || cost < best_cost) {
       best = len;
       best_cost = cost;

@@ -140,18 +140,15 @@ __device__ __forceinline__ void feature_tile(float (&e)[N], float (&o)[N], const
   if (PHI == kPaper || order == kRopeOutside) rotate();
 }
 
-// Tokens per summary workgroup. The chip holds two per CU at r = 32, one beyond, two for each chunk at r
-// = 128; the bf16 kernel takes two steps per turn. (Least length: at the 14B shape, r = 64, 2048
-// workgroups took 420 us, 1024 388: fewer partials to write and reduce.) Calls that fit the chip with one
-// step per workgroup take chunks of one step and the kernel's form without a turn of two, whose second
-// step would mostly add zeros: 2 heads of 320 tokens, r 16 10.0 -> 8.2 us, r 64 18.1 -> 14.7. Not with two
-// workgroups to a CU (304 of them, r 32: 15.3 against 13.4 in turns of two), nor past 96 partials to add
-// (116, r 16: 12.1 against 11.5).
+// Tokens per summary workgroup: one per CU to a round, two for each chunk at r = 128; the bf16 kernel takes
+// two steps per turn. (Least length: at the 14B shape, r = 64, 2048 workgroups took 420 us, 1024 388: fewer
+// partials to write and reduce.) Calls that fit the chip with one step per workgroup take chunks of one step
+// and the kernel's form without a turn of two, whose second step would mostly add zeros: 2 heads of 320
+// tokens, r 16 10.0 -> 8.2 us, r 64 18.1 -> 14.7. Not past 96 partials to add (116, r 16: 12.1 against 11.5).
 int summary_chunk_len(const Shape& s, int r) {
   if (!s.bf16) return chunk_tokens(s, 1024, 1024, kSummaryStep);
-  const long slots = r <= 32 ? 2 * kCus : r <= 64 ? kCus : kCus / 2;
-  const long steps = (s.N + kSummaryStep - 1) / kSummaryStep;
-  if (steps <= 96 && s.B * s.H * steps <= (r <= 64 ? kCus : kCus / 2)) return kSummaryStep;
+  const long slots = r <= 64 ? kCus : kCus / 2, steps = (s.N + kSummaryStep - 1) / kSummaryStep;
+  if (steps <= 96 && s.B * s.H * steps <= slots) return kSummaryStep;
   return chunk_tokens(s, 1024, slots, 2 * kSummaryStep);
 }
 
@@ -971,9 +968,11 @@ hipError_t readout_mfma(const Shape& s, const void* Qn, const void* Pq, int r, c
                         const float* st_, int ld, int order, const float* C, float eps_lr,
                         const void* Os, const float* logits, float eps, void* Out, hipStream_t st) {
   constexpr int threads = 64 * readout_waves<JT>();
-  // workgroups per CU by registers (LDS at r = 128)
-  constexpr int per_cu = JT == 1 ? 3 : JT == 2 ? 2 : 1;
-  const int chunk_len = chunk_tokens(s, kReadoutWorkgroups, per_cu * kCus, threads / 4);
+  // workgroups per CU by registers (LDS at r = 128), and what four waves alone cost (40 heads of 15876
+  // tokens, r 32: 113 us in 240 workgroups, 105 in 1000; r 64 125 in 240, 116 in 480; 6 of 39732, r 64: 46.7
+  // in 750, 43.4 in 468)
+  constexpr int per_cu = JT == 1 ? 3 : JT == 2 ? 2 : 1, alone = JT == 1 ? 17 : 19;
+  const int chunk_len = chunk_tokens(s, kReadoutWorkgroups, kCus, threads / 4, per_cu, alone);
   const int n_chunks = (s.N + chunk_len - 1) / chunk_len;
   const int total = s.B * s.H * n_chunks;
   hipLaunchKernelGGL((readout_mfma_kernel<JT, COMBINE, PHI>), dim3(total), dim3(threads), 0, st, s.N,

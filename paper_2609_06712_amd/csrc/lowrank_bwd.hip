@@ -462,9 +462,10 @@ __global__ __launch_bounds__(256) void lr_bwd_logit_kernel(long BN, int N, int H
   dlogits[e] = s;
 }
 
-// Most workgroups of each pass. The query side and the r > 32 key side hold one per CU; each stages P and
-// M anew and leaves partials to add (14B 720p layer, r 64, whole call: 4096 2.96 ms, 2048 2.84 ms, 1024
-// 2.77 ms; whole rounds of 256: see chunk_tokens).
+// Most workgroups of each pass. Each stages P and M anew and leaves partials to add (14B 720p layer, r 64,
+// whole call: 4096 2.96 ms, 2048 2.84 ms, 1024 2.77 ms). One per CU to a round for either side and every
+// rank, as registers and LDS allow at r 64 on the query side; where more fit they gain nothing (r 32, 12 heads
+// of 32760 tokens: 252 workgroups 314 us, 480 324, 768 320).
 constexpr long kLrBwdWorkgroups = 1024;
 int lr_bwd_chunk_len(const Shape& s) { return chunk_tokens(s, kLrBwdWorkgroups, kCus, kStep); }
 

@@ -70,9 +70,9 @@ def test_summary_chunks_follow_the_cost_of_whole_rounds():
     round-lengths of the workgroups that the chip holds, the shortest such chunk."""
     def chunks(heads, N, r, bf16):
         cus = 256
-        step, slots = (256, 2 * cus if r <= 32 else cus if r <= 64 else cus // 2) if bf16 else (128, 1024)
+        step, slots = (256, cus if r <= 64 else cus // 2) if bf16 else (128, 1024)
         steps = -(-N // 128)
-        if bf16 and steps <= 96 and heads * steps <= (cus if r <= 64 else cus // 2):
+        if bf16 and steps <= 96 and heads * steps <= slots:
             return steps
         want = 1024 // heads if heads < 1024 else 1
         least = -(--(-N // want) // step) * step
