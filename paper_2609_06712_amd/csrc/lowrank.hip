@@ -25,6 +25,10 @@
 #include "common.h"
 #include "launch.h"
 #include "reduce.h"
+#define MAP_FN __device__ __forceinline__
+#define MAP_RCP __builtin_amdgcn_rcpf
+#define MAP_EXP __expf
+#include "feature_maps.h"
 
 namespace rola {
 namespace {
@@ -78,38 +82,6 @@ __device__ __forceinline__ void feature_pair(float& e, float& o, float c, float 
 // a switch and a divergent erff / tanhf per value lets the values of a tile overlap: readout at
 // r 128 with GELU inside, 39689 tokens x 12 heads: 383 us with the per-value form, 132 now (with the longer chunks).
 constexpr int kPaper = -1;
-
-// GELU x Phi(x) from erfc(z) = t P(t) exp(-z^2), z = |x| / sqrt 2, t = 1 / (1 + 0.4 z): P is a degree-8
-// minimax fit of erfc's scaled form on z in [0, 5] (relative error 1.5e-8 before rounding), which keeps
-// the lower tail relatively accurate where 1 + erf cancels.
-__device__ __forceinline__ float gelu_fast(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, z, 1.0f));
-  float p = 0.02058017541f;
-  p = fmaf(p, t, -0.0333637342f);
-  p = fmaf(p, t, -0.1531883735f);
-  p = fmaf(p, t, 0.3820583653f);
-  p = fmaf(p, t, -0.143041639f);
-  p = fmaf(p, t, 0.2988953582f);
-  p = fmaf(p, t, 0.1714113825f);
-  p = fmaf(p, t, 0.2313518033f);
-  p = fmaf(p, t, 0.2252966763f);
-  const float tail = 0.5f * t * p * __expf(-z * z);  // 1 - Phi(|x|)
-  return x * (x >= 0.f ? 1.0f - tail : tail);
-}
-
-// tanh: x + x^3 Q(x^2) (degree-4 minimax, 3e-9 relative) up to 0.6, 1 - 2 / (1 + e^2|x|) beyond.
-__device__ __forceinline__ float tanh_fast(float x) {
-  const float a = fabsf(x), u = x * x;
-  float q = -0.005905868674f;
-  q = fmaf(q, u, 0.02080538484f);
-  q = fmaf(q, u, -0.05378668365f);
-  q = fmaf(q, u, 0.1333195824f);
-  q = fmaf(q, u, -0.3333329927f);
-  const float small = fmaf(x * u, q, x);
-  const float large = 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * a));
-  return a < 0.6f ? small : copysignf(large, x);
-}
 
 template <int PHI>
 __device__ __forceinline__ float feature_map(float x) {
