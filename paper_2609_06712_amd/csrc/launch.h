@@ -16,6 +16,8 @@ struct Shape {
 
 inline int num_blocks(int N, int block) { return (N + block - 1) / block; }
 
+constexpr int kMaxBlocks = 8192;  // blocks per head that the calls with a block size take
+
 // Tokens per workgroup of the low-rank kernels, which give each (b, h) to several workgroups of
 // consecutive tokens: a multiple of `step`, at least what about `workgroups` workgroups give (and no
 // more of them than that), chosen so that whole rounds of `slots` workgroups cost least, a round lasting
@@ -145,10 +147,8 @@ hipError_t launch_sparse_dq(const Shape& s, const void* Qr, const void* Kr, cons
                             const void* lseD, const GradTables& acc, float* dQ, void* ws,
                             hipStream_t st);
 
-// sparse_bwd.hip: gradients of the block-sparse attention (bf16, d 128, block 64 or 128, at most
-// kBwdMaxBlocks blocks per head: the transposed lists are built through one LDS word per block);
-// fp32 outputs; ws: sparse_backward_workspace_bytes(s, block, keep), 0 when unsupported.
-constexpr int kBwdMaxBlocks = 16384;
+// sparse_bwd.hip: gradients of the block-sparse attention (bf16, d 128, block 64 or 128; the transposed
+// lists are built through one LDS word per block of a head); fp32 outputs; ws: sparse_backward_workspace_bytes(s, block, keep), 0 when unsupported.
 size_t sparse_backward_workspace_bytes(const Shape& s, int block, int keep);
 hipError_t launch_sparse_backward(const Shape& s, const void* Qr, const void* Kr, const void* V,
                                   int block, int keep, const int32_t* idx, float scale,

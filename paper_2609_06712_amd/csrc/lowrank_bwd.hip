@@ -51,7 +51,8 @@ __device__ __forceinline__ float silu_grad(float y) {  // d/dy y sigmoid(y)
 // their tiles (token-major) to LDS and every wave contracts the step's 64 tokens for its own 32
 // channels, reading the operands with ds_read_b64_tr_b16 (token-major rows -> one lane per column).
 // fp32 operands enter as bf16 hi + lo pairs (three products, or two against exact bf16 data), which
-// keeps them to about 2^-16 relative. Partials per chunk as in the plain kernels.
+// keeps them to about 2^-16 relative. Each workgroup leaves its chunk's sums as r x 128 floats
+// per outer product, part[(b H + h) n_chunks + chunk], which launch_chunk_reduce adds in chunk order.
 constexpr int kStep = 64;  // tokens per workgroup step
 // LDS tiles hold their rows unpadded, the 16-byte chunks of a row swizzled by the row's bits so that
 // row-wise and token-major accesses do not conflict, and the transposing reads of P and M, which use one

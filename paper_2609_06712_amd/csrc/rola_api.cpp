@@ -71,8 +71,8 @@ rola_status check_block(const rola::Shape& s, int32_t block, const char* fn) {
     return fail(ROLA_ERR_UNSUPPORTED, "%s: block=%d (built: 32, 64, 128)", fn, block);
   if (s.bf16 && block == 32)
     return fail(ROLA_ERR_UNSUPPORTED, "%s: bf16 path is built for block 64 and 128", fn);
-  if (rola::num_blocks(s.N, block) > 8192)
-    return fail(ROLA_ERR_UNSUPPORTED, "%s: more than 8192 blocks", fn);
+  if (rola::num_blocks(s.N, block) > rola::kMaxBlocks)
+    return fail(ROLA_ERR_UNSUPPORTED, "%s: more than %d blocks", fn, rola::kMaxBlocks);
   if ((long long)rola::num_blocks(s.N, block) * s.H * s.B > 0x7fffffffll)
     return fail(ROLA_ERR_UNSUPPORTED, "%s: too many blocks", fn);
   return ROLA_OK;
@@ -484,9 +484,6 @@ static rola_status sparse_backward(const rola_problem* p, const void* Qr, const 
   TRY(check_block(s, block, fn));
   TRY(check_sparsity(sparsity, fn));
   if (!s.bf16) return fail(ROLA_ERR_UNSUPPORTED, "%s: built for the bf16 path", fn);
-  if (rola::num_blocks(s.N, block) > rola::kBwdMaxBlocks)
-    return fail(ROLA_ERR_UNSUPPORTED, "%s: %d blocks per head, at most %d", fn,
-                rola::num_blocks(s.N, block), rola::kBwdMaxBlocks);
   const Named ptrs[] = {{Qr, "Qr"}, {Kr, "Kr"}, {V, "V"}, {blk_idx, "blk_idx"}, {Os, "Os"},
                         {lse, "lse"}, {dOs, "dOs"}, {dQ, "dQ"}, {dK, "dK"}, {dV, "dV"}, {ws, "ws"}};
   for (const Named& q : ptrs)

@@ -186,7 +186,7 @@ __host__ __device__ inline int dkv_place(int wg, int heads, int nb) {
   return d < heads % kNumXcd * nb ? kNumXcd * whole + d : -1;
 }
 
-template <int BLK, int NBUF>
+template <int BLK>
 __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void sparse_dkv_kernel(
     int N, int nb, int heads, const int32_t* __restrict__ rev, float scale_log2, float scale,
@@ -199,8 +199,10 @@ void sparse_dkv_kernel(
   constexpr int DPW = 2 * (TILE / 1024) / NW;  // 1 KB tile loads per wave and step
   constexpr int SUBS = BLK / kBSub;            // steps per query block
   constexpr int PBUF = NKW * 2048;             // P of a step, fp16: per key tile 16 values a lane
+  constexpr int NBUF = kDkvNbuf;
   constexpr int AHEAD = NBUF - 3;              // stages in flight: three are read (one back, one on)
-  static_assert(DPW >= 1 && 2 * (TILE / 1024) % NW == 0 && AHEAD >= 1, "64- or 128-key blocks");
+  static_assert(DPW >= 1 && 2 * (TILE / 1024) % NW == 0, "64- or 128-key blocks");
+  static_assert(AHEAD == 1, "every load in flight is the next step's: the waits below are for all of them");
   __shared__ __attribute__((aligned(1024))) char lds[NBUF * STAGE + 2 * PBUF];
 
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
@@ -292,15 +294,7 @@ void sparse_dkv_kernel(
         // the compiler sinks the scalar loads behind the barrier).
         int qcur = query0(max(0, min(t, T - 1))), qiss = query0(max(0, min(issued, T - 1)));
         asm volatile("" : "+s"(qcur), "+s"(qiss));
-        if (AHEAD > 1 && issued == t + 1 + AHEAD) {  // stage t + 1 has landed
-          constexpr int a0 = (DPW + 1) * (AHEAD - 1), a1 = DPW * (AHEAD - 1);
-          if (wave == 0)
-            __builtin_amdgcn_s_waitcnt((a0 & 15) | ((a0 >> 4) << 14) | (7 << 4) | (15 << 8));
-          else
-            __builtin_amdgcn_s_waitcnt((a1 & 15) | ((a1 >> 4) << 14) | (7 << 4) | (15 << 8));
-        } else {
-          __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-        }
+        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0): stage t + 1 has landed
         __syncthreads();
         if (issued < T) issue(qiss, (b + 1 + AHEAD) % NBUF), ++issued;
         const int step = t - ROLE;
@@ -404,6 +398,8 @@ BwdWs bwd_layout(const Shape& s, int block, int keep) {
           align256(sparse_workspace_bytes(s, block, keep))};
 }
 
+static_assert(kMaxBlocks * sizeof(int32_t) <= 32768, "one LDS word per block of a head, beside the kernels' own");
+
 template <int BLK>
 hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void* V, int keep,
                       const int32_t* idx, float scale, const void* Os, const float* lse,
@@ -432,7 +428,7 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
   const hipError_t e2 = launch_sparse_dq(s, Qr, Kr, V, BLK, keep, idx, scale, dOs, lseD, acc, dQ,
                                          (char*)ws + lay.lsed + lay.bits + lay.rev + lay.order, st);
   if (e2 != hipSuccess) return e2;
-  hipLaunchKernelGGL((sparse_dkv_kernel<BLK, kDkvNbuf>), dim3(dkv_grid((int)heads, nb)), dim3(BLK * 4), 0,
+  hipLaunchKernelGGL(sparse_dkv_kernel<BLK>, dim3(dkv_grid((int)heads, nb)), dim3(BLK * 4), 0,
                      st, s.N, nb, (int)heads,
                      (const int32_t*)rev, sl, scale, (const bf16*)Qr, (const bf16*)Kr,
                      (const bf16*)V, (const bf16*)dOs, (const float2*)lseD, (const int32_t*)order,
@@ -443,9 +439,7 @@ hipError_t launch_bwd(const Shape& s, const void* Qr, const void* Kr, const void
 }  // namespace
 
 size_t sparse_backward_workspace_bytes(const Shape& s, int block, int keep) {
-  if (!s.bf16 || s.d != 128 || (block != 64 && block != 128) ||
-      num_blocks(s.N, block) > kBwdMaxBlocks)
-    return 0;
+  if (!s.bf16 || s.d != 128 || (block != 64 && block != 128)) return 0;
   const BwdWs w = bwd_layout(s, block, keep);
   return w.lsed + w.bits + w.rev + w.order + w.dq;
 }
