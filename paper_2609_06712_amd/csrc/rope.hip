@@ -75,11 +75,10 @@ __global__ __launch_bounds__(256) void rope_tables_kernel(int rows, int Hs, int 
 }
 
 // Xr = R(X): one thread per 4 pairs (8 elements) of a token, for `per` heads: the token's table entries
-// (twice the bytes of a bf16 row) are read once for them, four heads' rows are in flight at a time, and
+// (twice the bytes of a bf16 row) are read once for them, BATCH heads' rows are in flight at a time, and
 // the indices are shifts (a 64-bit division per thread and a table read per head made the bf16
 // rotation of 32760 tokens x 12 heads 50 us for 201 MB; 37 now).
-constexpr int kRopeBatch = 4;
-template <typename T>
+template <typename T, int BATCH>
 __global__ __launch_bounds__(256) void rope_apply_kernel(int heads, int per, int N, int shift, int ld,
                                                          const T* __restrict__ X,
                                                          const float* __restrict__ cos_tab,
@@ -94,12 +93,12 @@ __global__ __launch_bounds__(256) void rope_apply_kernel(int heads, int per, int
   const float4 s = *reinterpret_cast<const float4*>(sin_tab + n * ld + g * 4);
   const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {s.x, s.y, s.z, s.w};
   const int h0 = blockIdx.y * per, h1 = min(heads, h0 + per);
-  for (int h = h0; h < h1; h += kRopeBatch) {
-    float v[kRopeBatch][8];
+  for (int h = h0; h < h1; h += BATCH) {
+    float v[BATCH][8];
 #pragma unroll
-    for (int u = 0; u < kRopeBatch; ++u) load8(X + (min(h + u, h1 - 1) * pieces + i) * 8, v[u]);
+    for (int u = 0; u < BATCH; ++u) load8(X + (min(h + u, h1 - 1) * pieces + i) * 8, v[u]);
 #pragma unroll
-    for (int u = 0; u < kRopeBatch; ++u) {
+    for (int u = 0; u < BATCH; ++u) {
       if (h + u >= h1) break;
       float o[8];
 #pragma unroll
@@ -183,12 +182,19 @@ hipError_t launch_rope_apply(const Shape& s, const void* X, const float* cos_tab
   int per = 8;
   while (per > 1 && (long)gx * ((heads + per - 1) / per) < 4 * kCus) per /= 2;
   const dim3 grid(gx, (unsigned)((heads + per - 1) / per));
+  const auto launch = [&](auto zero) {
+    using T = decltype(zero);
+    const int most = heads < per ? heads : per;  // rows that a thread has to load
+    const auto kernel = most == 1   ? rope_apply_kernel<T, 1>
+                        : most == 2 ? rope_apply_kernel<T, 2>
+                                    : rope_apply_kernel<T, 4>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, heads, per, s.N, shift, ld, (const T*)X, cos_tab,
+                       sin_tab, (T*)Xr);
+  };
   if (s.bf16)
-    hipLaunchKernelGGL(rope_apply_kernel<bf16>, grid, dim3(256), 0, st, heads, per, s.N, shift, ld,
-                       (const bf16*)X, cos_tab, sin_tab, (bf16*)Xr);
+    launch(bf16{});
   else
-    hipLaunchKernelGGL(rope_apply_kernel<float>, grid, dim3(256), 0, st, heads, per, s.N, shift, ld,
-                       (const float*)X, cos_tab, sin_tab, (float*)Xr);
+    launch(0.f);
   return hipGetLastError();
 }
 

@@ -619,11 +619,11 @@ struct AttnArgs {
 // BOUND (merged lists, G > 1): the softmax reference of each wave is the bound on its scores that
 // the key-block norms give, where that bound is small enough (see the prologue).
 //
-// Three four-wave workgroups fit a CU (LDS, 168 VGPRs). Every such variant reaches that; where the
-// compiler is told, it orders the code for it (the r 64 epilogue that keeps u whole holds two): the fused layer with 128-token blocks needs the bound (12
-// heads of 32,760, r 32: 909 -> 844 us), dense attention (no list) gains by it (8,400 keys 1308 -> 1293,
-// 32,760 keys 5856 -> 5796), the static walk over lists without an epilogue loses (128-token blocks,
-// 20 heads of 32,175: 1697 with two, 1710 with three).
+// Three four-wave workgroups fit a CU (LDS, 168 VGPRs). Every such variant reaches that but the r 64 epilogue
+// that keeps u whole (two); where the compiler is told, it orders the code for it: the fused layer with
+// 128-token blocks needs the bound (12 heads of 32,760, r 32: 909 -> 844 us), dense attention (no list) gains
+// by it (8,400 keys 1308 -> 1293, 32,760 keys 5856 -> 5796), the static walk over lists without an epilogue
+// loses (128-token blocks, 20 heads of 32,175: 1697 with two, 1710 with three).
 template <int BLK, int G, int NBUF, int TAB, int RJ, bool WIDE, bool QUEUE, bool DQ = false,
           bool BOUND = false>
 __global__ __launch_bounds__(G * BLK * 2,
