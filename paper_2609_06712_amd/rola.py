@@ -159,13 +159,15 @@ _DTYPE_CODES = {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16}
 def _prob(B, H, N, d_h, grid, dtype) -> Problem:
     """problem() for a call's own use (shared: not to be written)."""
     T, Hs, Ws = grid
-    make = (_cached_problem if type(H) is type(d_h) is type(T) is type(Hs) is type(Ws) is int else Problem)
-    return make(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[dtype])
+    if type(H) is type(d_h) is type(T) is type(Hs) is type(Ws) is int:
+        return _cached_problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[dtype])
+    return Problem(B, H, N, d_h, T, Hs, Ws, _DTYPE_CODES[dtype])
 
 
 def _prob_of(x: torch.Tensor, grid) -> Problem:
-    B, H, N, d = x.shape
-    return _prob(B, H, N, d, grid, x.dtype)
+    T, Hs, Ws = grid
+    make = _cached_problem if type(T) is type(Hs) is type(Ws) is int else Problem
+    return make(*x.shape, T, Hs, Ws, _DTYPE_CODES[x.dtype])
 
 
 # ---- argument checks ------------------------------------------------------------------------------
